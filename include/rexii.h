@@ -160,15 +160,19 @@ typedef struct rexii_report {
                                (capped at 1e-2)                             */
     double max_rel_residual; /* largest final FP64 relative residual        */
     double seconds;          /* host wall time of the call (seconds_total)  */
-    double alg_bytes;        /* algorithmic HBM bytes of the Krylov kernels */
+    double alg_bytes;        /* algorithmic HBM bytes of the Krylov kernels
+                                (COCG steps that hold their vectors on the
+                                chip count the bytes the streaming pass
+                                moves for them)                             */
     int32_t stagnated;       /* FP64 solves stopped at their residual floor
                                above their tolerance (their residuals enter
                                err_bound)                                  */
     int32_t slots;           /* concurrent solves the engine ran with        */
     /* with opts.profile = 1: launches and summed HIP-event time of the COCG
-     * pass kernel, and the algorithmic bytes of those launches (a pass reads
-     * x, r, p and writes them once: 6 complex values per grid point and
-     * live solve; 3 for the first pass after an FP64 residual) */
+     * pass kernel (of the kernel that runs the inner steps on the chip where
+     * the grid allows it), and the algorithmic bytes of those launches (a
+     * pass reads x, r, p and writes them once: 6 complex values per grid
+     * point and live solve; 3 for the first pass after an FP64 residual) */
     int64_t kernel_launches;
     double kernel_ms;
     double kernel_bytes;

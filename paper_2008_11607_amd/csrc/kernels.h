@@ -172,7 +172,7 @@ struct Eng {
                          // [1] their common tile count (0 if they differ;
                          // bit 30 set when every slot works, so the list is
                          // 0, 1, ..., B-1), [2..] working slot indices
-  int* counter;          // [4] host-visible counts
+  int* counter;          // [4] host-visible counts ([2]: a chip group gave up)
   int2* items;           // [B * (cap_blk + 7)] (slot, tile): 8 band lists when tile counts differ
                          // (filled when the working slots' tile counts differ)
   double* part;          // [B][cap_blk][kNDots]
@@ -190,6 +190,33 @@ struct Eng {
   int ystride;           // row stride of yout (points)
   int pad_e;
   int* dbg;              // [16] consistency counters (debug builds only)
+  int* chip_ctl;         // control words of the chip kernel, zeroed by k_assign
+  int chip_words;        // their number; > 0: inner steps run in the chip
+                         // kernel, the passes leave kInner slots alone
+  int pad_c;
+};
+
+// A launch that keeps the slots' inner iterations on the chip
+// (kernels_chip.hip): groups of G blocks, one slot at a time per group.
+constexpr int kChipRec = 16;       // words of a block's record (one 128-byte line)
+constexpr int kChipCtlHead = 32;   // control words before the groups'
+constexpr int kChipCtlGroup = 32;  // control words per group
+constexpr int chip_pitch(int rt) { return rt | 1; }  // LDS places of an item's rows
+constexpr int kChipMaxLds = 152 * 1024;
+constexpr int kChipMaxG = 64;      // largest group timed
+struct Chip {
+  int nx, ny;        // the slots' common grid
+  int nch, L;        // chains of rows y, y + 2, ... and their length
+  int G, Gc, Sc;     // blocks per group, strips per chain, column segments per strip
+  int K;             // inner steps of a slot per launch, at most
+  int nt, lds;       // threads and dynamic LDS bytes of a block
+  int ngroups;
+  int variant;       // index of the kernel (chip_variants)
+  int ctl_words;
+  int gpx;           // groups per XCD (a group then lies on one), or 0
+  unsigned long long* rec;  // [ngroups][3][G][kChipRec] partial sums
+  void* ring;               // [ngroups][3][G][2][nx] edge rows of q
+  int* ctl;                 // [ctl_words], zero before each launch (k_assign)
 };
 
 // Per-pole bilinear dot of the depth derivative (adjoint): for a forward
@@ -207,6 +234,16 @@ struct AdjDot {
 
 template <typename T>
 void launch_pass(const Eng& e, int grid, hipStream_t s);
+// Kernels of kernels_chip.hip by inner precision: items per thread, chain
+// rows per item, largest block.
+struct ChipVariant {
+  int Q, RT, max_nt;
+};
+int chip_variants(int is_f32);
+ChipVariant chip_variant(int is_f32, int k);
+// blocks of nt threads and lds bytes that fit one CU
+int chip_occupancy(int is_f32, int k, int nt, int lds);
+void launch_chip(const Eng& e, const Chip& c, hipStream_t s);
 // Variable-depth (flux form) shifted systems, per pole:
 //   K eta = (L_H + gamma C_H - zeta) eta = sc (eta0 + a1 D_H + a2 Z_H),
 //   L_H = dx(H dx .) + dy(H dy .),  C_H = dx(H dy .) - dy(H dx .),

@@ -478,6 +478,7 @@ __device__ __forceinline__ void cocg_pass(const Eng& e) {
     if (!work_item(e, m, w, it)) continue;
     const SlotCtl c = load_ctl(&e.slots[it.slot]);
     if (c.status == kInner) {
+      if (e.chip_words > 0) continue;  // k_chip
       T a[kNDots];
 #pragma unroll
       for (int k = 0; k < kNDots; ++k) a[k] = T(0);
@@ -516,6 +517,7 @@ __global__ __launch_bounds__(kSNT) void k_pass_scalars(Eng e) {
   const int status = ldc(&S->status);
   const bool outer = (status == kOuterPending || status == kInnerDone);
   if (status != kInner && status != kPrime && !outer) return;
+  if (status == kInner && e.chip_words > 0) return;  // k_chip
   double tot[kNDots];
   slot_sums_n<kNDots>(e.part + size_t(blockIdx.x) * e.cap_blk * kNDots, ldc(&S->nblk), tot, red);
   if (threadIdx.x != 0) return;
@@ -802,6 +804,7 @@ __global__ __launch_bounds__(kSchedNT) void k_assign(Eng e) {
   __shared__ int s_bo[kMaxSlots];
   __shared__ int s_min, s_max;
   const int next0 = ldc(e.next);
+  for (int k = threadIdx.x; k < e.chip_words; k += kSchedNT) e.chip_ctl[k] = 0;
 #ifdef REXII_DEBUG_CHECKS
   if (threadIdx.x == 0) {
     int fin = 0;

@@ -644,12 +644,88 @@ static size_t problem_bytes(const Problem& p) {
   return al256(2 * p.n() * 8) + al256(3 * p.n() * 8) + al256((8 + 256) * 8) + al256(p.n() * 8) + al256(p.n() * 4);
 }
 
+// Launch shape of the chip kernel for slots on an nx x ny grid; false where
+// no variant holds a slot (the passes then stream it).
+//   A group of G blocks holds one slot: G = 1 with every chain in the block,
+//   or G = nch Gc with Gc strips per chain.  A thread takes Q column segments
+//   of RT (or RT - 1) chain rows, so RT = ceil(L / (Gc Sc)).
+// Among the shapes that fit, the least estimated time of a step times the
+// turns that the queue takes.  The estimate, in cycles, follows steps timed
+// on MI355X: a wavefront issues about 50 VALU instructions a point and 350 a
+// step (4 cycles each), and a step waits beyond that 2300 cycles in a group
+// of one (3.5 us a step for 64^2 in FP64, 8 rows a thread), 5400 + 40 G on
+// one XCD (4.9 us for 256^2 in FP64 with G = 16, 6.6 us for 512^2 in FP32
+// with G = 32 and 16 rows), 6000 + 110 G across XCDs (8.1 us for 512^2 in
+// FP64 with G = 64).
+static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* out) {
+  const int nch = (ny % 2 == 0) ? 2 : 1, L = ny / nch;
+  const int eb = is_f32 ? 8 : 16;
+  double best = 0.0;
+  for (int k = 0; k < chip_variants(is_f32); ++k) {
+    const ChipVariant v = chip_variant(is_f32, k);
+    for (int segs = 1; segs * nx <= v.Q * v.max_nt; ++segs) {
+      const int nt = ((segs * nx + v.Q - 1) / v.Q + 63) / 64 * 64;
+      if (nt > v.max_nt) break;
+      const size_t lds = size_t(segs) * nx * chip_pitch(v.RT) * eb;
+      if (lds > size_t(kChipMaxLds)) break;
+      int occ = -1;
+      for (int one = 0; one < 2; ++one) {
+        // the chains in one block, or the fewest strips that give RT rows
+        int G = 1, Gc = 1, Sc = segs / nch;
+        if (!one) {
+          Sc = segs;
+          Gc = (L + segs * v.RT - 1) / (segs * v.RT);
+          G = nch * Gc;
+          if (G == 1) continue;
+        } else if (segs % nch) {
+          continue;
+        }
+        if ((L + Gc * Sc - 1) / (Gc * Sc) != v.RT || L < Gc * Sc || G > kChipMaxG) continue;
+        if (occ < 0) occ = chip_occupancy(is_f32, k, nt, int(lds));
+        if (occ < 1) break;
+        // on one XCD where the queue fills every XCD's groups
+        const int gpx = (G > 1) ? (cus / 8) * occ / G : 0;
+        const bool onx = gpx > 0 && nsolves >= 8 * gpx;
+        const int groups = onx ? 8 * gpx : std::min(cus * occ / G, std::max(1, nsolves));
+        if (groups < 1) continue;
+        const int per_cu = (groups * G + cus - 1) / cus;
+        const double cyc = v.Q * v.RT * 50.0 + 350.0;
+        const double chain = ((nt / 64 + 3) / 4) * 4.0 * cyc +
+                             (G == 1 ? 2300.0 : onx ? 5400.0 + 40.0 * G : 6000.0 + 110.0 * G);
+        const double t = std::max(double(per_cu) * (nt / 64) * cyc, chain) * std::max(1.0, double(nsolves) / groups);
+        if (best == 0.0 || t < best) {
+          best = t;
+          out->nx = nx;
+          out->ny = ny;
+          out->nch = nch;
+          out->L = L;
+          out->G = G;
+          out->Gc = Gc;
+          out->Sc = Sc;
+          out->nt = nt;
+          out->lds = int(lds);
+          out->ngroups = groups;
+          out->gpx = onx ? gpx : 0;
+          out->variant = k;
+        }
+      }
+    }
+  }
+  if (best == 0.0) return false;
+  // steps of one launch: loading and storing a slot's vectors costs about a
+  // step of the streaming passes, a launch's last groups wait for each other
+  out->K = 256;
+  out->ctl_words = kChipCtlHead + kChipCtlGroup * out->ngroups;
+  return true;
+}
+
 struct Engine {
   hipStream_t st;
   EngineSize z;
   int precision = 0, chunk = 16, grid = 0;
   bool profile = false;
   Eng e{};
+  Chip chip{};             // the chip kernel's launch (e.chip_words > 0)
   int* hcount = nullptr;   // pinned host mirror of the counters
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
@@ -677,6 +753,7 @@ struct Engine {
   explicit Engine(hipStream_t s) : st(s) {
     // every byte of e (padding included) is defined: e keys the graph cache
     std::memset(static_cast<void*>(&e), 0, sizeof(e));
+    std::memset(static_cast<void*>(&chip), 0, sizeof(chip));
   }
   ~Engine() {
     for (hipEvent_t ev : evs) (void)hipEventDestroy(ev);
@@ -823,13 +900,50 @@ struct Engine {
     grid = int(std::max<size_t>(size_t(cus) * std::max(1, occ), items));
     grid = ((grid + 7) / 8) * 8;
     e.grid_small = ((cus * 4 + 7) / 8) * 8;
+    setup_chip(cus);
+  }
+
+  // Inner steps on the chip where every problem has the same grid and a
+  // shape fits.  The chip kernel never swaps r and p, so its mailboxes lie
+  // in the second r and p vectors.
+  void setup_chip(int cus) {
+    if (z.method != 0) return;
+    for (int i = 1; i < z.ninst; ++i)
+      if (plans[i]->nx != plans[0]->nx || plans[i]->ny != plans[0]->ny) return;
+    Chip c;
+    std::memset(static_cast<void*>(&c), 0, sizeof(c));
+    if (!chip_config(plans[0]->nx, plans[0]->ny, e.d_is_f32, cus, z.B, &c)) return;
+    const size_t room = size_t(z.B) * z.cap * z.eb;
+    const size_t rec = size_t(c.ngroups) * 3 * c.G * kChipRec * 8, ctl = size_t(c.ctl_words) * 4;
+    const size_t ring = (c.Gc > 1) ? size_t(c.ngroups) * 6 * c.G * c.nx * z.eb : 0;
+    if (rec + ctl > room || ring > room) return;
+    c.rec = static_cast<unsigned long long*>(e.p1);
+    c.ctl = reinterpret_cast<int*>(static_cast<char*>(e.p1) + rec);
+    c.ring = e.r1;
+    chip = c;
+    e.chip_ctl = c.ctl;
+    e.chip_words = c.ctl_words;
+    double none;
+    std::memset(&none, 0xff, sizeof(none));
+    launch_fill_value(reinterpret_cast<double*>(c.rec), rec / 8, none, st);
+    if (ring > 0) launch_fill_value(static_cast<double*>(c.ring), ring / 8, none, st);
   }
 
   template <typename T>
   void enqueue_chunk(bool with_events) {
     launch_retire(e, st);
     launch_assign(e, st);
-    for (int i = 0; i < chunk; ++i) {
+    if (e.chip_words > 0) {
+      // residual and prime steps, then up to K inner steps of every slot
+      for (int i = 0; i < 2; ++i) {
+        launch_pass<T>(e, grid, st);
+        launch_pass_scalars(e, st);
+      }
+      if (with_events) HIPCHK(hipEventRecord(evs[0], st));
+      launch_chip(e, chip, st);
+      if (with_events) HIPCHK(hipEventRecord(evs[1], st));
+    }
+    for (int i = 0; e.chip_words == 0 && i < chunk; ++i) {
       if (z.method == 1) {
         launch_bcg<T>(e, grid, st, with_events ? &evs[kBcgEvents * i] : nullptr);
       } else {
@@ -848,9 +962,10 @@ struct Engine {
   // captured for the same values is replayed as it is.
   template <typename T>
   std::vector<char> graph_key() const {
-    std::vector<char> k(sizeof(Eng) + 4 * sizeof(int) + sizeof(void*));
+    std::vector<char> k(sizeof(Eng) + 4 * sizeof(int) + sizeof(void*) + sizeof(Chip));
     char* p = k.data();
     std::memcpy(p, &e, sizeof(Eng));
+    std::memcpy(p + k.size() - sizeof(Chip), &chip, sizeof(Chip));
     const int v[4] = {grid, chunk, int(sizeof(T)), z.method};
     std::memcpy(p + sizeof(Eng), v, sizeof(v));
     const void* hc = hcount;
@@ -946,7 +1061,8 @@ struct Engine {
       if (profile) {
         enqueue_chunk<T>(true);
         HIPCHK(hipStreamSynchronize(st));
-        for (int i = 0; i < chunk; ++i) {
+        const int steps = e.chip_words > 0 ? 1 : chunk;
+        for (int i = 0; i < steps; ++i) {
           float ms = 0.f;
           if (z.method == 1) {
             const hipEvent_t* ev = &evs[kBcgEvents * i];
@@ -960,10 +1076,17 @@ struct Engine {
           }
           kernel_ms += ms;
         }
-        launches += chunk;
+        launches += steps;
       } else {
         HIPCHK(hipGraphLaunch(gexec, st));
         HIPCHK(hipStreamSynchronize(st));
+      }
+      if (hcount[2] == 1) throw HipError{REXII_ERR_HIP, "a block of the chip kernel waited past its limit"};
+      if (hcount[2] == 2 && chip.gpx > 0 && !profile) {
+        // an XCD had fewer blocks than its groups need: groups of any blocks
+        chip.gpx = 0;
+        launch_fill_zero(reinterpret_cast<double*>(e.counter), 2, st);
+        build_graph<T>();
       }
       if (hcount[0] == 0) break;
       if (every > 0.0) {
@@ -978,6 +1101,10 @@ struct Engine {
     }
     stats.resize(z.S);
     read_to_host(stats.data(), e.stats, z.S * sizeof(SolveStat), st);
+    // steps of the chip kernel count as the bytes that the passes stream for
+    // them (in FP64 every other step leaves d alone)
+    if (e.chip_words > 0 && z.eb == 16)
+      for (SolveStat& s : stats) s.skips = s.it_total / 2;
     solve_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
 #ifdef REXII_DEBUG_CHECKS
     int dbg[16];
@@ -1822,6 +1949,29 @@ static int autotune_slots(const std::vector<JobItem>& items, const rexii_opts& o
     }
   }
   const bool bicg = depth || o.method == 1;
+  if (!bicg) {
+    // slots whose inner steps run on the chip: the count decides little (the
+    // groups take the slots in turn), the default stands
+    std::vector<Problem> pbs(items.size());
+    std::vector<Problem*> ptrs;
+    for (size_t i = 0; i < items.size(); ++i) {
+      if (items[i].skip || sizing_plan(items[i], o, pbs[i]) != REXII_OK) continue;
+      ptrs.push_back(&pbs[i]);
+    }
+    bool same = !ptrs.empty();
+    for (Problem* p : ptrs) same = same && p->pl.nx == ptrs[0]->pl.nx && p->pl.ny == ptrs[0]->pl.ny;
+    Chip c{};
+    if (same) {
+      const EngineSize z = engine_size(ptrs, 0, o.precision, o.tile_rows);
+      if (chip_config(ptrs[0]->pl.nx, ptrs[0]->pl.ny, o.precision == REXII_PREC_MIXED, cus, z.B, &c)) {
+        // (the plan counts unpaired solves: half of them may pair up)
+        const int B = std::max(1, std::min(z.B, (z.S + 1) / 2));
+        tune_store(key, B, z.th, 0.0);
+        *th = z.th;
+        return B;
+      }
+    }
+  }
   std::vector<int> ths;
   if (bicg && o.tile_rows == 0)
     ths = {32, 16};
