@@ -265,7 +265,6 @@ int bcg_occupancy(int mixed, int th);
 void launch_pass_scalars(const Eng& e, hipStream_t s);
 void launch_retire(const Eng& e, hipStream_t s);
 void launch_assign(const Eng& e, hipStream_t s);
-void launch_count_finished(const Eng& e, hipStream_t s);
 int pass_occupancy(int mixed);
 void launch_fill_zero(double* p, size_t n, hipStream_t s);
 void launch_prep(const double* f, int nx, int ny, double* D0, double* Z0, int* flags, hipStream_t s);

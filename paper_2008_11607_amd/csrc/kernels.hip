@@ -661,10 +661,16 @@ __device__ __forceinline__ bool finished(int st) {
   return st == kDone || st == kFailMaxIter || st == kFailBreakdown || st == kRetry;
 }
 
-// Exclusive prefix sum of one int per thread over a block of kSchedNT
-// threads (4 wavefronts); *total receives the block total.
-constexpr int kSchedNT = 256;
-constexpr int kSchedPer = kMaxSlots / kSchedNT;  // slots per thread
+// Exclusive prefix sum of one int per thread over a block of NT threads;
+// *total receives the block total, sh holds NT / 64 ints.
+constexpr int kSchedNT = 1024;                   // k_assign: one slot per thread
+static_assert(kSchedNT >= kMaxSlots, "k_assign gives every slot a thread");
+constexpr int kRetNT = 256;
+constexpr int kRetPer = kMaxSlots / kRetNT;      // slots per thread of the list
+constexpr int kRetPts = 64;                      // points of a k_retire block at a time
+constexpr int kRetSub = kRetNT / kRetPts;        // parts of a run of slots
+constexpr int kRetBatch = 64;                    // slots whose records are in LDS together
+template <int NT>
 __device__ __forceinline__ int block_scan_excl(int v, int* sh, int* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   int x = v;
@@ -676,118 +682,192 @@ __device__ __forceinline__ int block_scan_excl(int v, int* sh, int* total) {
   __syncthreads();  // sh free
   if (lane == 63) sh[wid] = x;
   __syncthreads();
-  int off = 0;
-  for (int k = 0; k < wid; ++k) off += sh[k];
-  *total = sh[0] + sh[1] + sh[2] + sh[3];
+  int off = 0, tot = 0;
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) {
+    if (k < wid) off += sh[k];
+    tot += sh[k];
+  }
+  *total = tot;
   return off + x - v;
 }
 
 // Finished slots, in index order, into list[0 .. *n) (whole block).
 __device__ __forceinline__ void finished_slots(const Eng& e, int* list, int* sh, int* n) {
-  int st[kSchedPer];
+  int st[kRetPer];
   int cnt = 0;
 #pragma unroll
-  for (int j = 0; j < kSchedPer; ++j) {
-    const int s = threadIdx.x * kSchedPer + j;
+  for (int j = 0; j < kRetPer; ++j) {
+    const int s = threadIdx.x * kRetPer + j;
     st[j] = (s < e.B) ? ldc(&e.slots[s].status) : kIdle;
-    cnt += finished(st[j]) ? 1 : 0;
   }
-  int pos = block_scan_excl(cnt, sh, n);
 #pragma unroll
-  for (int j = 0; j < kSchedPer; ++j)
-    if (finished(st[j])) list[pos++] = threadIdx.x * kSchedPer + j;
+  for (int j = 0; j < kRetPer; ++j) cnt += finished(st[j]) ? 1 : 0;
+  int pos = block_scan_excl<kRetNT>(cnt, sh, n);
+#pragma unroll
+  for (int j = 0; j < kRetPer; ++j)
+    if (finished(st[j])) list[pos++] = threadIdx.x * kRetPer + j;
   __syncthreads();
 }
 
 // Finished slots: A[inst] += Re(c_j x64) (or copy x64 out), then x64 = 0.
-// Each point walks the finished slots in index order.
-__global__ __launch_bounds__(kSchedNT) void k_retire(Eng e) {
-  if (ldc(&e.counter[3]) == 0) return;  // nothing finished in the previous chunk
+// The records of 64 slots are read into LDS together; a run of slots of one
+// problem is split over the four parts of a block, each adding its slots in
+// index order, and the parts are added in order: a thread has the loads of
+// four slots in flight and a point four threads.  One thread per point and
+// one record at a time took 428 us for 234 slots of 64^2 (46 MB).
+struct RetRec {
+  double2 c0, c1, c2;
+  double* A;
+  size_t yrow;
+  int slot, n, inst;
+  int mode;   // bit 0: accumulate (else only x64 = 0), bit 1: the last d is still to be added
+};
+__global__ __launch_bounds__(kRetNT) void k_retire(Eng e) {
   __shared__ int list[kMaxSlots];
-  __shared__ int sh[4];
+  __shared__ int sh[kRetNT / 64];
+  __shared__ RetRec rec[kRetBatch];
+  __shared__ double part[kRetSub][3][kRetPts];
   int nfin = 0;
   finished_slots(e, list, sh, &nfin);
-  for (int q = 0; q < nfin; ++q) {
-    const int s = list[q];
-    const Slot* S = &e.slots[s];
-    const Inst I = ld_inst(&e.inst[ldc(&S->inst)]);
-    const int n = I.nx * I.ny;
-    if (ldc(&S->status) == kRetry) {
-      // solved again in FP64 by the host: nothing is kept from this attempt
-      for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        e.x64[size_t(s) * e.cap + i] = make_double2(0.0, 0.0);
-      continue;
+  const int tp = threadIdx.x & (kRetPts - 1), sub = threadIdx.x / kRetPts;
+  for (int q0 = 0; q0 < nfin; q0 += kRetBatch) {
+    const int nb = min(kRetBatch, nfin - q0);
+    __syncthreads();
+    if (int(threadIdx.x) < nb) {
+      const int s = list[q0 + threadIdx.x];
+      const Slot* S = &e.slots[s];
+      const int inst = ldc(&S->inst), sv = ldc(&S->solve), st = ldc(&S->status);
+      const int rounds = ldc(&S->rounds), discard = ldc(&S->discard);
+      const SolveDev* D = &e.solves[sv];
+      const Inst* I = &e.inst[inst];
+      RetRec r;
+      r.c0 = ldc(&D->c0);
+      r.c1 = ldc(&D->c1);
+      r.c2 = ldc(&D->c2);
+      const int yi = ldc(&D->yidx), nx = ldc(&I->nx), ny = ldc(&I->ny);
+      r.A = ldc_ptr(&I->A);
+      r.yrow = e.yout ? size_t(yi) * e.ystride : 0;
+      r.slot = s;
+      r.n = nx * ny;
+      r.inst = inst;
+      // kRetry: solved again in FP64 by the host, nothing is kept; the last
+      // inner correction d counts once the solve has run an inner round
+      r.mode = (st == kRetry ? 0 : 1) | ((rounds >= 2 && discard == 0) ? 2 : 0);
+      rec[threadIdx.x] = r;
     }
-    // the last inner correction d is still to be added (once the solve has
-    // run an inner round)
-    const bool add_d = ldc(&S->rounds) >= 2 && ldc(&S->discard) == 0;
-    const int sv = ldc(&S->solve);
-    const double2 c0 = ldc(&e.solves[sv].c0), c1 = ldc(&e.solves[sv].c1), c2 = ldc(&e.solves[sv].c2);
-    const size_t yrow = e.yout ? size_t(ldc(&e.solves[sv].yidx)) * e.ystride : 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-      double2* xp = e.x64 + size_t(s) * e.cap + i;
-      double2 x = *xp;
-      if (add_d) {
-        if (e.d_is_f32) {
-          const float2 dv = reinterpret_cast<const float2*>(e.d)[size_t(s) * e.cap + i];
-          x.x += double(dv.x);
-          x.y += double(dv.y);
-        } else {
-          const double2 dv = reinterpret_cast<const double2*>(e.d)[size_t(s) * e.cap + i];
-          x.x += dv.x;
-          x.y += dv.y;
+    __syncthreads();
+    for (int i0 = blockIdx.x * kRetPts; i0 < e.cap; i0 += gridDim.x * kRetPts) {
+      const int i = i0 + tp;
+      for (int b = 0, f = 0; b < nb; b = f) {
+        // the run b .. f - 1 of slots of one problem
+        const int inst = rec[b].inst, n = rec[b].n;
+        f = b + 1;
+        while (f < nb && rec[f].inst == inst) ++f;
+        if (i0 >= n) continue;
+        const int per = (f - b + kRetSub - 1) / kRetSub;
+        const int k0 = min(f, b + sub * per), k1 = min(f, k0 + per);
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+        if (i < n) {
+          constexpr int kU = 4;
+          for (int k = k0; k < k1; k += kU) {
+            double2 x[kU], d[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+              x[u] = d[u] = make_double2(0.0, 0.0);
+              if (k + u >= k1) continue;
+              const RetRec& r = rec[k + u];
+              const size_t g = size_t(r.slot) * e.cap + i;
+              if (r.mode & 1) x[u] = e.x64[g];
+              if (r.mode == 3) {
+                if (e.d_is_f32) {
+                  const float2 v = reinterpret_cast<const float2*>(e.d)[g];
+                  d[u] = make_double2(double(v.x), double(v.y));
+                } else {
+                  d[u] = reinterpret_cast<const double2*>(e.d)[g];
+                }
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+              if (k + u >= k1) continue;
+              const RetRec& r = rec[k + u];
+              e.x64[size_t(r.slot) * e.cap + i] = make_double2(0.0, 0.0);
+              if (!(r.mode & 1)) continue;
+              const double2 v = cadd(x[u], d[u]);
+              if (e.yout) e.yout[r.yrow + i] = v;
+              a0 += r.c0.x * v.x - r.c0.y * v.y;
+              a1 += r.c1.x * v.x - r.c1.y * v.y;
+              a2 += r.c2.x * v.x - r.c2.y * v.y;
+            }
+          }
         }
+        part[sub][0][tp] = a0;
+        part[sub][1][tp] = a1;
+        part[sub][2][tp] = a2;
+        __syncthreads();
+        if (sub < 3 && i < n) {
+          double t = part[0][sub][tp];
+#pragma unroll
+          for (int k = 1; k < kRetSub; ++k) t += part[k][sub][tp];
+          rec[b].A[size_t(sub) * n + i] += t;
+        }
+        __syncthreads();
       }
-      if (e.yout) e.yout[yrow + i] = x;
-      I.A[i] += c0.x * x.x - c0.y * x.y;
-      I.A[n + i] += c1.x * x.x - c1.y * x.y;
-      I.A[2 * n + i] += c2.x * x.x - c2.y * x.y;
-      *xp = make_double2(0.0, 0.0);
     }
   }
 }
 
-// Next solve of the queue into slot s.
-__device__ __forceinline__ void assign_solve(Eng& e, int s, int next) {
+// Next solve of the queue into slot s.  The solve's and the problem's fields
+// are read in two rounds, each with every load in flight, then written.
+__device__ __forceinline__ int assign_solve(const Eng& e, int s, int next) {
   Slot* S = &e.slots[s];
   const SolveDev* D = &e.solves[next];
-  const int dinst = ldc(&D->inst);
-  S->zeta = ldc(&D->zeta);
-  S->a1 = ldc(&D->a1);
-  S->a2 = ldc(&D->a2);
-  S->gamma = ldc(&D->gamma);
-  S->sc = ldc(&D->sc);
-  S->omega = make_double2(0.0, 0.0);
-  S->tol2 = ldc(&D->tol2);
-  S->ref2 = ldc(&D->ref2);
-  S->rr = S->alpha = S->beta = make_double2(0.0, 0.0);
+  const double2 zeta = ldc(&D->zeta), a1 = ldc(&D->a1), a2 = ldc(&D->a2), gamma = ldc(&D->gamma), sc = ldc(&D->sc);
+  const double tol2 = ldc(&D->tol2), ref2 = ldc(&D->ref2);
+  const int inst = ldc(&D->inst), max_it = ldc(&D->max_it);
+  const Inst* I = &e.inst[inst];
+  const int nx = ldc(&I->nx), ny = ldc(&I->ny), tiles_x = ldc(&I->tiles_x), nblk = ldc(&I->nblk);
+  const double cx = ldc(&I->cx), cy = ldc(&I->cy), cxy = ldc(&I->cxy);
+  const double *H = ldc_ptr(&I->H), *eta0 = ldc_ptr(&I->eta0), *D0 = ldc_ptr(&I->D0), *Z0 = ldc_ptr(&I->Z0);
+  const void* Hin = ldc_ptr(&I->Hin);
+  const double2 zero = make_double2(0.0, 0.0);
+  S->zeta = zeta;
+  S->a1 = a1;
+  S->a2 = a2;
+  S->gamma = gamma;
+  S->sc = sc;
+  S->omega = zero;
+  S->tol2 = tol2;
+  S->ref2 = ref2;
+  S->rr = S->alpha = S->beta = zero;
   S->bn2 = S->rn2 = S->prev_rn2 = S->in_tol2 = 0.0;
   S->status = kOuterPending;
   S->parity = 0;
   S->prime = 0;
   S->it_total = S->it_inner = S->rounds = 0;
   S->solve = next;
-  S->inst = dinst;
-  const Inst* I = &e.inst[dinst];
-  S->nx = ldc(&I->nx);
-  S->ny = ldc(&I->ny);
-  S->tiles_x = ldc(&I->tiles_x);
-  S->nblk = ldc(&I->nblk);
-  S->cx = ldc(&I->cx);
-  S->cy = ldc(&I->cy);
-  S->cxy = ldc(&I->cxy);
-  S->H = ldc_ptr(&I->H);
-  S->Hin = ldc_ptr(&I->Hin);
-  S->eta0 = ldc_ptr(&I->eta0);
-  S->D0 = ldc_ptr(&I->D0);
-  S->Z0 = ldc_ptr(&I->Z0);
+  S->inst = inst;
+  S->nx = nx;
+  S->ny = ny;
+  S->tiles_x = tiles_x;
+  S->nblk = nblk;
+  S->cx = cx;
+  S->cy = cy;
+  S->cxy = cxy;
+  S->H = H;
+  S->Hin = Hin;
+  S->eta0 = eta0;
+  S->D0 = D0;
+  S->Z0 = Z0;
   S->stagnated = 0;
   S->discard = 0;
-  S->max_it = ldc(&D->max_it);
-  S->dcp = S->dcr = make_double2(0.0, 0.0);
+  S->max_it = max_it;
+  S->dcp = S->dcr = zero;
   S->dmode = kDUpdate;
   S->fin = 0;
   S->skips = 0;
+  return nblk;
 }
 
 // One block: record finished solves, hand out the next ones in queue order
@@ -797,93 +877,61 @@ __device__ __forceinline__ void assign_solve(Eng& e, int s, int next) {
 // the (slot, tile) table of the work positions as 8 band lists (one per
 // XCD).
 // Every slot is handled by its own thread; the orders are those of a
-// sequential walk over the slots.
+// sequential walk over the slots.  (Four slots a thread, one field after the
+// other: 22-31 us.)
 __global__ __launch_bounds__(kSchedNT) void k_assign(Eng e) {
-  __shared__ int sh[4];
+  __shared__ int sh[kSchedNT / 64];
   __shared__ int s_nb[kMaxSlots];
   __shared__ int s_bo[kMaxSlots];
   __shared__ int s_min, s_max;
   const int next0 = ldc(e.next);
   for (int k = threadIdx.x; k < e.chip_words; k += kSchedNT) e.chip_ctl[k] = 0;
-#ifdef REXII_DEBUG_CHECKS
-  if (threadIdx.x == 0) {
-    int fin = 0;
-    for (int s = 0; s < e.B; ++s) fin += finished(ldc(&e.slots[s].status)) ? 1 : 0;
-    if (fin != ldc(&e.counter[3])) atomicAdd(&e.dbg[1], 1);
-    if (fin > 0 && ldc(&e.counter[3]) == 0) atomicAdd(&e.dbg[2], 1);
-  }
-  __syncthreads();
-#endif
   if (threadIdx.x == 0) {
     s_min = 1 << 30;
     s_max = 0;
   }
-  int st[kSchedPer];
-  int nidle = 0;
-#pragma unroll
-  for (int j = 0; j < kSchedPer; ++j) {
-    const int s = threadIdx.x * kSchedPer + j;
-    st[j] = -1;  // no such slot
-    if (s >= e.B) continue;
-    Slot* S = &e.slots[s];
-    st[j] = ldc(&S->status);
-    if (finished(st[j])) {
-      SolveStat& ss = e.stats[ldc(&S->solve)];
+  const int s = threadIdx.x;
+  Slot* S = &e.slots[s];
+  int st = -1, nb = 0;  // no such slot
+  if (s < e.B) {
+    st = ldc(&S->status);
+    nb = ldc(&S->nblk);
+    if (finished(st)) {
+      SolveStat ss;
+      const int sv = ldc(&S->solve);
       ss.rn2 = ldc(&S->rn2);
       ss.bn2 = ldc(&S->bn2);
       ss.it_total = ldc(&S->it_total);
       ss.rounds = ldc(&S->rounds);
-      ss.status = st[j];
+      ss.status = st;
       ss.stagnated = ldc(&S->stagnated);
       ss.skips = ldc(&S->skips);
-      st[j] = kIdle;
+      ss.pad = 0;
+      e.stats[sv] = ss;
+      st = kIdle;
       S->status = kIdle;
     }
-    nidle += (st[j] == kIdle) ? 1 : 0;
   }
   int total_idle = 0;
-  int rank = block_scan_excl(nidle, sh, &total_idle);
-  int nwork = 0, ntiles = 0, nband = 0;
-  int nb[kSchedPer];
-#pragma unroll
-  for (int j = 0; j < kSchedPer; ++j) {
-    const int s = threadIdx.x * kSchedPer + j;
-    nb[j] = 0;
-    if (st[j] < 0) continue;
-    if (st[j] == kIdle) {
-      const int q = next0 + rank++;
-      if (q < e.S) {
-        assign_solve(e, s, q);
-        st[j] = kOuterPending;
-        nb[j] = ldc(&e.inst[ldc(&e.solves[q].inst)].nblk);
-      }
-    } else {
-      nb[j] = ldc(&e.inst[ldc(&e.slots[s].inst)].nblk);
-    }
-    if (st[j] != kIdle) {
-      ++nwork;
-      ntiles += nb[j];
-      nband += (nb[j] + 7) >> 3;
-    }
+  const int rank = block_scan_excl<kSchedNT>(st == kIdle ? 1 : 0, sh, &total_idle);
+  if (st == kIdle && next0 + rank < e.S) {
+    nb = assign_solve(e, s, next0 + rank);
+    st = kOuterPending;
   }
+  const bool works = st > kIdle;
   const int next = min(next0 + total_idle, e.S);
   int working = 0, total = 0, per = 0;
-  int wpos = block_scan_excl(nwork, sh, &working);
-  (void)block_scan_excl(ntiles, sh, &total);
-  int bpos = block_scan_excl(nband, sh, &per);
+  const int wpos = block_scan_excl<kSchedNT>(works ? 1 : 0, sh, &working);
+  (void)block_scan_excl<kSchedNT>(works ? nb : 0, sh, &total);
+  const int bpos = block_scan_excl<kSchedNT>(works ? (nb + 7) >> 3 : 0, sh, &per);
   int lmin = 1 << 30, lmax = 0;
-#pragma unroll
-  for (int j = 0; j < kSchedPer; ++j) {
-    const int s = threadIdx.x * kSchedPer + j;
-    if (st[j] < 0) continue;
+  if (s < e.B) {
     s_bo[s] = bpos;
-    s_nb[s] = (st[j] != kIdle) ? nb[j] : 0;
-    if (st[j] != kIdle) {
-      e.work[2 + wpos++] = s;
-      bpos += (nb[j] + 7) >> 3;
-      lmin = min(lmin, nb[j]);
-      lmax = max(lmax, nb[j]);
-    }
+    s_nb[s] = works ? nb : 0;
+  }
+  if (works) {
+    e.work[2 + wpos] = s;
+    lmin = lmax = nb;
   }
   atomicMin(&s_min, lmin);
   atomicMax(&s_max, lmax);
@@ -910,20 +958,6 @@ __global__ __launch_bounds__(kSchedNT) void k_assign(Eng e) {
       e.items[size_t(x) * per + bo + j] = (t < n) ? make_int2(s, t) : make_int2(-1, -1);
     }
   }
-}
-
-// Count of slots that finished during the chunk (read by the next retire).
-__global__ __launch_bounds__(kSchedNT) void k_count_finished(Eng e) {
-  __shared__ int sh[4];
-  int cnt = 0;
-#pragma unroll
-  for (int j = 0; j < kSchedPer; ++j) {
-    const int s = threadIdx.x * kSchedPer + j;
-    if (s < e.B) cnt += finished(ldc(&e.slots[s].status)) ? 1 : 0;
-  }
-  int fin = 0;
-  (void)block_scan_excl(cnt, sh, &fin);
-  if (threadIdx.x == 0) e.counter[3] = fin;
 }
 
 // ---------------------------------------------------------------------------
@@ -1134,13 +1168,11 @@ void launch_pass_scalars(const Eng& e, hipStream_t s) {
   hipLaunchKernelGGL(k_pass_scalars, dim3(e.B), dim3(kSNT), 0, s, e);
 }
 void launch_retire(const Eng& e, hipStream_t s) {
-  hipLaunchKernelGGL(k_retire, dim3(flat_blocks(size_t(e.cap))), dim3(kSchedNT), 0, s, e);
+  const size_t bl = (size_t(e.cap) + kRetPts - 1) / kRetPts;
+  hipLaunchKernelGGL(k_retire, dim3(unsigned(bl > 8192 ? 8192 : bl)), dim3(kRetNT), 0, s, e);
 }
 void launch_assign(const Eng& e, hipStream_t s) {
   hipLaunchKernelGGL(k_assign, dim3(1), dim3(kSchedNT), 0, s, e);
-}
-void launch_count_finished(const Eng& e, hipStream_t s) {
-  hipLaunchKernelGGL(k_count_finished, dim3(1), dim3(kSchedNT), 0, s, e);
 }
 void launch_fill_zero(double* p, size_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_zero, dim3(flat_blocks(n)), dim3(256), 0, s, p, n);

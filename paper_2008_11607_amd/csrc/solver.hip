@@ -953,7 +953,6 @@ struct Engine {
         launch_pass_scalars(e, st);
       }
     }
-    launch_count_finished(e, st);
     HIPCHK(hipMemcpyAsync(hcount, e.counter, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   }
 
@@ -962,10 +961,9 @@ struct Engine {
   // captured for the same values is replayed as it is.
   template <typename T>
   std::vector<char> graph_key() const {
-    std::vector<char> k(sizeof(Eng) + 4 * sizeof(int) + sizeof(void*) + sizeof(Chip));
+    std::vector<char> k(sizeof(Eng) + 4 * sizeof(int) + sizeof(void*));
     char* p = k.data();
     std::memcpy(p, &e, sizeof(Eng));
-    std::memcpy(p + k.size() - sizeof(Chip), &chip, sizeof(Chip));
     const int v[4] = {grid, chunk, int(sizeof(T)), z.method};
     std::memcpy(p + sizeof(Eng), v, sizeof(v));
     const void* hc = hcount;
@@ -1042,10 +1040,13 @@ struct Engine {
       (void)hipEventDestroy(b);
       return double(ms);
     }
+    // a chunk of the chip path is seven launches, enqueued faster than they
+    // run: no graph
+    const bool graphed = !profile && e.chip_words == 0;
     if (profile) {
       evs.resize((z.method == 1 ? kBcgEvents : 2) * chunk);
       for (hipEvent_t& ev : evs) HIPCHK(hipEventCreate(&ev));
-    } else {
+    } else if (graphed) {
       build_graph<T>();
     }
     const auto w0 = std::chrono::steady_clock::now();
@@ -1078,16 +1079,15 @@ struct Engine {
         }
         launches += steps;
       } else {
-        HIPCHK(hipGraphLaunch(gexec, st));
+        if (graphed)
+          HIPCHK(hipGraphLaunch(gexec, st));
+        else
+          enqueue_chunk<T>(false);
         HIPCHK(hipStreamSynchronize(st));
       }
       if (hcount[2] == 1) throw HipError{REXII_ERR_HIP, "a block of the chip kernel waited past its limit"};
-      if (hcount[2] == 2 && chip.gpx > 0 && !profile) {
-        // an XCD had fewer blocks than its groups need: groups of any blocks
-        chip.gpx = 0;
-        launch_fill_zero(reinterpret_cast<double*>(e.counter), 2, st);
-        build_graph<T>();
-      }
+      // an XCD had fewer blocks than its groups need: groups of any blocks
+      if (hcount[2] == 2) chip.gpx = 0;
       if (hcount[0] == 0) break;
       if (every > 0.0) {
         const auto now = std::chrono::steady_clock::now();
