@@ -402,8 +402,10 @@ rexii_status rexii_apply_fourier_noalloc(const rexii_swe_op* op, const double* f
  *     u = ||f||_W V_m Re sum_k w_k (t T_m - z_k I)^{-1} e_1.
  * W = diag(g, H, H) makes A skew-adjoint, so the process is a real
  * two-term recurrence and T_m is skew-tridiagonal.  Pass 1 forms the
- * recurrence coefficients; the host solves the small problems; pass 2
- * repeats the same steps and accumulates u, so the basis is never stored.
+ * recurrence coefficients and keeps as many of the vectors as the workspace
+ * holds; the small problems are solved (on the GPU where the workspace has
+ * room for their recurrences, else on the host); pass 2 sums the kept vectors
+ * and repeats the steps beyond them, accumulating u.
  * The poles come from the M rule for the Gershgorin bound of T_m, which is
  * at most rho(A).  m grows until the last 8 coefficients of the small
  * solution hold under tol / 10 of its norm (checked from m = 0.75 t rho on).
@@ -412,17 +414,23 @@ rexii_status rexii_apply_fourier_noalloc(const rexii_swe_op* op, const double* f
  *     overlapping.
  *   opts: h, tol, m0 as for rexii_apply; max_iter caps the Krylov dimension
  *     m (default 50000); profile = 1 fills step_ms.
- *   Workspace: rexii_multishift_workspace_size() bytes, or NULL.
+ *   Workspace: at least rexii_multishift_workspace_size() bytes (no vector is
+ *     kept: every step runs twice), better rexii_multishift_basis_size() (the
+ *     vectors and the small problem to expect for this t, at most 32 GiB of
+ *     vectors; a depth field is read on the null stream), or NULL (as the
+ *     least).  Any size between keeps what fits.
  *   Report: solves = max_iters = m, total_iters = sum of m over states,
  *     P, M, N for the largest small problem, rho = its Gershgorin bound,
  *     max_rel_residual = largest tail ratio, alg_bytes = algorithmic HBM
- *     bytes of both passes.  With profile = 1: step_ms[0] pass 1, [1] host
- *     small problems, [2] pass 2 (ms); kernel_ms = step_ms[2] and
+ *     bytes of both passes.  With profile = 1: step_ms[0] pass 1, [1]
+ *     small problems (host time), [2] pass 2 (ms); kernel_ms = step_ms[2] and
  *     kernel_bytes = pass 2's algorithmic bytes.
  * Errors: INVALID_ARG, NONFINITE (f), NOT_CONVERGED (m reached max_iter;
  * u is written from that m), OOM, HIP, WORKSPACE. */
 rexii_status rexii_multishift_workspace_size(const rexii_swe_op* op, int32_t nrhs, const rexii_opts* opts,
                                              size_t* bytes);
+rexii_status rexii_multishift_basis_size(const rexii_swe_op* op, int32_t nrhs, double t, const rexii_opts* opts,
+                                         size_t* bytes);
 
 rexii_status rexii_apply_multishift(const rexii_swe_op* op, int32_t nrhs, const double* f, double* u, double t,
                                     const rexii_opts* opts, void* workspace, size_t ws_bytes,

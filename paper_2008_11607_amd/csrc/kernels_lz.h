@@ -1,6 +1,7 @@
 // Launchers of the shared-Krylov (multi-shift) path (kernels_lz.hip).
-// States are [nrhs][3][ny][nx] FP64; beta is [nrhs][ldb] with beta_0 = ||f||_W
-// and beta_j = ||w_j||_W; part is [nrhs][lz_blocks()] block partial sums.
+// States are [3][ny][nx] FP64, a batch's states `stride` doubles apart; beta
+// is [nrhs][ldb] with beta_0 = ||f||_W and beta_j = ||w_j||_W; part is
+// [nrhs][lz_blocks()] block partial sums.
 #ifndef REXII_KERNELS_LZ_H
 #define REXII_KERNELS_LZ_H
 
@@ -9,16 +10,28 @@
 
 namespace rexii {
 
+// Two poles z, -conj(z) of a term with their weights.
+struct LzPair {
+  double2 z, w1, w2;
+};
+
 int lz_blocks(int nx, int ny);
 // buf = f, beta[r][0] = ||f_r||_W, flag[0] |= 1 on a non-finite value of f.
-void launch_lz_start(const double* f, double* buf, const double* H, double H0, double g, int nx, int ny, int nrhs,
-                     double* part, int* flag, double* beta, int ldb, hipStream_t s);
-// Lanczos step j (1-based) on cur = buf_j, prev = buf_{j-1} (overwritten with
-// buf_{j+1}); with part, beta[r][j] = ||w_j||_W is formed; with y and u,
-// u += y_j v_j; last: only the accumulation.
-void launch_lz_step(const double* cur, double* prev, const double* H, double H0, double g, double fc, int nx, int ny,
-                    int nrhs, int j, double* beta, int ldb, double* part, const double* y, int ldy, double* u,
-                    int last, hipStream_t s);
+void launch_lz_start(const double* f, double* buf, size_t stride, const double* H, double H0, double g, int nx, int ny,
+                     int nrhs, double* part, int* flag, double* beta, int ldb, hipStream_t s);
+// Lanczos step j (1-based) on cur = buf_j, prev = buf_{j-1}; out (which may
+// be prev) receives buf_{j+1}; with part, beta[r][j] = ||w_j||_W is formed;
+// with y and u, u += y_j v_j; last: only the accumulation.
+void launch_lz_step(const double* cur, const double* prev, double* out, size_t stride, const double* H, double H0,
+                    double g, double fc, int nx, int ny, int nrhs, int j, double* beta, int ldb, double* part,
+                    const double* y, int ldy, double* u, int last, hipStream_t s);
+// u = sum_{j < m} coef[j] vecs[j], vectors of n3 doubles.
+void launch_lz_gather(const double* vecs, size_t n3, int m, const double* coef, double* u, hipStream_t s);
+// The small problem of one state: b = its beta row, y[j], coef[j] = y_j / b_{j-1}
+// and out = (|y|^2, |last 8 of y|^2); scratch: lz_small_bytes(m, npair), 256-byte aligned.
+size_t lz_small_bytes(int m, int npair);
+void launch_lz_small(const double* b, int m, double t, const LzPair* pairs, int npair, void* scratch, double* y,
+                     double* coef, double* out, hipStream_t s);
 
 }  // namespace rexii
 

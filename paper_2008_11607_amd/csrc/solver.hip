@@ -142,6 +142,22 @@ static DevCtx* device_ctx() {
   return c;
 }
 
+// Holds the device's set while it lives, unless another call has it.
+struct CtxHold {
+  DevCtx* c = nullptr;
+  DevCtx* prev = tl_ctx;
+  CtxHold() {
+    if (tl_ctx) return;
+    DevCtx* d = device_ctx();
+    if (d && d->mu.try_lock()) tl_ctx = c = d;
+  }
+  ~CtxHold() {
+    if (!c) return;
+    tl_ctx = prev;
+    c->mu.unlock();
+  }
+};
+
 // Pinned host memory of at least `bytes` from the held set (grown on
 // demand), or nullptr when the thread holds none.
 static void* ctx_pinned(size_t bytes) {
@@ -2651,8 +2667,9 @@ struct SmallResult {
 // (tT - z_2)^{-1} e_1 = -D conj((tT - z_1)^{-1} e_1).  Each solve is Gaussian
 // elimination without pivoting, stable here because the Hermitian part of
 // tT - z is -Re(z) I, definite.
-static SmallResult small_problem(const double* b, int m, double t, double h, int m0, double beta0,
-                                 double rho_cap, std::vector<double>& y) {
+// The plan of the small problem of dimension m: pole count, poles, weights.
+static SmallResult small_plan(const double* b, int m, double t, double h, int m0, double rho_cap, std::vector<cplx>& z,
+                              std::vector<cplx>& w) {
   SmallResult res;
   double rho = 0.0;
   for (int j = 1; j <= m; ++j) {
@@ -2665,10 +2682,16 @@ static SmallResult small_problem(const double* b, int m, double t, double h, int
   res.rho = rho;
   res.M = m_rule(t, std::max(rho, 1e-300), h, m0);
   res.N = res.M + terms_L();
-  std::vector<cplx> z, w;
   poles_weights(res.M, h, z, w);
   res.P = int(z.size());
   res.kappa = kappa_sum(w, h);
+  return res;
+}
+
+// The small problem on the host (where the workspace has no room for the
+// kernel's recurrences).
+static void small_problem(const double* b, int m, double t, double beta0, const std::vector<cplx>& z,
+                          const std::vector<cplx>& w, SmallResult& res, std::vector<double>& y) {
   const int npair = res.P / 2;
   unsigned nth = std::thread::hardware_concurrency();
   nth = std::max(1u, std::min(16u, nth));
@@ -2714,8 +2737,37 @@ static SmallResult small_problem(const double* b, int m, double t, double h, int
     if (j >= m - 8) tail += y[j] * y[j];
   }
   res.tail = (tot > 0.0) ? std::sqrt(tail / tot) : 0.0;
-  return res;
 }
+
+// Device memory of a shared-Krylov call: 2 + K vectors a state (K of them kept
+// from pass 1) and scratch for the small problem.  The least (K = 0, no
+// scratch: the small problem runs on the host) works at every size; more
+// makes pass 2 a sum over kept vectors.
+// Krylov dimension and pole pairs to expect for t rho (the dimension at which
+// the small solution's tail has met tol, with the next check's margin).
+static int lz_expect_m(double trho, int mmax) { return int(std::min<double>(mmax, 1.35 * trho + 128.0)); }
+static int lz_expect_pairs(double trho, double h) { return int(trho / h) + 64; }
+static size_t lz_scratch(double trho, double h, int mmax) {
+  const int np = lz_expect_pairs(trho, h);
+  return al256(size_t(np) * sizeof(LzPair)) + al256(lz_small_bytes(lz_expect_m(trho, mmax), np));
+}
+constexpr size_t kLzBudget = size_t(32) << 30;   // most bytes of kept vectors asked for
+
+static size_t multishift_bytes(int nx, int ny, int nrhs, int max_iter) {
+  const size_t n3 = 3 * size_t(nx) * ny;
+  const int mmax = std::max(8, max_iter > 0 ? max_iter : kMultishiftMaxM);
+  return 2 * al256(size_t(nrhs) * n3 * 8) + al256(size_t(nrhs) * lz_blocks(nx, ny) * 8) +
+         al256(size_t(nrhs) * (mmax + 2) * 8) + al256(size_t(nrhs) * mmax * 8) + al256(256);
+}
+// ... and with room for the vectors and the small problem to expect for t rho
+static size_t multishift_basis_bytes(int nx, int ny, int nrhs, int max_iter, double h, double trho) {
+  const int mmax = std::max(8, max_iter > 0 ? max_iter : kMultishiftMaxM);
+  const size_t vec = size_t(nrhs) * 3 * size_t(nx) * ny * 8;
+  const size_t kept = std::min<size_t>(size_t(lz_expect_m(trho, mmax)), kLzBudget / vec);
+  return multishift_bytes(nx, ny, nrhs, max_iter) + lz_scratch(trho, h, mmax) + al256(size_t(mmax) * 8) + kept * vec +
+         4096;
+}
+
 
 static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const double* f, double* u, double t,
                                    const rexii_opts* opts_in, void* ws, size_t ws_bytes, hipStream_t st,
@@ -2740,8 +2792,9 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     const int mmax = std::max(8, o.max_iter > 0 ? o.max_iter : kMultishiftMaxM);
     const int ldb = mmax + 2, ldy = mmax;
     const int nb = lz_blocks(nx, ny);
-    const size_t need = 2 * al256(size_t(nrhs) * n3 * 8) + al256(size_t(nrhs) * nb * 8) +
-                        al256(size_t(nrhs) * ldb * 8) + al256(size_t(nrhs) * ldy * 8) + al256(256);
+    const size_t need = multishift_bytes(nx, ny, nrhs, o.max_iter);
+    // pinned staging of the device's set, if no other call holds it
+    CtxHold hold;
     Arena ar(ws, ws_bytes);
     if (!ws) {
       ar.reserve_own(need + 4096);
@@ -2750,15 +2803,31 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     } else if (reinterpret_cast<uintptr_t>(ws) & 255) {
       return set_error(REXII_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
     }
-    double* X = ar.take<double>(size_t(nrhs) * n3);
-    double* Y = ar.take<double>(size_t(nrhs) * n3);
+    const double* Hf = op->H_field;
+    const double H0 = op->H0, g = op->g, fc = op->f_cor;
+    // scale of A for the breakdown test (beta_j -> 0: an invariant subspace)
+    const double hscale = Hf ? device_hmax(Hf, n, st) : H0;
+    const double rho_ref = std::sqrt(g * hscale) * std::sqrt(double(nx) * nx + double(ny) * ny) + std::fabs(fc);
     double* part = ar.take<double>(size_t(nrhs) * nb);
     double* beta = ar.take<double>(size_t(nrhs) * ldb);
     double* ydev = ar.take<double>(size_t(nrhs) * ldy);
     double* flagd = ar.take<double>(32);
     int* flag = reinterpret_cast<int*>(flagd);
-    const double* Hf = op->H_field;
-    const double H0 = op->H0, g = op->g, fc = op->f_cor;
+    double* small_out = flagd + 8;   // |y|^2 and its tail
+    // what the workspace holds beyond the least: the small problem's scratch,
+    // then kept vectors
+    const size_t two = 2 * size_t(nrhs) * n3 * 8;
+    size_t scr_bytes = lz_scratch(t * rho_ref, o.h, mmax) + al256(size_t(mmax) * 8);
+    if (ar.remaining() < two + scr_bytes + 1024) scr_bytes = 0;
+    double* coef = scr_bytes ? ar.take<double>(mmax) : nullptr;
+    char* scr = scr_bytes ? ar.take<char>(scr_bytes - al256(size_t(mmax) * 8)) : nullptr;
+    const size_t scr_room = scr_bytes ? scr_bytes - al256(size_t(mmax) * 8) : 0;
+    const size_t room = ar.remaining() / 256 * 256;
+    const int kept = scr ? int(std::min<size_t>(size_t(mmax), (room - two) / (size_t(nrhs) * n3 * 8))) : 0;
+    const size_t stride = size_t(kept + 2) * n3;
+    double* vecs = ar.take<double>(size_t(nrhs) * stride);
+    // place of buf_j (1-based) of state 0: kept, or one of the last two in turn
+    auto place = [&](int j) { return vecs + size_t(j <= kept ? j - 1 : kept + ((j - kept - 1) & 1)) * n3; };
     hipEvent_t ev[2] = {};  // around the whole call (pass 2 is timed per state)
     const bool prof = (o.profile != 0);
     if (prof)
@@ -2775,7 +2844,7 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     // checks for breakdown and, once m reaches t rho(T), for convergence
     launch_fill_zero(flagd, 32, st);
     if (prof) HIPCHK(hipEventRecord(ev[0], st));
-    launch_lz_start(f, X, Hf, H0, g, nx, ny, nrhs, part, flag, beta, ldb, st);
+    launch_lz_start(f, place(1), stride, Hf, H0, g, nx, ny, nrhs, part, flag, beta, ldb, st);
     std::vector<double> hb(size_t(nrhs) * ldb, 0.0);
     // device-to-host reads go to pinned host memory, ordered on the stream
     // and waited for through an event
@@ -2785,9 +2854,15 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
         if (p) (void)hipHostFree(p);
       }
     } pin;
-    HIPCHK(hipHostMalloc(&pin.p, size_t(nrhs) * ldb * 8 + 256, hipHostMallocDefault));
-    double* hbp = static_cast<double*>(pin.p);
+    const size_t pin_need = size_t(nrhs) * ldb * 8 + 256;
+    void* pinned = (pin_need <= (size_t(8) << 20)) ? ctx_pinned(pin_need) : nullptr;
+    if (!pinned) {
+      HIPCHK(hipHostMalloc(&pin.p, pin_need, hipHostMallocDefault));
+      pinned = pin.p;
+    }
+    double* hbp = static_cast<double*>(pinned);
     int* hflag = reinterpret_cast<int*>(hbp + size_t(nrhs) * ldb);
+    double* hsmall = reinterpret_cast<double*>(hflag + 2);
     hipEvent_t rd = nullptr;
     HIPCHK(hipEventCreateWithFlags(&rd, hipEventDisableTiming));
     struct EvFree {
@@ -2799,23 +2874,25 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       HIPCHK(hipEventSynchronize(rd));
     };
     HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(hbp, beta, size_t(nrhs) * ldb * 8, hipMemcpyDeviceToHost, st));
-    wait_reads();
+    // beta_{lo} .. beta_{hi} of every state to the host
+    auto read_beta = [&](int lo, int hi) {
+      HIPCHK(hipMemcpy2DAsync(hbp + lo, size_t(ldb) * 8, beta + lo, size_t(ldb) * 8, size_t(hi - lo + 1) * 8, nrhs,
+                              hipMemcpyDeviceToHost, st));
+      wait_reads();
+      for (int r = 0; r < nrhs; ++r)
+        std::copy(hbp + size_t(r) * ldb + lo, hbp + size_t(r) * ldb + hi + 1, hb.begin() + size_t(r) * ldb + lo);
+    };
+    read_beta(0, 0);
     const int bad = *hflag;
-    std::copy(hbp, hbp + size_t(nrhs) * ldb, hb.begin());
     if (bad) return set_error(REXII_ERR_NONFINITE, "non-finite value in f");
-    // scale of A for the breakdown test (beta_j -> 0: an invariant subspace)
-    const double hscale = Hf ? device_hmax(Hf, n, st) : H0;
-    const double rho_ref = std::sqrt(g * hscale) * std::sqrt(double(nx) * nx + double(ny) * ny) + std::fabs(fc);
     std::vector<int> mr(nrhs, 0);     // Krylov dimension per state (0: not fixed yet)
     for (int r = 0; r < nrhs; ++r)
       if (!(hb[size_t(r) * ldb] > 0.0)) mr[r] = -1;  // zero state: u = 0
-    std::vector<std::vector<double>> ys(nrhs);
+    std::vector<std::vector<double>> ys(nrhs), cfs(nrhs);
     std::vector<SmallResult> sr(nrhs);
-    // pass 2 of a state is enqueued as soon as its small problem is solved,
-    // so the GPU runs it while the host solves the next state's; the stream
-    // orders it before any later pass-1 chunk (pass 1 never touches u, and a
-    // state's own coefficients up to its m are never rewritten)
+    // pass 2 of a state is enqueued as soon as its small problem is solved;
+    // the stream orders it before any later pass-1 chunk (pass 1 never touches
+    // u, and a state's own coefficients up to its m are never rewritten)
     std::vector<char> fin(nrhs, 0);
     std::vector<hipEvent_t> ev2(prof ? 2 * nrhs : 0, nullptr);
     struct Ev2Guard {
@@ -2826,44 +2903,81 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       }
     } guard2{ev2};
     for (auto& e : ev2) HIPCHK(hipEventCreate(&e));
-    launch_fill_zero(u, size_t(nrhs) * n3, st);
+    // pass 2: the sum over the kept vectors, then the steps beyond them once
+    // more with u += y_j v_j
+    int64_t m2_kept = 0, m2_again = 0;
     auto pass2 = [&](int r, int mm) {
-      double* Xr = X + size_t(r) * n3;
-      double* Yr = Y + size_t(r) * n3;
+      double* ur = u + size_t(r) * n3;
       double* br = beta + size_t(r) * ldb;
       double* yr = ydev + size_t(r) * ldy;
-      HIPCHK(hipMemcpyAsync(yr, ys[r].data(), size_t(mm) * 8, hipMemcpyHostToDevice, st));
+      const int mk = std::min(mm, kept);
       if (prof) HIPCHK(hipEventRecord(ev2[2 * r], st));
-      launch_lz_start(f + size_t(r) * n3, Xr, Hf, H0, g, nx, ny, 1, part, flag, br, ldb, st);
-      for (int j = 1; j <= mm; ++j) {
-        const double* cur = (j % 2 == 1) ? Xr : Yr;
-        double* prv = (j % 2 == 1) ? Yr : Xr;
-        launch_lz_step(cur, prv, Hf, H0, g, fc, nx, ny, 1, j, br, ldb, nullptr, yr, ldy, u + size_t(r) * n3,
-                       j == mm ? 1 : 0, st);
+      if (mk > 0) {
+        launch_lz_gather(place(1) + size_t(r) * stride, n3, mk, coef, ur, st);
+      } else {
+        launch_fill_zero(ur, n3, st);
+        launch_lz_start(f + size_t(r) * n3, place(1) + size_t(r) * stride, stride, Hf, H0, g, nx, ny, 1, part, flag, br,
+                        ldb, st);
       }
+      for (int j = std::max(mk, 1); j <= mm && mm > mk; ++j)
+        launch_lz_step(place(j) + size_t(r) * stride, place(std::max(j - 1, 1)) + size_t(r) * stride,
+                       place(j + 1) + size_t(r) * stride, stride, Hf, H0, g, fc, nx, ny, 1, j, br, ldb, nullptr, yr,
+                       ldy, j <= mk ? nullptr : ur, j == mm ? 1 : 0, st);
+      m2_kept += mk;
+      m2_again += (mm > mk) ? mm - std::max(mk, 1) + 1 : 0;
       if (prof) HIPCHK(hipEventRecord(ev2[2 * r + 1], st));
       HIPCHK(hipGetLastError());
     };
     const int chunk = 32;
     int m = 0, launched = 0, next_check = 0;
     bool done = false, hit_max = false;
-    double host_s = 0.0;
+    double host_s = 0.0, rho_seen = 0.0;
     auto enqueue = [&](int upto) {
-      for (int j = launched + 1; j <= upto; ++j) {
-        const double* cur = (j % 2 == 1) ? X : Y;
-        double* prv = (j % 2 == 1) ? Y : X;
-        launch_lz_step(cur, prv, Hf, H0, g, fc, nx, ny, nrhs, j, beta, ldb, part, nullptr, 0, nullptr, 0, st);
-      }
+      for (int j = launched + 1; j <= upto; ++j)
+        launch_lz_step(place(j), place(std::max(j - 1, 1)), place(j + 1), stride, Hf, H0, g, fc, nx, ny, nrhs, j, beta,
+                       ldb, part, nullptr, 0, nullptr, 0, st);
       launched = std::max(launched, upto);
     };
+    std::vector<cplx> zp, wp;
+    std::vector<LzPair> pairs;
+    // the small problem of state r at dimension mm: sr[r], and y (and coef) on
+    // the device
+    auto solve_small = [&](int r, int mm) {
+      const double* b = hb.data() + size_t(r) * ldb;
+      sr[r] = small_plan(b, mm, t, o.h, m0, rho_ref, zp, wp);
+      const int np = sr[r].P / 2;
+      double* yr = ydev + size_t(r) * ldy;
+      const size_t pb = al256(size_t(np) * sizeof(LzPair));
+      if (pb + lz_small_bytes(mm, np) <= scr_room) {
+        pairs.resize(np);
+        for (int q = 0; q < np; ++q)
+          pairs[q] = LzPair{make_double2(zp[2 * q].re, zp[2 * q].im), make_double2(wp[2 * q].re, wp[2 * q].im),
+                            make_double2(wp[2 * q + 1].re, wp[2 * q + 1].im)};
+        HIPCHK(hipMemcpyAsync(scr, pairs.data(), size_t(np) * sizeof(LzPair), hipMemcpyHostToDevice, st));
+        launch_lz_small(beta + size_t(r) * ldb, mm, t, reinterpret_cast<const LzPair*>(scr), np, scr + pb, yr, coef,
+                        small_out, st);
+        HIPCHK(hipMemcpyAsync(hsmall, small_out, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+        wait_reads();
+        sr[r].tail = (hsmall[0] > 0.0) ? std::sqrt(hsmall[1] / hsmall[0]) : 0.0;
+      } else {
+        small_problem(b, mm, t, b[0], zp, wp, sr[r], ys[r]);
+        HIPCHK(hipMemcpyAsync(yr, ys[r].data(), size_t(mm) * 8, hipMemcpyHostToDevice, st));
+        if (kept > 0) {
+          cfs[r].resize(mm);
+          for (int j = 0; j < mm; ++j) cfs[r][j] = ys[r][j] / b[j];
+          HIPCHK(hipMemcpyAsync(coef, cfs[r].data(), size_t(mm) * 8, hipMemcpyHostToDevice, st));
+        }
+      }
+    };
     while (!done) {
-      enqueue(std::min(mmax, m + chunk));
+      // straight to the next chunk end at which a check can fall due (the
+      // bound on rho(T) only grows with m)
+      const double due = std::max(double(next_check), 0.75 * t * rho_seen);
+      int to = m + chunk;
+      if (rho_seen > 0.0 && due > to) to = m + chunk * int(std::ceil((due - m) / chunk));
+      enqueue(std::min(mmax, to));
       HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpy2DAsync(hbp + m + 1, size_t(ldb) * 8, beta + m + 1, size_t(ldb) * 8,
-                              size_t(launched - m) * 8, nrhs, hipMemcpyDeviceToHost, st));
-      wait_reads();
-      for (int r = 0; r < nrhs; ++r)
-        std::copy(hbp + size_t(r) * ldb + m + 1, hbp + size_t(r) * ldb + launched + 1, hb.begin() + size_t(r) * ldb + m + 1);
+      read_beta(m + 1, launched);
       m = launched;
       // breakdown: an invariant subspace of dimension j (exact result)
       double rho_all = 0.0;
@@ -2879,23 +2993,23 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
         }
       }
       rho_all = std::min(rho_all, rho_ref);
+      rho_seen = std::max(rho_seen, rho_all);
       const bool all_fixed = std::all_of(mr.begin(), mr.end(), [](int v) { return v != 0; });
       hit_max = (m >= mmax);
       if (!(all_fixed || hit_max || (m >= next_check && m >= 0.75 * t * rho_all))) continue;
-      // the next chunk runs on the GPU while the host solves the small problems
-      if (!all_fixed && !hit_max) enqueue(std::min(mmax, m + chunk));
       const auto h0 = std::chrono::steady_clock::now();
       // states share the operator and converge at similar m: stop at the
       // first one that has not converged yet
       bool conv = true;
       for (int r = 0; r < nrhs; ++r) {
         if (fin[r]) continue;
-        if (mr[r] < 0) {  // zero state: u stays 0
+        if (mr[r] < 0) {  // zero state: u = 0
+          launch_fill_zero(u + size_t(r) * n3, n3, st);
           fin[r] = 1;
           continue;
         }
         const int mm = (mr[r] > 0) ? mr[r] : m;
-        sr[r] = small_problem(hb.data() + size_t(r) * ldb, mm, t, o.h, m0, hb[size_t(r) * ldb], rho_ref, ys[r]);
+        solve_small(r, mm);
         if (!(mr[r] > 0 || hit_max || sr[r].tail <= 0.1 * o.tol)) {
           conv = false;
           break;
@@ -2909,11 +3023,7 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       done = conv || hit_max;
     }
     int mfin = 0;
-    int64_t m2 = 0;  // pass-2 steps over all states
-    for (int r = 0; r < nrhs; ++r) {
-      mfin = std::max(mfin, mr[r]);
-      if (mr[r] > 0) m2 += mr[r];
-    }
+    for (int r = 0; r < nrhs; ++r) mfin = std::max(mfin, mr[r]);
     if (prof) HIPCHK(hipEventRecord(ev[1], st));
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
@@ -2948,10 +3058,12 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       rep->max_rel_residual = tail;
       rep->pole_tol = o.tol;
       // per step and state: pass 1 reads buf_j, buf_{j-1} (and the depth),
-      // writes buf_{j+1}; pass 2 also reads and writes u
-      const double per1 = (Hf ? 80.0 : 72.0), per2 = per1 + 48.0;
-      rep->alg_bytes = (double(launched) * nrhs * per1 + double(m2) * per2) * double(n);
-      rep->kernel_launches = 2 * int64_t(launched) + m2;
+      // writes buf_{j+1}; pass 2 reads each kept vector, and a repeated step
+      // also reads and writes u
+      const double per1 = (Hf ? 80.0 : 72.0);
+      const double bytes2 = (double(m2_kept) * 24.0 + double(m2_again) * (per1 + 48.0)) * double(n);
+      rep->alg_bytes = double(launched) * nrhs * per1 * double(n) + bytes2;
+      rep->kernel_launches = 2 * int64_t(launched) + m2_again + (m2_kept > 0 ? nrhs : 0);
       if (prof) {
         float a = 0.f, b2 = 0.f;
         HIPCHK(hipEventElapsedTime(&a, ev[0], ev[1]));
@@ -2965,7 +3077,7 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
         rep->step_ms[1] = host_s * 1e3;
         rep->step_ms[2] = b2;         // pass 2, summed over states
         rep->kernel_ms = b2;
-        rep->kernel_bytes = double(m2) * double(n) * per2;
+        rep->kernel_bytes = bytes2;
       }
       rep->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     }
@@ -2976,13 +3088,6 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
   } catch (const std::bad_alloc&) {
     return set_error(REXII_ERR_OOM, "host allocation failed");
   }
-}
-
-static size_t multishift_bytes(int nx, int ny, int nrhs, int max_iter) {
-  const size_t n3 = 3 * size_t(nx) * ny;
-  const int mmax = std::max(8, max_iter > 0 ? max_iter : kMultishiftMaxM);
-  return 2 * al256(size_t(nrhs) * n3 * 8) + al256(size_t(nrhs) * lz_blocks(nx, ny) * 8) +
-         al256(size_t(nrhs) * (mmax + 2) * 8) + al256(size_t(nrhs) * mmax * 8) + al256(256);
 }
 
 }  // namespace rexii
@@ -3062,6 +3167,27 @@ rexii_status rexii_multishift_workspace_size(const rexii_swe_op* op, int32_t nrh
   if (v != REXII_OK) return v;
   if (!bytes || nrhs <= 0) return set_error(REXII_ERR_INVALID_ARG, "need bytes and nrhs > 0");
   *bytes = multishift_bytes(op->nx, op->ny, nrhs, resolve_opts(opts).max_iter);
+  return clear_error();
+}
+
+rexii_status rexii_multishift_basis_size(const rexii_swe_op* op, int32_t nrhs, double t, const rexii_opts* opts,
+                                         size_t* bytes) {
+  rexii_status v = check_op_and_t(op, t, true);
+  if (v != REXII_OK) return v;
+  if (!bytes || nrhs <= 0) return set_error(REXII_ERR_INVALID_ARG, "need bytes and nrhs > 0");
+  const rexii_opts o = resolve_opts(opts);
+  try {
+    double hs = op->H0;
+    if (op->H_field) {
+      CtxHold hold;
+      hs = device_hmax(op->H_field, size_t(op->nx) * op->ny, nullptr);
+    }
+    const double rho = std::sqrt(op->g * hs) * std::sqrt(double(op->nx) * op->nx + double(op->ny) * op->ny) +
+                       std::fabs(op->f_cor);
+    *bytes = multishift_basis_bytes(op->nx, op->ny, nrhs, o.max_iter, o.h, t * rho);
+  } catch (const HipError& he) {
+    return set_error(he.st, he.msg);
+  }
   return clear_error();
 }
 
