@@ -104,6 +104,49 @@ __device__ __forceinline__ double lane_value(double v, int l) {
   return __longlong_as_double((long long)((static_cast<unsigned long long>(hi) << 32) | lo));
 }
 
+// A block's place among the groups of a launch.  Groups fill in the order in
+// which blocks start (of any XCD, or with gpx > 0 of one XCD each, gpx groups
+// per XCD): a block waits only for blocks that start as soon as others leave.
+// ctl: [8 + x] tickets, then per group at kChipCtlHead + g kChipCtlGroup:
+// [0] arrivals, [1] state (0 forming, 1 ready, 2 cancelled).  Returns false
+// for a block beyond the groups and for a group that did not fill (*late).
+struct GroupPlace {
+  int gid, rank, xcd;
+};
+__device__ __forceinline__ bool join_group(int* ctl, int G, int gpx, int* sh, GroupPlace& gp, bool& late) {
+  if (threadIdx.x == 0) {
+    int x = 0;
+    if (gpx > 0) asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
+    x &= 7;
+    const int ticket = __hip_atomic_fetch_add(&ctl[8 + x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int k = ticket / G;
+    const bool over = gpx > 0 && k >= gpx;
+    const int g = x * gpx + k;
+    int* w = ctl + kChipCtlHead + (over ? 0 : g) * kChipCtlGroup;
+    if (!over && __hip_atomic_fetch_add(&w[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1)
+      atomicCAS(&w[1], 0, 1);
+    unsigned n = 0;
+    int st = 2, lt = 0;
+    while (!over && (st = ldc(&w[1])) == 0) {
+      if (++n > kFormPolls && atomicCAS(&w[1], 0, 2) == 0) lt = 1;
+      __builtin_amdgcn_s_sleep(2);
+    }
+    sh[0] = st;
+    sh[1] = g;
+    sh[2] = ticket - k * G;
+    sh[3] = x;
+    sh[4] = lt;
+  }
+  __syncthreads();
+  const bool ok = uni(sh[0]) == 1;
+  gp.gid = uni(sh[1]);
+  gp.rank = uni(sh[2]);
+  gp.xcd = uni(sh[3]);
+  late = uni(sh[4]) != 0;
+  __syncthreads();
+  return ok;
+}
+
 }  // namespace rexii
 
 #endif

@@ -84,7 +84,6 @@ struct ChipCtl {       // in LDS: what one thread or wavefront tells the block
   int act;             // 1: the inner solve has ended
   int bad;             // a wait gave up
   int slot;
-  int ticket;
 };
 
 }  // namespace
@@ -117,35 +116,15 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
   const bool local = c.gpx > 0;
   if (tid == 0) ctl.bad = 0;
   if (G > 1) {
-    if (tid == 0) {
-      // with gpx groups per XCD a group takes blocks of one XCD
-      int x = 0;
-      if (local) asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
-      x &= 7;
-      const int ticket = __hip_atomic_fetch_add(&c.ctl[8 + x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int g = x * c.gpx + ticket / G;
-      // (a block beyond its XCD's groups has nothing to do: state 2)
-      const bool over = local && ticket / G >= c.gpx;
-      int* w = c.ctl + kChipCtlHead + (over ? 0 : g) * kChipCtlGroup;
-      // state word w[1]: 0 forming, 1 ready, 2 cancelled
-      if (!over && __hip_atomic_fetch_add(&w[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1)
-        atomicCAS(&w[1], 0, 1);
-      unsigned n = 0;
-      int st = 2;
-      while (!over && (st = ldc(&w[1])) == 0) {
-        if (++n > kFormPolls && atomicCAS(&w[1], 0, 2) == 0) e.counter[2] = 2;
-        __builtin_amdgcn_s_sleep(2);
-      }
-      ctl.ticket = g * G + ticket % G;
-      ctl.slot = st;
+    GroupPlace gp;
+    bool late = false;
+    if (!join_group(c.ctl, G, c.gpx, reinterpret_cast<int*>(red), gp, late)) {
+      if (late && tid == 0) e.counter[2] = 2;
+      return;
     }
-    __syncthreads();
-    const int ticket = uni(ctl.ticket);
-    if (uni(ctl.slot) != 1) return;
-    gid = ticket / G;
-    rank = ticket - gid * G;
+    gid = gp.gid;
+    rank = gp.rank;
     gc = c.ctl + kChipCtlHead + gid * kChipCtlGroup;
-    __syncthreads();
   }
   // ---- geometry of the block's strip and of the thread's items
   const bool ringed = c.Gc > 1;

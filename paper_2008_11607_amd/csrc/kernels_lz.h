@@ -15,6 +15,30 @@ struct LzPair {
   double2 z, w1, w2;
 };
 
+// A launch of Lanczos steps with the vectors on the chip (k_lz_chip).
+constexpr int kLzChipMaxG = 256;
+struct LzChip {
+  int nx, ny, nrhs;
+  int G, Sc, nt, rt, lds;   // blocks a state, runs a column, threads, rows a run, LDS bytes
+  int gpx, rec_stride;      // groups per XCD (a state then lies on one) or 0; words between records
+  int groups, ctl_words;
+  int j0, steps;            // first step (1-based) and their number
+  int kept, ldb;            // vectors kept in memory (place of buf_j: see run_multishift), row of beta
+  size_t stride;            // doubles between states
+  double g, fc, H0;
+  const double* H;          // depth field or nullptr
+  double* vecs;
+  double* beta;
+  unsigned long long* rec;
+  unsigned long long* ring;
+  int* ctl;
+  int* flag;                // 1: a wait passed its limit, 2: a group did not form
+};
+bool lz_chip_config(int nx, int ny, int nrhs, bool depth, int cus, LzChip* c);
+size_t lz_chip_bytes(const LzChip& c);
+void lz_chip_mailboxes(LzChip& c, void* mem, hipStream_t s);
+void launch_lz_chip(const LzChip& c, hipStream_t s);
+
 int lz_blocks(int nx, int ny);
 // buf = f, beta[r][0] = ||f_r||_W, flag[0] |= 1 on a non-finite value of f.
 void launch_lz_start(const double* f, double* buf, size_t stride, const double* H, double H0, double g, int nx, int ny,

@@ -25,8 +25,12 @@
 // w_j = buf_{j+1}, to a place of its own or over buf_{j-1}.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
 #include "kernels_lz.h"
-#include "device_util.h"
+#include "chip_sync.h"
 
 namespace rexii {
 
@@ -175,6 +179,297 @@ __global__ __launch_bounds__(kLzNT) void k_lz_norm(const double* __restrict__ pa
   for (int k = threadIdx.x; k < nblk; k += kLzNT) s += part[size_t(r) * nblk + k];
   s = block_sum_lz(s, sh);
   if (threadIdx.x == 0) beta[size_t(r) * ldb + slot] = sqrt(s);
+}
+
+// ---------------------------------------------------------------------------
+// Lanczos steps with the vectors on the chip.  A group of G blocks holds a
+// state: a block has a strip of grid rows, a thread a column's run of RT (or
+// RT - 1) rows with buf_j and buf_{j-1} (and the depth) in registers; LDS
+// holds eta and H u for the east and west neighbours and the runs' edge rows
+// of H v.  A launch runs `steps` steps from the vectors in memory; a step
+// writes buf_{j+1} there (the basis), posts eta and H v of the strip's edge
+// rows and one partial norm, and waits once for the other blocks, as the
+// chip COCG kernel does (three mailbox buffers, emptied in turn).
+//
+// Bound: the exchange.  One launch of k_lz_step and one of k_lz_norm a step
+// took 14 us at 512^2 and 12 us at 64^2.
+// ---------------------------------------------------------------------------
+template <int RT, bool DEPTH>
+__global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lz_lds[];
+  __shared__ double red[8];
+  __shared__ double bc[3];      // 1 / beta_j, beta_j / beta_{j-1}, beta_j
+  __shared__ int sh[8];
+  constexpr int PR = RT | 1;
+  const int tid = int(threadIdx.x), nt = int(blockDim.x), lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6;
+  const int nx = c.nx, ny = c.ny, G = c.G;
+  const bool local = c.gpx > 0;
+  int st = int(blockIdx.x), rank = 0, gid = st;
+  if (tid == 0) sh[5] = 0;      // a wait gave up
+  if (G > 1) {
+    GroupPlace gp;
+    bool late = false;
+    if (!join_group(c.ctl, G, c.gpx, sh, gp, late)) {
+      if (late && tid == 0) c.flag[0] = 2;
+      return;
+    }
+    gid = gp.gid;
+    rank = gp.rank;
+    st = local ? (gid - gp.xcd * c.gpx) * 8 + gp.xcd : gid;
+    if (st >= c.nrhs) return;
+  }
+  const size_t n = size_t(nx) * ny, n3 = 3 * n;
+  double* vec = c.vecs + size_t(st) * c.stride;
+  double* br = c.beta + size_t(st) * c.ldb;
+  auto place = [&](int j) { return vec + size_t(j <= c.kept ? j - 1 : c.kept + ((j - c.kept - 1) & 1)) * n3; };
+  // ---- the block's rows ya .. ya + R - 1 and the thread's run of them
+  const int ya = int((long long)rank * ny / G), R = int((long long)(rank + 1) * ny / G) - ya;
+  const int s = tid / nx;
+  const bool valid = s < c.Sc;
+  const int col = valid ? tid - s * nx : 0, seg = valid ? s : 0;
+  auto first_row = [&](int q) { return int((long long)q * R / c.Sc); };
+  const int r0 = first_row(seg);
+  const bool full = first_row(seg + 1) - r0 == RT;
+  const bool rtop = valid && G > 1 && seg == 0, rbot = valid && G > 1 && seg == c.Sc - 1;
+  const int su = (seg == 0) ? c.Sc - 1 : seg - 1, sd = (seg == c.Sc - 1) ? 0 : seg + 1;
+  const int item = seg * nx + col, iu = su * nx + col, id = sd * nx + col;
+  const int base = item * PR;
+  const int west = (seg * nx + (col == 0 ? nx - 1 : col - 1)) * PR, east = (seg * nx + (col + 1 == nx ? 0 : col + 1)) * PR;
+  const int utop = iu * PR + first_row(su + 1) - first_row(su) - 1, ubot = id * PR;
+  const int items = c.Sc * nx;
+  double* E = reinterpret_cast<double*>(lz_lds);
+  double* U = E + size_t(items) * PR;
+  double* VT = U + size_t(items) * PR;   // H v of a run's first row
+  double* VB = VT + items;               // ... and of its last
+  const int y0 = ya + r0;
+  auto gofs = [&](int i) {               // grid point of row i (-1 .. RT) of the run
+    int y = y0 + i;
+    y = (y < 0) ? y + ny : (y >= ny ? y - ny : y);
+    return unsigned(y * nx + col);
+  };
+  unsigned long long* rec = c.rec + size_t(gid) * 3 * G * c.rec_stride;
+  unsigned long long* ring = c.ring + size_t(gid) * 3 * G * 4 * nx;   // [3][G][top eta, H v, bottom eta, H v][nx]
+  const int up_rank = (rank == 0) ? G - 1 : rank - 1, dn_rank = (rank + 1 == G) ? 0 : rank + 1;
+  const double hx = 0.5 * nx, hy = 0.5 * ny, g = c.g, fc = c.fc;
+
+  double A[3][RT], B[3][RT], H[DEPTH ? RT : 1];
+  double et = 0.0, vt = 0.0, eb = 0.0, vb = 0.0;   // ring rows: eta and H v above and below
+  {
+    const double* cu = place(c.j0);
+    const double* pv = place(c.j0 > 1 ? c.j0 - 1 : 1);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const bool in = valid && (i < RT - 1 || full);
+      const unsigned q = in ? gofs(i) : 0u;
+      if (DEPTH) H[i] = in ? c.H[q] : 0.0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        A[k][i] = in ? cu[k * n + q] : 0.0;
+        B[k][i] = (in && c.j0 > 1) ? pv[k * n + q] : 0.0;
+      }
+    }
+    if (rtop) {
+      const unsigned q = gofs(-1);
+      et = cu[q];
+      vt = (DEPTH ? c.H[q] : c.H0) * cu[2 * n + q];
+    }
+    if (rbot) {
+      const unsigned q = gofs(full ? RT : RT - 1);
+      eb = cu[q];
+      vb = (DEPTH ? c.H[q] : c.H0) * cu[2 * n + q];
+    }
+  }
+  auto depth = [&](int i) { return DEPTH ? H[DEPTH ? i : 0] : c.H0; };
+  // eta, H u and the edge rows of H v of a vector into LDS
+  auto share = [&](const double (&v)[3][RT]) __attribute__((always_inline)) {
+    if (!valid) return;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+      if (i < RT - 1 || full) {
+        E[base + i] = v[0][i];
+        U[base + i] = depth(i) * v[1][i];
+      }
+    VT[item] = depth(0) * v[2][0];
+    VB[item] = (full || RT == 1) ? depth(RT - 1) * v[2][RT - 1] : depth(RT > 1 ? RT - 2 : 0) * v[2][RT > 1 ? RT - 2 : 0];
+  };
+  share(A);
+  double bj1 = br[c.j0 - 1], sc = 1.0 / bj1, sp = (c.j0 >= 2) ? bj1 / br[c.j0 - 2] : 0.0;
+  __syncthreads();
+  unsigned sync_no = 0;
+  bool bad = false;
+  // step j: cu = buf_j, pv = buf_{j-1}, replaced by buf_{j+1}
+  auto step = [&](const double (&cu)[3][RT], double (&pv)[3][RT], int j) __attribute__((always_inline)) {
+    const unsigned buf = sync_no % 3u, obuf = (sync_no + 2u) % 3u;
+    double acc = 0.0;
+    if (valid) {
+      double eS = rtop ? et : E[utop], vS = rtop ? vt : VB[iu];
+      const double eL = rbot ? eb : E[ubot], vL = rbot ? vb : VT[id];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        double eN, vN;
+        if (i == RT - 1) {
+          eN = eL;
+          vN = vL;
+        } else {
+          eN = cu[0][i + 1];
+          vN = depth(i + 1) * cu[2][i + 1];
+          if (i == RT - 2) {
+            eN = full ? eN : eL;
+            vN = full ? vN : vL;
+          }
+        }
+        const double ae = -(hx * (U[east + i] - U[west + i]) + hy * (vN - vS));
+        const double au = -g * hx * (E[east + i] - E[west + i]) + fc * cu[2][i];
+        const double av = -g * hy * (eN - eS) - fc * cu[1][i];
+        eS = cu[0][i];
+        vS = depth(i) * cu[2][i];
+        double w0 = sc * ae + sp * pv[0][i], w1 = sc * au + sp * pv[1][i], w2 = sc * av + sp * pv[2][i];
+        if (i == RT - 1 && !full) w0 = w1 = w2 = 0.0;
+        pv[0][i] = w0;
+        pv[1][i] = w1;
+        pv[2][i] = w2;
+        acc += g * w0 * w0 + depth(i) * (w1 * w1 + w2 * w2);
+      }
+    }
+    acc = wave_total63(acc);
+    if (lane == 63) red[wid] = acc;
+    if (G > 1) stores_done();   // the words emptied after the last sync
+    __syncthreads();            // every neighbour value has been read
+    share(pv);
+    if (G > 1) {
+      unsigned long long* rx = ring + (size_t(buf) * G + rank) * 4 * nx + col;
+      if (rtop) {
+        post(rx, pv[0][0], local);
+        post(rx + nx, depth(0) * pv[2][0], local);
+      }
+      if (rbot) {
+        const int l = RT > 1 ? RT - 2 : 0;
+        post(rx + 2 * nx, full ? pv[0][RT - 1] : pv[0][l], local);
+        post(rx + 3 * nx, full ? depth(RT - 1) * pv[2][RT - 1] : depth(l) * pv[2][l], local);
+      }
+    }
+    if (wid == 0) {
+      double v = 0.0;
+      for (int k = 0; k < nw; ++k) v += red[k];
+      if (G > 1) {
+        unsigned long long* rb = rec + size_t(buf) * G * c.rec_stride;
+        if (lane == 0) post(rb + size_t(rank) * c.rec_stride, v, local);
+        v = 0.0;
+        for (int b0 = 0; b0 < G; b0 += 64) {
+          const unsigned long long* th = rb + size_t(b0 + lane < G ? b0 + lane : 0) * c.rec_stride;
+          unsigned long long w;
+          unsigned k = 0;
+          while (!__all((w = ald(th)) != kNoWord)) {
+            if (++k > kRunPolls) {
+              sh[5] = 1;
+              break;
+            }
+          }
+          const double t = wave_total63(b0 + lane < G ? __longlong_as_double((long long)w) : 0.0);
+          v += lane_value(t, 63);
+        }
+      }
+      const double b = sqrt(v);
+      if (lane == 0) {
+        bc[0] = 1.0 / b;
+        bc[1] = b / bj1;
+        bc[2] = b;
+        if (rank == 0) br[j] = b;
+      }
+    }
+    // the vector, for the basis and the next launch
+    if (valid) {
+      double* ov = place(j + 1);
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+        if (i < RT - 1 || full) {
+          const unsigned q = gofs(fresh(i));
+          __builtin_nontemporal_store(pv[0][i], ov + q);
+          __builtin_nontemporal_store(pv[1][i], ov + n + q);
+          __builtin_nontemporal_store(pv[2][i], ov + 2 * n + q);
+        }
+    }
+    if (G > 1) {
+      const unsigned long long* rup = ring + (size_t(buf) * G + up_rank) * 4 * nx + 2 * nx + col;
+      const unsigned long long* rdn = ring + (size_t(buf) * G + dn_rank) * 4 * nx + col;
+      unsigned k = 0;
+      if (rtop) {
+        unsigned long long a, b;
+        while ((a = ald(rup)) == kNoWord || (b = ald(rup + nx)) == kNoWord) {
+          if (++k > kRunPolls) {
+            sh[5] = 1;
+            break;
+          }
+        }
+        et = __longlong_as_double((long long)a);
+        vt = __longlong_as_double((long long)ald(rup + nx));
+      }
+      if (rbot) {
+        unsigned long long a, b;
+        while ((a = ald(rdn)) == kNoWord || (b = ald(rdn + nx)) == kNoWord) {
+          if (++k > kRunPolls) {
+            sh[5] = 1;
+            break;
+          }
+        }
+        eb = __longlong_as_double((long long)a);
+        vb = __longlong_as_double((long long)ald(rdn + nx));
+      }
+    }
+    __syncthreads();
+    ++sync_no;
+    sc = bc[0];
+    sp = bc[1];
+    bj1 = bc[2];
+    if (G > 1) {
+      if (tid == 0) mst(rec + (size_t(obuf) * G + rank) * c.rec_stride, kNoWord, local);
+      unsigned long long* rx = ring + (size_t(obuf) * G + rank) * 4 * nx + col;
+      if (rtop) {
+        mst(rx, kNoWord, local);
+        mst(rx + nx, kNoWord, local);
+      }
+      if (rbot) {
+        mst(rx + 2 * nx, kNoWord, local);
+        mst(rx + 3 * nx, kNoWord, local);
+      }
+      bad = uni(sh[5]) != 0;
+    }
+  };
+  for (int k = 0; k < c.steps && !bad; k += 2) {
+    step(A, B, c.j0 + k);
+    if (k + 1 >= c.steps || bad) break;
+    step(B, A, c.j0 + k + 1);
+  }
+  if (bad) {
+    if (tid == 0) c.flag[0] = 1;
+    return;
+  }
+  // ---- the mailboxes empty for the next launch
+  if (G > 1) {
+    stores_done();
+    __syncthreads();
+    if (tid == 0) {
+      int* gc = c.ctl + kChipCtlHead + gid * kChipCtlGroup;
+      __hip_atomic_fetch_add(&gc[2], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned k = 0;
+      while (ldc(&gc[2]) < G) {
+        if (++k > kRunPolls) {
+          c.flag[0] = 1;
+          break;
+        }
+      }
+    }
+    __syncthreads();
+    if (tid < 3) ast(rec + (size_t(tid) * G + rank) * c.rec_stride, kNoWord);
+    for (int k = tid; k < 12 * nx; k += nt) ast(ring + (size_t(k / (4 * nx)) * G + rank) * 4 * nx + k % (4 * nx), kNoWord);
+  }
+}
+
+// Zeroes the control words and the flag before a launch.
+__global__ __launch_bounds__(256) void k_lz_ctl(int* ctl, int words, int* flag) {
+  for (int k = threadIdx.x; k < words; k += 256) ctl[k] = 0;
+  if (threadIdx.x == 0) flag[0] = 0;
 }
 
 // u = sum_j coef[j] buf_{j+1}, j < m, the vectors n3 doubles apart: memory
@@ -338,6 +633,99 @@ void launch_lz_gather(const double* vecs, size_t n3, int m, const double* coef, 
     hipLaunchKernelGGL(k_lz_gather<double2>, grid, dim3(256), 0, s, vecs, n3, m, coef, u);
   else
     hipLaunchKernelGGL(k_lz_gather<double>, grid, dim3(256), 0, s, vecs, n3, m, coef, u);
+}
+
+namespace {
+using LzChipFn = void (*)(LzChip);
+constexpr int kLzMaxRT = 10;
+template <bool D>
+LzChipFn lz_chip_fn(int rt) {
+  static const LzChipFn f[kLzMaxRT] = {k_lz_chip<1, D>, k_lz_chip<2, D>, k_lz_chip<3, D>, k_lz_chip<4, D>,
+                                       k_lz_chip<5, D>, k_lz_chip<6, D>, k_lz_chip<7, D>, k_lz_chip<8, D>,
+                                       k_lz_chip<9, D>, k_lz_chip<10, D>};
+  return f[rt - 1];
+}
+}  // namespace
+
+// Launch shape of k_lz_chip; false where no shape fits or k_lz_step is the
+// faster.  Estimates in us, from steps timed on MI355X: a thread's row takes
+// about 40 VALU instructions, a step 250 more; the exchange about 1.6 us on
+// one XCD and 2.3 us + 12 ns a block across; the vector's write is bound by
+// about 0.4 TB/s per XCD.  k_lz_step and k_lz_norm: 10 us + 80 bytes a point
+// at 5 TB/s.
+bool lz_chip_config(int nx, int ny, int nrhs, bool depth, int cus, LzChip* c) {
+  double best = 10.0 + 80.0 * nx * double(ny) * nrhs / 5e6;
+  bool found = false;
+  for (int Sc = 1; Sc * nx <= 512; ++Sc) {
+    const int nt = (Sc * nx + 63) / 64 * 64;
+    for (int rt = 1; rt <= kLzMaxRT; ++rt) {
+      const int G = (ny + Sc * rt - 1) / (Sc * rt);
+      if ((ny + G * Sc - 1) / (G * Sc) != rt || ny < G * Sc || G > kLzChipMaxG) continue;
+      if (G > 1 && ny / G < 1) continue;
+      const size_t lds = (size_t(2) * (rt | 1) + 2) * Sc * nx * 8;
+      if (lds > size_t(kChipMaxLds)) continue;
+      const void* f = reinterpret_cast<const void*>(depth ? lz_chip_fn<true>(rt) : lz_chip_fn<false>(rt));
+      if (lds > 48 * 1024 &&
+          hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kChipMaxLds) != hipSuccess) {
+        (void)hipGetLastError();
+        continue;
+      }
+      int occ = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, nt, lds) != hipSuccess || occ < 1) {
+        (void)hipGetLastError();
+        continue;
+      }
+      for (int loc = 0; loc < 2; ++loc) {
+        const int gpx = (nrhs + 7) / 8, fit = (cus / 8) * occ / G;   // groups an XCD has to take, and can at once
+        if (loc && (G == 1 || fit < 1)) continue;
+        if (!loc && cus * occ < G) continue;
+        const double turns = loc ? std::ceil(double(gpx) / fit) : std::ceil(double(nrhs) / (cus * occ / G));
+        const double valu = ((nt / 64 + 3) / 4) * 4.0 * (rt * 40.0 + 250.0) / 2370.0;
+        const double wr = 24.0 * nx * double(ny) / 0.4e6 * (loc ? std::min(fit, gpx) : std::max(1.0, double(nrhs) / turns) / std::min(8.0, double(G)));
+        const double t = turns * std::max(valu + (G == 1 ? 0.7 : loc ? 1.6 : 2.3 + 0.012 * G), wr);
+        if (t < best) {
+          best = t;
+          found = true;
+          c->nx = nx;
+          c->ny = ny;
+          c->nrhs = nrhs;
+          c->G = G;
+          c->Sc = Sc;
+          c->nt = nt;
+          c->rt = rt;
+          c->lds = int(lds);
+          c->gpx = loc ? gpx : 0;
+          c->rec_stride = loc ? kChipRec : 1;
+          c->groups = loc ? 8 * gpx : nrhs;
+          c->ctl_words = kChipCtlHead + kChipCtlGroup * c->groups;
+        }
+      }
+    }
+  }
+  return found;
+}
+size_t lz_chip_bytes(const LzChip& c) {
+  const size_t rec = size_t(c.groups) * 3 * c.G * c.rec_stride * 8, ring = size_t(c.groups) * 12 * c.G * c.nx * 8;
+  return (c.G > 1 ? ring + rec : 0) + size_t(c.ctl_words) * 4 + 1024;
+}
+// Lays the mailboxes out in mem (256-byte aligned) and empties them.
+void lz_chip_mailboxes(LzChip& c, void* mem, hipStream_t s) {
+  const size_t rec = (size_t(c.groups) * 3 * c.G * c.rec_stride * 8 + 255) / 256 * 256;
+  const size_t ring = size_t(c.groups) * 12 * c.G * c.nx * 8;
+  char* p = static_cast<char*>(mem);
+  c.ctl = reinterpret_cast<int*>(p);
+  p += (size_t(c.ctl_words) * 4 + 255) / 256 * 256;
+  c.rec = reinterpret_cast<unsigned long long*>(p);
+  c.ring = reinterpret_cast<unsigned long long*>(p + rec);
+  if (c.G == 1) return;
+  double none;
+  memset(&none, 0xff, sizeof(none));
+  launch_fill_value(reinterpret_cast<double*>(c.rec), (rec + ring) / 8, none, s);
+}
+void launch_lz_chip(const LzChip& c, hipStream_t s) {
+  hipLaunchKernelGGL(k_lz_ctl, dim3(1), dim3(256), 0, s, c.ctl, c.ctl_words, c.flag);
+  hipLaunchKernelGGL(c.H ? lz_chip_fn<true>(c.rt) : lz_chip_fn<false>(c.rt), dim3(c.groups * c.G), dim3(c.nt), c.lds, s,
+                     c);
 }
 
 size_t lz_small_bytes(int m, int npair) {

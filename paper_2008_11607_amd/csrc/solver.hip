@@ -2752,6 +2752,18 @@ static size_t lz_scratch(double trho, double h, int mmax) {
   return al256(size_t(np) * sizeof(LzPair)) + al256(lz_small_bytes(lz_expect_m(trho, mmax), np));
 }
 constexpr size_t kLzBudget = size_t(32) << 30;   // most bytes of kept vectors asked for
+constexpr size_t kLzOwn = size_t(2) << 30;       // ... and allocated by a call without a workspace
+// the chip kernel's shape on the current device, if it is to be used
+static bool lz_shape(int nx, int ny, int nrhs, bool depth, LzChip* c) {
+  std::memset(static_cast<void*>(c), 0, sizeof(*c));
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return lz_chip_config(nx, ny, nrhs, depth, cus, c);
+}
 
 static size_t multishift_bytes(int nx, int ny, int nrhs, int max_iter) {
   const size_t n3 = 3 * size_t(nx) * ny;
@@ -2760,12 +2772,15 @@ static size_t multishift_bytes(int nx, int ny, int nrhs, int max_iter) {
          al256(size_t(nrhs) * (mmax + 2) * 8) + al256(size_t(nrhs) * mmax * 8) + al256(256);
 }
 // ... and with room for the vectors and the small problem to expect for t rho
-static size_t multishift_basis_bytes(int nx, int ny, int nrhs, int max_iter, double h, double trho) {
+static size_t multishift_basis_bytes(int nx, int ny, int nrhs, int max_iter, bool depth, double h, double trho,
+                                     size_t budget) {
   const int mmax = std::max(8, max_iter > 0 ? max_iter : kMultishiftMaxM);
   const size_t vec = size_t(nrhs) * 3 * size_t(nx) * ny * 8;
-  const size_t kept = std::min<size_t>(size_t(lz_expect_m(trho, mmax)), kLzBudget / vec);
-  return multishift_bytes(nx, ny, nrhs, max_iter) + lz_scratch(trho, h, mmax) + al256(size_t(mmax) * 8) + kept * vec +
-         4096;
+  const size_t kept = std::min<size_t>(size_t(lz_expect_m(trho, mmax)), budget / vec);
+  LzChip c;
+  const size_t mail = lz_shape(nx, ny, nrhs, depth, &c) ? al256(lz_chip_bytes(c)) : 0;
+  return multishift_bytes(nx, ny, nrhs, max_iter) + lz_scratch(trho, h, mmax) + al256(size_t(mmax) * 8) + mail +
+         kept * vec + 4096;
 }
 
 
@@ -2795,19 +2810,25 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     const size_t need = multishift_bytes(nx, ny, nrhs, o.max_iter);
     // pinned staging of the device's set, if no other call holds it
     CtxHold hold;
-    Arena ar(ws, ws_bytes);
-    if (!ws) {
-      ar.reserve_own(need + 4096);
-    } else if (ws_bytes < need) {
-      return set_error(REXII_ERR_WORKSPACE, "workspace smaller than rexii_multishift_workspace_size()");
-    } else if (reinterpret_cast<uintptr_t>(ws) & 255) {
-      return set_error(REXII_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-    }
     const double* Hf = op->H_field;
     const double H0 = op->H0, g = op->g, fc = op->f_cor;
+    if (ws && ws_bytes < need)
+      return set_error(REXII_ERR_WORKSPACE, "workspace smaller than rexii_multishift_workspace_size()");
+    if (ws && (reinterpret_cast<uintptr_t>(ws) & 255))
+      return set_error(REXII_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
     // scale of A for the breakdown test (beta_j -> 0: an invariant subspace)
     const double hscale = Hf ? device_hmax(Hf, n, st) : H0;
     const double rho_ref = std::sqrt(g * hscale) * std::sqrt(double(nx) * nx + double(ny) * ny) + std::fabs(fc);
+    Arena ar(ws, ws_bytes);
+    if (!ws) {
+      try {
+        ar.reserve_own(
+            multishift_basis_bytes(nx, ny, nrhs, o.max_iter, Hf != nullptr, o.h, t * rho_ref, kLzOwn));
+      } catch (const HipError&) {
+        (void)hipGetLastError();
+        ar.reserve_own(need + 4096);
+      }
+    }
     double* part = ar.take<double>(size_t(nrhs) * nb);
     double* beta = ar.take<double>(size_t(nrhs) * ldb);
     double* ydev = ar.take<double>(size_t(nrhs) * ldy);
@@ -2822,6 +2843,15 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     double* coef = scr_bytes ? ar.take<double>(mmax) : nullptr;
     char* scr = scr_bytes ? ar.take<char>(scr_bytes - al256(size_t(mmax) * 8)) : nullptr;
     const size_t scr_room = scr_bytes ? scr_bytes - al256(size_t(mmax) * 8) : 0;
+    LzChip chip;
+    bool on_chip = scr && lz_shape(nx, ny, nrhs, Hf != nullptr, &chip);
+    if (on_chip) {
+      const size_t mail = lz_chip_bytes(chip);
+      if (ar.remaining() < two + al256(mail) + 1024)
+        on_chip = false;
+      else
+        lz_chip_mailboxes(chip, ar.take<char>(mail), st);
+    }
     const size_t room = ar.remaining() / 256 * 256;
     const int kept = scr ? int(std::min<size_t>(size_t(mmax), (room - two) / (size_t(nrhs) * n3 * 8))) : 0;
     const size_t stride = size_t(kept + 2) * n3;
@@ -2932,7 +2962,26 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     int m = 0, launched = 0, next_check = 0;
     bool done = false, hit_max = false;
     double host_s = 0.0, rho_seen = 0.0;
+    if (on_chip) {
+      chip.kept = kept;
+      chip.ldb = ldb;
+      chip.stride = stride;
+      chip.g = g;
+      chip.fc = fc;
+      chip.H0 = H0;
+      chip.H = Hf;
+      chip.vecs = vecs;
+      chip.beta = beta;
+      chip.flag = flag;
+    }
     auto enqueue = [&](int upto) {
+      if (on_chip && upto > launched) {
+        chip.j0 = launched + 1;
+        chip.steps = upto - launched;
+        launch_lz_chip(chip, st);
+        launched = upto;
+        return;
+      }
       for (int j = launched + 1; j <= upto; ++j)
         launch_lz_step(place(j), place(std::max(j - 1, 1)), place(j + 1), stride, Hf, H0, g, fc, nx, ny, nrhs, j, beta,
                        ldb, part, nullptr, 0, nullptr, 0, st);
@@ -2977,7 +3026,15 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       if (rho_seen > 0.0 && due > to) to = m + chunk * int(std::ceil((due - m) / chunk));
       enqueue(std::min(mmax, to));
       HIPCHK(hipGetLastError());
+      if (on_chip) HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
       read_beta(m + 1, launched);
+      if (on_chip && *hflag != 0) {
+        if (*hflag == 1) throw HipError{REXII_ERR_HIP, "a block of the Lanczos kernel waited past its limit"};
+        // a group of blocks did not come together: these steps once more, one launch each
+        on_chip = false;
+        launched = m;
+        continue;
+      }
       m = launched;
       // breakdown: an invariant subspace of dimension j (exact result)
       double rho_all = 0.0;
@@ -3184,7 +3241,7 @@ rexii_status rexii_multishift_basis_size(const rexii_swe_op* op, int32_t nrhs, d
     }
     const double rho = std::sqrt(op->g * hs) * std::sqrt(double(op->nx) * op->nx + double(op->ny) * op->ny) +
                        std::fabs(op->f_cor);
-    *bytes = multishift_basis_bytes(op->nx, op->ny, nrhs, o.max_iter, o.h, t * rho);
+    *bytes = multishift_basis_bytes(op->nx, op->ny, nrhs, o.max_iter, op->H_field != nullptr, o.h, t * rho, kLzBudget);
   } catch (const HipError& he) {
     return set_error(he.st, he.msg);
   }
