@@ -189,10 +189,13 @@ __global__ __launch_bounds__(kLzNT) void k_lz_norm(const double* __restrict__ pa
 // of H v.  A launch runs `steps` steps from the vectors in memory; a step
 // writes buf_{j+1} there (the basis), posts eta and H v of the strip's edge
 // rows and one partial norm, and waits once for the other blocks, as the
-// chip COCG kernel does (three mailbox buffers, emptied in turn).
+// chip COCG kernel does.  Four mailbox buffers: the words of sync i are
+// emptied after sync i + 1 and known to be gone at the end of i + 2, before
+// the record of i + 3 is posted; nobody looks for i + 4 before it has that.
 //
 // Bound: the exchange.  One launch of k_lz_step and one of k_lz_norm a step
-// took 14 us at 512^2 and 12 us at 64^2.
+// took 14 us at 512^2 and 12 us at 64^2, a step here 7.5 and 2.4 us (whole
+// calls: 512^2, t rho 1000 17.3 -> 12.0 ms; 64^2, t rho 100 4.0 -> 0.9 ms).
 // ---------------------------------------------------------------------------
 template <int RT, bool DEPTH>
 __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
@@ -248,8 +251,8 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
     y = (y < 0) ? y + ny : (y >= ny ? y - ny : y);
     return unsigned(y * nx + col);
   };
-  unsigned long long* rec = c.rec + size_t(gid) * 3 * G * c.rec_stride;
-  unsigned long long* ring = c.ring + size_t(gid) * 3 * G * 4 * nx;   // [3][G][top eta, H v, bottom eta, H v][nx]
+  unsigned long long* rec = c.rec + size_t(gid) * 4 * G * c.rec_stride;
+  unsigned long long* ring = c.ring + size_t(gid) * 16 * G * nx;   // [4][G][top eta, H v, bottom eta, H v][nx]
   const int up_rank = (rank == 0) ? G - 1 : rank - 1, dn_rank = (rank + 1 == G) ? 0 : rank + 1;
   const double hx = 0.5 * nx, hy = 0.5 * ny, g = c.g, fc = c.fc;
 
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
   bool bad = false;
   // step j: cu = buf_j, pv = buf_{j-1}, replaced by buf_{j+1}
   auto step = [&](const double (&cu)[3][RT], double (&pv)[3][RT], int j) __attribute__((always_inline)) {
-    const unsigned buf = sync_no % 3u, obuf = (sync_no + 2u) % 3u;
+    const unsigned buf = sync_no & 3u, obuf = (sync_no + 3u) & 3u;
     double acc = 0.0;
     if (valid) {
       double eS = rtop ? et : E[utop], vS = rtop ? vt : VB[iu];
@@ -334,8 +337,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
     }
     acc = wave_total63(acc);
     if (lane == 63) red[wid] = acc;
-    if (G > 1) stores_done();   // the words emptied after the last sync
-    __syncthreads();            // every neighbour value has been read
+    __syncthreads();  // every neighbour value has been read
     share(pv);
     if (G > 1) {
       unsigned long long* rx = ring + (size_t(buf) * G + rank) * 4 * nx + col;
@@ -378,18 +380,6 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
         if (rank == 0) br[j] = b;
       }
     }
-    // the vector, for the basis and the next launch
-    if (valid) {
-      double* ov = place(j + 1);
-#pragma unroll
-      for (int i = 0; i < RT; ++i)
-        if (i < RT - 1 || full) {
-          const unsigned q = gofs(fresh(i));
-          __builtin_nontemporal_store(pv[0][i], ov + q);
-          __builtin_nontemporal_store(pv[1][i], ov + n + q);
-          __builtin_nontemporal_store(pv[2][i], ov + 2 * n + q);
-        }
-    }
     if (G > 1) {
       const unsigned long long* rup = ring + (size_t(buf) * G + up_rank) * 4 * nx + 2 * nx + col;
       const unsigned long long* rdn = ring + (size_t(buf) * G + dn_rank) * 4 * nx + col;
@@ -416,6 +406,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
         eb = __longlong_as_double((long long)a);
         vb = __longlong_as_double((long long)ald(rdn + nx));
       }
+      stores_done();  // the words emptied after the sync before (long done)
     }
     __syncthreads();
     ++sync_no;
@@ -434,6 +425,20 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
         mst(rx + 3 * nx, kNoWord, local);
       }
       bad = uni(sh[5]) != 0;
+    }
+    // the vector, for the basis and the next launch: written here, a whole
+    // step before the next loads that a wavefront waits for (loads complete
+    // after the stores issued before them)
+    if (valid) {
+      double* ov = place(j + 1);
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+        if (i < RT - 1 || full) {
+          const unsigned q = gofs(fresh(i));
+          __builtin_nontemporal_store(pv[0][i], ov + q);
+          __builtin_nontemporal_store(pv[1][i], ov + n + q);
+          __builtin_nontemporal_store(pv[2][i], ov + 2 * n + q);
+        }
     }
   };
   for (int k = 0; k < c.steps && !bad; k += 2) {
@@ -461,8 +466,8 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       }
     }
     __syncthreads();
-    if (tid < 3) ast(rec + (size_t(tid) * G + rank) * c.rec_stride, kNoWord);
-    for (int k = tid; k < 12 * nx; k += nt) ast(ring + (size_t(k / (4 * nx)) * G + rank) * 4 * nx + k % (4 * nx), kNoWord);
+    if (tid < 4) ast(rec + (size_t(tid) * G + rank) * c.rec_stride, kNoWord);
+    for (int k = tid; k < 16 * nx; k += nt) ast(ring + (size_t(k / (4 * nx)) * G + rank) * 4 * nx + k % (4 * nx), kNoWord);
   }
 }
 
@@ -649,10 +654,11 @@ LzChipFn lz_chip_fn(int rt) {
 
 // Launch shape of k_lz_chip; false where no shape fits or k_lz_step is the
 // faster.  Estimates in us, from steps timed on MI355X: a thread's row takes
-// about 40 VALU instructions, a step 250 more; the exchange about 1.6 us on
-// one XCD and 2.3 us + 12 ns a block across; the vector's write is bound by
-// about 0.4 TB/s per XCD.  k_lz_step and k_lz_norm: 10 us + 80 bytes a point
-// at 5 TB/s.
+// about 40 VALU instructions, a step 250 more; the exchange beyond them about
+// 1.2 us + 2 ns a column on one XCD and 1.3 us + 9 ns a column + 4 ns a block across (64^2:
+// 2.4 us a step in all, 256^2: 4.2, 512^2: 7.5, much the same for 64 to 128
+// blocks); the vector's write is bound by about 0.55 TB/s per XCD.  k_lz_step
+// and k_lz_norm: 10 us + 80 bytes a point at 5 TB/s (14 us at 512^2).
 bool lz_chip_config(int nx, int ny, int nrhs, bool depth, int cus, LzChip* c) {
   double best = 10.0 + 80.0 * nx * double(ny) * nrhs / 5e6;
   bool found = false;
@@ -680,9 +686,13 @@ bool lz_chip_config(int nx, int ny, int nrhs, bool depth, int cus, LzChip* c) {
         if (loc && (G == 1 || fit < 1)) continue;
         if (!loc && cus * occ < G) continue;
         const double turns = loc ? std::ceil(double(gpx) / fit) : std::ceil(double(nrhs) / (cus * occ / G));
-        const double valu = ((nt / 64 + 3) / 4) * 4.0 * (rt * 40.0 + 250.0) / 2370.0;
-        const double wr = 24.0 * nx * double(ny) / 0.4e6 * (loc ? std::min(fit, gpx) : std::max(1.0, double(nrhs) / turns) / std::min(8.0, double(G)));
-        const double t = turns * std::max(valu + (G == 1 ? 0.7 : loc ? 1.6 : 2.3 + 0.012 * G), wr);
+        const int per_cu = loc ? (G * std::min(fit, gpx) + cus / 8 - 1) / (cus / 8)
+                               : (G * std::min(nrhs, cus * occ / G) + cus - 1) / cus;   // blocks that share a CU
+        const double valu = per_cu * ((nt / 64 + 3) / 4) * 4.0 * (rt * 40.0 + 250.0) / 2370.0;
+        const double wr = 24.0 * nx * double(ny) / 0.55e6 * (loc ? std::min(fit, gpx) : std::max(1.0, double(nrhs) / turns) / std::min(8.0, double(G)));
+        // (one wavefront a SIMD waits out its own latencies: 1.5 times as long)
+        const double own = (nt * per_cu <= 256 ? 1.5 : 1.0) * valu + (G == 1 ? 0.9 : loc ? 1.2 + 0.002 * nx : 1.3 + 0.009 * nx + 0.004 * G);
+        const double t = turns * (std::max(own, wr) + 0.2 * std::min(own, wr));
         if (t < best) {
           best = t;
           found = true;
@@ -705,13 +715,13 @@ bool lz_chip_config(int nx, int ny, int nrhs, bool depth, int cus, LzChip* c) {
   return found;
 }
 size_t lz_chip_bytes(const LzChip& c) {
-  const size_t rec = size_t(c.groups) * 3 * c.G * c.rec_stride * 8, ring = size_t(c.groups) * 12 * c.G * c.nx * 8;
+  const size_t rec = size_t(c.groups) * 4 * c.G * c.rec_stride * 8, ring = size_t(c.groups) * 16 * c.G * c.nx * 8;
   return (c.G > 1 ? ring + rec : 0) + size_t(c.ctl_words) * 4 + 1024;
 }
 // Lays the mailboxes out in mem (256-byte aligned) and empties them.
 void lz_chip_mailboxes(LzChip& c, void* mem, hipStream_t s) {
-  const size_t rec = (size_t(c.groups) * 3 * c.G * c.rec_stride * 8 + 255) / 256 * 256;
-  const size_t ring = size_t(c.groups) * 12 * c.G * c.nx * 8;
+  const size_t rec = (size_t(c.groups) * 4 * c.G * c.rec_stride * 8 + 255) / 256 * 256;
+  const size_t ring = size_t(c.groups) * 16 * c.G * c.nx * 8;
   char* p = static_cast<char*>(mem);
   c.ctl = reinterpret_cast<int*>(p);
   p += (size_t(c.ctl_words) * 4 + 255) / 256 * 256;

@@ -81,3 +81,24 @@ def test_zero_state_and_cap(rx):
     with pytest.raises(rx.RexiiError) as e:
         rx.apply_multishift(f[1].clone(), t, fc=10.0, max_iter=20)
     assert e.value.status == -3
+
+
+@pytest.mark.parametrize("nx,ny,nrhs,depth", [(4, 4, 1, False), (7, 5, 3, True), (512, 6, 1, True), (511, 33, 2, False),
+                                              (65, 63, 9, True), (128, 128, 1, False), (200, 300, 17, False),
+                                              (513, 40, 1, True), (512, 512, 1, True)])
+def test_steps_on_the_chip_match_launched_steps(rx, nx, ny, nrhs, depth):
+    """One block a state, one XCD a state, blocks across XCDs, more states than
+    fit at once, a row past the widest block: against the least workspace,
+    whose steps are one launch each.  Both are the same recurrence in FP64."""
+    fc = 10.0
+    H = torch.from_numpy(inputs.variable_depth(nx, ny)).cuda() if depth else None
+    f = torch.stack([torch.from_numpy(inputs.gaussian_bumps(nx, ny, nbumps=2, seed=80 + r, velocity=True))
+                     for r in range(nrhs)]).cuda()
+    t = 30.0 / rx.rho(nx, ny, fc=fc, Hfield=H)
+    lo, hi = _sizes(rx, nx, ny, nrhs, t, fc, H)
+    a, ra = _call(rx, f, t, fc, H, lo)
+    b, rb = _call(rx, f, t, fc, H, hi)
+    assert ra["solves"] == rb["solves"]
+    assert float((a - b).norm() / a.norm()) <= 1e-12
+    c, _ = _call(rx, f, t, fc, H, hi)
+    assert bool((b == c).all())
