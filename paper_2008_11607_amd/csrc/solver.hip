@@ -1736,6 +1736,68 @@ static void run_pc(Job& jb, Arena& ar) {
   en->solve_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
 }
 
+// A batch of unlike grids whose slots each fit on the chip: one engine per
+// grid in turn, in the same memory, instead of one engine that streams every
+// slot through HBM (a launch of the chip kernel has one shape).  The engines'
+// statistics are merged into jb.en.  False: nothing was done.
+static bool run_by_grid(Job& jb, Arena& ar, size_t mark, const EngineSize& z) {
+  if (z.method != 0) return false;
+  std::vector<std::vector<int>> groups;   // problem indices by grid, in order of first use
+  std::map<std::pair<int, int>, size_t> index;
+  for (size_t i = 0; i < jb.ptrs.size(); ++i) {
+    const Plan& pl = jb.ptrs[i]->pl;
+    auto it = index.emplace(std::make_pair(pl.nx, pl.ny), groups.size());
+    if (it.second) groups.emplace_back();
+    groups[it.first->second].push_back(int(i));
+  }
+  if (groups.size() < 2) return false;
+  int dev = 0, cus = 0;
+  HIPCHK(hipGetDevice(&dev));
+  HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const bool mixed = jb.o.precision == REXII_PREC_MIXED;
+  for (const auto& g : groups) {
+    Chip c;
+    if (!chip_config(jb.ptrs[g[0]]->pl.nx, jb.ptrs[g[0]]->pl.ny, mixed ? 1 : 0, cus, z.B, &c)) return false;
+  }
+  std::unique_ptr<Engine> all(new Engine(jb.st));
+  all->z = z;
+  all->z.B = 0;
+  all->precision = jb.o.precision;
+  for (Problem* p : jb.ptrs) all->plans.push_back(&p->pl);
+  for (const auto& g : groups) {
+    Job sub;
+    sub.st = jb.st;
+    sub.o = jb.o;
+    for (int i : g) sub.ptrs.push_back(jb.ptrs[i]);
+    ar.reset(mark);
+    EngineSize zs = engine_size(sub.ptrs, jb.o.pole_batch, jb.o.precision, jb.o.tile_rows);
+    while (zs.B > 1 && engine_bytes(zs) > ar.remaining()) zs.B = std::max(1, (zs.B * 3) / 4);
+    sub.en = new Engine(jb.st);
+    Engine& en = *sub.en;
+    en.setup(ar, sub.ptrs, zs, jb.o.precision, jb.o.max_iter, mixed ? jb.o.inner_tol : 0.0, jb.o.profile != 0, nullptr,
+             zs.cap);
+    if (mixed) {
+      en.run<float>();
+      rerun_fp64(sub, ar, mark, nullptr);
+    } else {
+      en.run<double>();
+    }
+    for (size_t j = 0; j < en.stats.size(); ++j) {
+      all->stats.push_back(en.stats[j]);
+      all->solve_inst.push_back(g[en.solve_inst[j]]);
+      all->solve_index.push_back(en.solve_index[j]);
+      all->retried.push_back(j < en.retried.size() ? en.retried[j] : 0);
+    }
+    all->z.B = std::max(all->z.B, zs.B);
+    all->pass_bytes += en.pass_bytes;
+    all->kernel_ms += en.kernel_ms;
+    all->launches += en.launches;
+    all->solve_seconds += en.solve_seconds;
+  }
+  jb.en = all.release();
+  return true;
+}
+
 // Prepares every problem (input checks, div/curl, plans) and runs the engine
 // (only max_chunks chunks if > 0; returns their time in ms).
 static double run_job(Job& jb, Arena& ar, int max_chunks = 0) {
@@ -1848,6 +1910,7 @@ static double run_job(Job& jb, Arena& ar, int max_chunks = 0) {
   const EngineSize z = engine_size(jb.ptrs, jb.o.pole_batch, jb.o.precision, jb.o.tile_rows);
   double2* yout = jb.keep ? ar.take<double2>(size_t(z.S) * z.cap) : nullptr;
   const size_t mark = ar.mark();   // the engine's memory starts here
+  if (max_chunks == 0 && !jb.keep && run_by_grid(jb, ar, mark, z)) return 0.0;
   jb.en = new Engine(jb.st);
   jb.en->setup(ar, jb.ptrs, z, jb.o.precision, jb.o.max_iter,
                (jb.o.precision == REXII_PREC_MIXED) ? jb.o.inner_tol : 0.0,
