@@ -92,6 +92,26 @@ __device__ __forceinline__ V sel(bool c, V a, V b) {
   return v;
 }
 
+__device__ __forceinline__ float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma1(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// c + a b + d e and c + a b - d e
+template <typename T>
+__device__ __forceinline__ T fma2(T a, T b, T d, T e, T c) {
+  return fma1(d, e, fma1(a, b, c));
+}
+template <typename T>
+__device__ __forceinline__ T fms(T a, T b, T d, T e, T c) {
+  return fma1(-d, e, fma1(a, b, c));
+}
+// c + a b, complex
+template <typename V>
+__device__ __forceinline__ V cfma(V a, V b, V c) {
+  V r;
+  r.x = fma1(-a.y, b.y, fma1(a.x, b.x, c.x));
+  r.y = fma1(a.y, b.x, fma1(a.x, b.y, c.y));
+  return r;
+}
+
 __device__ __forceinline__ double quad_sum(double v) {
   v += dpp_f64<0xb1, 0xf>(v);
   v += dpp_f64<0x4e, 0xf>(v);

@@ -19,11 +19,16 @@
 //   sums of all G blocks; alpha, beta, stop test (every block by itself)
 // so a step waits once for the other blocks.
 //
-// Bound: VALU issue (about 50 instructions a point and step) plus one exchange
-// between the blocks a step.  Measured whole calls, passes -> chip: 64^2
-// t rho 100 FP64 7.3 -> 1.8 ms, 130 x 66 with velocities t rho 150 56.7 ->
-// 15.9 ms, 256^2 t rho 300 FP64 296 -> 100 ms, 512^2 t rho 250 mixed 543 ->
-// 235 ms (the passes run at 5.5 TB/s of HBM there).
+// Bound: VALU issue (42 instructions a point and step, and about 250 a
+// wavefront) plus one exchange between the blocks a step: 4.4 us a step for
+// 256^2 in FP64 (16 blocks), 5.7 us for 512^2 in FP32 (32 blocks), of which
+// about 2.0 and 3.0 us are VALU.  Measured whole calls, passes -> chip: 64^2
+// t rho 100 FP64 7.3 -> 1.4 ms, 130 x 66 with velocities t rho 150 56.7 ->
+// 13.5 ms, 256^2 t rho 300 FP64 225 to 296 -> 70 ms, 512^2 t rho 250 mixed
+// 504 to 543 -> 175 ms (the passes run at 5.5 TB/s of HBM there).  Tried and
+// left out: two blocks of 256 threads a CU (10 to 25% slower), four
+// wavefronts a SIMD at 128 registers (spills), the edge rows' state in LDS
+// (3 to 6% slower), sleeps in the waits and raised wave priority (no change).
 //
 // Communication between the blocks of a group: agent-scope stores and loads.
 // A mailbox word (a sum of a block's record, or part of an edge value) holds
@@ -221,7 +226,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
     double2 al64 = sw.c64(SLOT_OFF(alpha)), be64 = sw.c64(SLOT_OFF(beta)), rr64 = make_double2(0.0, 0.0);
     al64.x *= cx64;
     al64.y *= cx64;
-    const V zeta = mk<V>(zeta64.x * icx, zeta64.y * icx);
+    const V nzeta = mk<V>(-zeta64.x * icx, -zeta64.y * icx);
     const T ry = T(sw.f64(SLOT_OFF(cy)) * icx);
     const size_t sb = size_t(slot) * e.cap;
     V* gr = reinterpret_cast<V*>(par ? e.r1 : e.r0) + sb;
@@ -275,8 +280,10 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
         if (!valid[j]) continue;
-        const V hb = rbot[j] ? pb[j] : P[bot[j]];
-        V up = rtop[j] ? pt[j] : P[top[j]];
+        // (the LDS reads are in bounds for every item: a select, no branch)
+        const V lt = P[top[j]], lb = P[bot[j]];
+        V up = sel(rtop[j], pt[j], lt);
+        const V hb = sel(rbot[j], pb[j], lb);
         V cur = P[base[j]];
         V we[2][kRows], ea[2][kRows], so[2][kRows];
         auto fetch = [&](int g) {
@@ -301,22 +308,25 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
             const V w = we[g & 1][u], x = ea[g & 1][u];
             const V nxt = (i == RT - 1) ? hb : (i == RT - 2 ? sel(full[j], so[g & 1][u], hb) : so[g & 1][u]);
             V v;
-            v.x = (x.x + w.x - T(2) * cur.x) + ry * (nxt.x + up.x - T(2) * cur.x) - zeta.x * cur.x + zeta.y * cur.y;
-            v.y = (x.y + w.y - T(2) * cur.y) + ry * (nxt.y + up.y - T(2) * cur.y) - zeta.x * cur.y - zeta.y * cur.x;
+            v.x = fma1(ry, fma1(T(-2), cur.x, nxt.x + up.x), fma1(T(-2), cur.x, x.x + w.x));
+            v.y = fma1(ry, fma1(T(-2), cur.y, nxt.y + up.y), fma1(T(-2), cur.y, x.y + w.y));
+            v = cfma(nzeta, cur, v);
             if (i == RT - 1) {
               v = sel(full[j], v, zero2<V>());
               cur = sel(full[j], cur, zero2<V>());
             }
             const V rv = r[j][i];
-            a[0] += cur.x * v.x - cur.y * v.y;
-            a[1] += cur.x * v.y + cur.y * v.x;
-            a[2] += v.x * rv.x - v.y * rv.y;
-            a[3] += v.x * rv.y + v.y * rv.x;
-            a[4] += v.x * v.x - v.y * v.y;
-            a[5] += v.x * v.y;
-            a[6] += rv.x * rv.x - rv.y * rv.y;
-            a[7] += rv.x * rv.y;
-            a[8] += rv.x * rv.x + rv.y * rv.y;
+            // (fused by hand: left to the compiler each of these costs a
+            // product and a sum more)
+            a[0] = fms(cur.x, v.x, cur.y, v.y, a[0]);
+            a[1] = fma2(cur.x, v.y, cur.y, v.x, a[1]);
+            a[2] = fms(v.x, rv.x, v.y, rv.y, a[2]);
+            a[3] = fma2(v.x, rv.y, v.y, rv.x, a[3]);
+            a[4] = fms(v.x, v.x, v.y, v.y, a[4]);
+            a[5] = fma1(v.x, v.y, a[5]);
+            a[6] = fms(rv.x, rv.x, rv.y, rv.y, a[6]);
+            a[7] = fma1(rv.x, rv.y, a[7]);
+            a[8] = fma2(rv.x, rv.x, rv.y, rv.y, a[8]);
             // formed here, not sunk to a later use (with the operands of
             // every row kept until then)
             pin(v.x);
@@ -468,7 +478,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       ++steps;
       // ---- the next step's vectors
       const double2 au = uni(ctl.al), bu = uni(ctl.be);
-      const V al = mk<V>(au.x, au.y), be = mk<V>(bu.x, bu.y);
+      const V nal = mk<V>(-au.x, -au.y), be = mk<V>(bu.x, bu.y);
       const V ad = mk<V>(au.x * icx, au.y * icx);
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
@@ -478,21 +488,21 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
           if (i % kRows == 0) asm volatile("" ::: "memory");
           if (i < RT - 1 || full[j]) {
             const V pc = P[base[j] + i];
-            d[j][i] = cadd(d[j][i], cmul(ad, pc));
-            r[j][i] = csub(r[j][i], cmul(al, q[j][i]));
+            d[j][i] = cfma(ad, pc, d[j][i]);
+            r[j][i] = cfma(nal, q[j][i], r[j][i]);
             pin(d[j][i].x);
             pin(d[j][i].y);
-            P[base[j] + i] = cadd(r[j][i], cmul(be, pc));
+            P[base[j] + i] = cfma(be, pc, r[j][i]);
           }
         }
       }
       if (ringed) {
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
-          rt[j] = csub(rt[j], cmul(al, qt[j]));
-          pt[j] = cadd(rt[j], cmul(be, pt[j]));
-          rb[j] = csub(rb[j], cmul(al, qb[j]));
-          pb[j] = cadd(rb[j], cmul(be, pb[j]));
+          rt[j] = cfma(nal, qt[j], rt[j]);
+          pt[j] = cfma(be, pt[j], rt[j]);
+          rb[j] = cfma(nal, qb[j], rb[j]);
+          pb[j] = cfma(be, pb[j], rb[j]);
         }
       }
       __syncthreads();
@@ -520,13 +530,13 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       }
     }
     if (rank == 0 && tid == 0) {
-      Slot* W = &e.slots[slot];
-      W->it_inner = it0 + steps;
-      W->it_total = itt0 + steps;
-      W->alpha = make_double2(al64.x * icx, al64.y * icx);
-      W->beta = be64;
-      if (steps > 0) W->rr = rr64;
-      if (act == 1) W->status = kInnerDone;
+      Slot* Z = &e.slots[slot];
+      Z->it_inner = it0 + steps;
+      Z->it_total = itt0 + steps;
+      Z->alpha = make_double2(al64.x * icx, al64.y * icx);
+      Z->beta = be64;
+      if (steps > 0) Z->rr = rr64;
+      if (act == 1) Z->status = kInnerDone;
     }
     __syncthreads();
   }
