@@ -29,6 +29,21 @@ void launch_mode_coef(double2* coef, double2* part, int cnx, int cny, int sym, c
                       double t, double g, double H, double fc, double scale, const double* tab, int nterm, int nw,
                       int ns, hipStream_t s);
 bool mode_sum_in_apply(int entries, int ns);
+// Pole sums with the far terms of each box of theta as one polynomial
+// (kernels_fft.hip).  nbox = 0: the direct sums are the better way.
+constexpr int kCheb = 32;  // Chebyshev points per box: half a wave
+struct FarBoxes {
+  double w, inv_w, tg;  // uniform boxes: width, first edge
+  double d, inv_h;      // poles at theta = +-h j +- i d
+  int k, nbox;          // graded boxes 0..k, boxes in all
+};
+// For theta in [0, thmax], terms j with poles z = -d + i h j.
+FarBoxes far_boxes(double thmax, double h, double d, int entries, int nterm);
+void far_shape(int nbox, int nterm, int* nw, int* ns);  // waves per block, term splits
+size_t far_doubles2(const FarBoxes& fb, int nterm);  // double2 of scratch
+void launch_mode_boxed(double2* coef, double2* far, const FarBoxes& fb, int cnx, int cny, int sym, const double* sxt,
+                       const double* syt, double t, double g, double H, double fc, double scale, const double* tab,
+                       int nterm, hipStream_t s);
 // F [3][ny][nx/2+1] <- a0 F + C1 t A F + C2 (t A)^2 F with (C1, C2) from
 // coef (ns <= 1: scaled entries; ns > 1: ns x ne unscaled split sums, added
 // in order and multiplied by scale).

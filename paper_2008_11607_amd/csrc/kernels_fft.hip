@@ -76,57 +76,77 @@ double axis_symbol(int k, int n, int deriv) {
   return 2.0 * M_PI * double(ks);
 }
 
-// Re c1 and Re c2 at theta^2 = th2 over the terms [w per, (w + 1) per) of
-// the table (per = ceil(nterm / nw)); the table index is wave-uniform, so
-// the entries arrive through scalar loads.
-__device__ __forceinline__ void term_sums(const double* __restrict__ tab, int nterm, int w, int nw, double th2,
-                                          double& c1, double& c2) {
-  const int per = (nterm + nw - 1) / nw;
-  const int lo = min(nterm, w * per), hi = min(nterm, lo + per);
-  // (A s + B) / d is accumulated as (s/d) A + (1/d) B: one scalar (table)
-  // operand per FMA, and four independent chains.  Four terms share one
-  // reciprocal: 1/d1 = (d2 d3 d4) / (d1 d2 d3 d4).  d >= b^2 = (2 h^2 mu n)^2
-  // for n >= 1 and d >= a^2 = (h mu)^4 for n = 0, and d < 4 (theta^2 + (h N)^2)^2,
-  // so the product stays in range for any h above 1e-3 and theta below 1e18.
+// The four running sums of a range of terms: (A s + B) / d is accumulated as
+// (s/d) A + (1/d) B, one table operand per FMA and four independent chains.
+struct TermAcc {
   double c1a = 0.0, c1b = 0.0, c2a = 0.0, c2b = 0.0;
-  auto one = [&](const double* q, double i1) {
-    const double e1 = i1 * (q[0] + th2);
+  __device__ __forceinline__ void one(const double* q, double s, double i1) {
+    const double e1 = i1 * s;
     c1a = fma(e1, q[2], c1a);
     c1b = fma(i1, q[3], c1b);
     c2a = fma(e1, q[4], c2a);
     c2b = fma(i1, q[5], c2b);
+  }
+};
+
+// Adds the terms [lo, hi) at theta^2 = th2 + lo2 (lo2: rounding of th2 where
+// it is known, else 0), but those in the lane's [nl, nh).  The range is
+// wave-uniform, so the entries arrive through scalar loads.
+template <bool LOW, bool SKIP = false>
+__device__ __forceinline__ void term_range(const double* __restrict__ tab, int lo, int hi, double th2, double lo2,
+                                           TermAcc& c, int nl = 0, int nh = 0) {
+  // Four terms share one reciprocal: 1/d1 = (d2 d3 d4) / (d1 d2 d3 d4).
+  // d >= b^2 = (2 h^2 mu n)^2 for n >= 1 and d >= a^2 = (h mu)^4 for n = 0, and
+  // d < 4 (theta^2 + (h N)^2)^2, so the product stays in range for any h above
+  // 1e-3 and theta below 1e18.
+  auto sum = [&](const double* q) { return LOW ? (q[0] + th2) + lo2 : q[0] + th2; };
+  auto add = [&](const double* q, int j, double s, double i1) {
+    c.one(q, s, SKIP && j >= nl && j < nh ? 0.0 : i1);
   };
-  auto den = [&](const double* q) { return sq_plus(q[0] + th2, q[1]); };
-  auto pair = [&](const double* q) {
-    const double d1 = den(q), d2 = den(q + kTermDoubles);
+  auto pair = [&](const double* q, int j) {
+    const double s1 = sum(q), s2 = sum(q + kTermDoubles);
+    const double d1 = sq_plus(s1, q[1]), d2 = sq_plus(s2, q[kTermDoubles + 1]);
     const double r = recip(d1 * d2);
-    one(q, r * d2);
-    one(q + kTermDoubles, r * d1);
+    add(q, j, s1, r * d2);
+    add(q + kTermDoubles, j + 1, s2, r * d1);
   };
-  auto quad = [&](const double* q) {
-    const double d1 = den(q), d2 = den(q + kTermDoubles);
-    const double d3 = den(q + 2 * kTermDoubles), d4 = den(q + 3 * kTermDoubles);
+  auto quad = [&](const double* q, int j) {
+    const double s1 = sum(q), s2 = sum(q + kTermDoubles);
+    const double s3 = sum(q + 2 * kTermDoubles), s4 = sum(q + 3 * kTermDoubles);
+    const double d1 = sq_plus(s1, q[1]), d2 = sq_plus(s2, q[kTermDoubles + 1]);
+    const double d3 = sq_plus(s3, q[2 * kTermDoubles + 1]), d4 = sq_plus(s4, q[3 * kTermDoubles + 1]);
     const double p12 = d1 * d2, p34 = d3 * d4;
     const double r = recip(p12 * p34);
     const double r12 = r * p34, r34 = r * p12;
-    one(q, r12 * d2);
-    one(q + kTermDoubles, r12 * d1);
-    one(q + 2 * kTermDoubles, r34 * d4);
-    one(q + 3 * kTermDoubles, r34 * d3);
+    add(q, j, s1, r12 * d2);
+    add(q + kTermDoubles, j + 1, s2, r12 * d1);
+    add(q + 2 * kTermDoubles, j + 2, s3, r34 * d4);
+    add(q + 3 * kTermDoubles, j + 3, s4, r34 * d3);
   };
   int j = lo;
   for (; j + 7 < hi; j += 8) {  // unrolled by hand: the loads of two quads issue together
     const double* q = tab + size_t(j) * kTermDoubles;
-    quad(q);
-    quad(q + 4 * kTermDoubles);
+    quad(q, j);
+    quad(q + 4 * kTermDoubles, j + 4);
   }
-  for (; j + 1 < hi; j += 2) pair(tab + size_t(j) * kTermDoubles);
+  for (; j + 1 < hi; j += 2) pair(tab + size_t(j) * kTermDoubles, j);
   if (j < hi) {
     const double* q = tab + size_t(j) * kTermDoubles;
-    one(q, recip(den(q)));
+    const double s1 = sum(q);
+    add(q, j, s1, recip(sq_plus(s1, q[1])));
   }
-  c1 = c1a + c1b;
-  c2 = c2a + c2b;
+}
+
+// Re c1 and Re c2 at theta^2 = th2 over the terms [w per, (w + 1) per) of
+// the table (per = ceil(nterm / nw)).
+__device__ __forceinline__ void term_sums(const double* __restrict__ tab, int nterm, int w, int nw, double th2,
+                                          double& c1, double& c2) {
+  const int per = (nterm + nw - 1) / nw;
+  const int lo = min(nterm, w * per), hi = min(nterm, lo + per);
+  TermAcc c;
+  term_range<false>(tab, lo, hi, th2, 0.0, c);
+  c1 = c.c1a + c.c1b;
+  c2 = c.c2a + c.c2b;
 }
 
 // Canonical wavenumber of k on an axis of n points: the smallest index
@@ -233,6 +253,215 @@ __global__ __launch_bounds__(256) void k_mode_coef_sum(double2* __restrict__ coe
   coef[e] = make_double2(scale * c1, scale * c2);
 }
 
+// ---------------------------------------------------------------------------
+// Pole sums by near and far terms.
+//
+// As functions of s = theta^2 the terms are analytic but for poles at
+// s = -z^2 = (y^2 - d^2) +- 2 i d y, y = h j, d = h |mu|.  theta in [0, theta_max]
+// is cut into boxes; for the s of one box the terms whose poles lie outside
+// the ellipse with foci at the box's ends and semi-axes (kFarA, kFarB) half
+// widths (sum rho = 3.2) are summed as one polynomial: their sum is formed at
+// kCheb Chebyshev points of the box and interpolated (each term's error is
+// rho^-kCheb = 7e-17 of the term).  The few terms inside (y within about
+// 1.76 half widths of the box's centre in theta) are added directly.  So
+// nbox kCheb theta values meet the whole table instead of every distinct one,
+// and each of those meets (near terms + a polynomial).
+//
+// Box edges in theta: 0, 4, 8, 16, .. up to tg = 4 2^k >= w, then steps of w:
+// c1 ~ 1/theta and c2 ~ 1/theta^2 vary by no more than 4 within a box beyond
+// the first, so the interpolation's error is relative to the values there.
+// The polynomial's variable is s, not theta: theta^2 - s_c is exact to the
+// rounding of theta^2, a rounded theta (5e-13 at 5000) is used only to pick
+// the box.
+// ---------------------------------------------------------------------------
+constexpr double kFarA = 1.75625, kFarB = 1.44375;  // (rho +- 1/rho) / 2, rho = 3.2
+
+__device__ __forceinline__ int far_box(const FarBoxes& fb, double th) {
+  int b;
+  if (th < fb.tg) {
+    b = th < 4.0 ? 0 : ilogb(th) - 1;
+  } else {
+    b = fb.k + 1 + int((th - fb.tg) * fb.inv_w);
+  }
+  return min(max(b, 0), fb.nbox - 1);
+}
+
+// Centre and half width of box b in s.
+__device__ __forceinline__ void far_span(const FarBoxes& fb, int b, double& sc, double& sd) {
+  const double lo = b == 0 ? 0.0 : b <= fb.k ? ldexp(4.0, b - 1) : fb.tg + (b - fb.k - 1) * fb.w;
+  const double hi = b <= fb.k ? ldexp(4.0, b) : lo + fb.w;
+  sc = 0.5 * fma(lo, lo, hi * hi);
+  sd = 0.5 * (hi - lo) * (hi + lo);
+}
+
+// The near terms [lo, hi) of a box: with v = y^2 the pole is inside the
+// ellipse where (v - p)^2 / al^2 + 4 d^2 v / be^2 < 1, p = d^2 + sc; one
+// term more on either side covers the rounding of the roots.
+__device__ __forceinline__ void far_window(const FarBoxes& fb, double sc, double sd, int nterm, int& lo, int& hi) {
+  const double al = kFarA * sd, p = fma(fb.d, fb.d, sc);
+  const double q = p - 2.0 * fb.d * fb.d * ((kFarA / kFarB) * (kFarA / kFarB));
+  const double disc = fma(q, q, fma(-p, p, al * al));
+  lo = hi = 0;
+  if (!(disc > 0.0)) return;
+  const double r = sqrt(disc), vh = q + r, vl = q - r;
+  if (!(vh > 0.0)) {
+    // every y > 0 is far; n = 0 has its pole at v = 0
+    hi = p * p < al * al ? 1 : 0;
+    return;
+  }
+  lo = vl > 0.0 ? min(nterm, max(0, int(sqrt(vl) * fb.inv_h) - 1)) : 0;
+  hi = int(min(double(nterm), sqrt(vh) * fb.inv_h + 2.0));
+}
+
+// Far sums at the Chebyshev points.  Lanes 0..31 and 32..63 of every wave
+// hold the points of two neighbouring boxes; the term slices are split over
+// the block's waves and the grid's rows as in k_mode_coef.  node[s][b][i].
+__global__ __launch_bounds__(64 * kModeWaves) void k_mode_far(double2* __restrict__ node, FarBoxes fb,
+                                                              const double* __restrict__ tab, int nterm) {
+  extern __shared__ double red[];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int nw = int(blockDim.x >> 6);
+  const int slices = int(gridDim.y) * nw, sl = int(blockIdx.y) * nw + w;
+  const int per = (nterm + slices - 1) / slices;
+  const int lo = min(nterm, sl * per), hi = min(nterm, lo + per);
+  const int b = int(blockIdx.x) * 2 + (lane >> 5), i = lane & 31;
+  const int bb = min(b, fb.nbox - 1);
+  double sc, sd;
+  far_span(fb, bb, sc, sd);
+  int nl, nh;
+  far_window(fb, sc, sd, nterm, nl, nh);
+  const double x = cospi((2 * i + 1) * (0.5 / kCheb));
+  const double th2 = fma(sd, x, sc), lo2 = fma(sd, x, sc - th2);  // the point and its rounding
+  // the range that is near for either box
+  const int l0 = __builtin_amdgcn_readlane(nl, 0), l1 = __builtin_amdgcn_readlane(nl, 32);
+  const int h0 = __builtin_amdgcn_readlane(nh, 0), h1 = __builtin_amdgcn_readlane(nh, 32);
+  const int ul = l0 < h0 ? (l1 < h1 ? min(l0, l1) : l0) : l1;
+  const int uh = l0 < h0 ? (l1 < h1 ? max(h0, h1) : h0) : max(l1, h1);
+  TermAcc c;
+  term_range<true>(tab, lo, min(hi, ul), th2, lo2, c);
+  term_range<true, true>(tab, max(lo, ul), min(hi, uh), th2, lo2, c, nl, nh);
+  term_range<true>(tab, max(lo, uh), hi, th2, lo2, c);
+  double c1 = c.c1a + c.c1b, c2 = c.c2a + c.c2b;
+  if (nw > 1) {
+    if (w > 0) {
+      red[(w - 1) * 128 + lane] = c1;
+      red[(w - 1) * 128 + 64 + lane] = c2;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    for (int v = 1; v < nw; ++v) {
+      c1 += red[(v - 1) * 128 + lane];
+      c2 += red[(v - 1) * 128 + 64 + lane];
+    }
+  }
+  if (b < fb.nbox) node[(size_t(blockIdx.y) * fb.nbox + b) * kCheb + i] = make_double2(c1, c2);
+}
+
+// Chebyshev coefficients of one box per block from its node sums (splits
+// added in order): c_k = (2 - [k = 0]) / kCheb sum_i f_i cos(pi k (2i+1) / (2 kCheb)).
+__global__ __launch_bounds__(4 * kCheb) void k_mode_cheb(double2* __restrict__ cheb, const double2* __restrict__ node,
+                                                         int nbox, int ns) {
+  __shared__ double ct[4 * kCheb];
+  __shared__ double2 part[4 * kCheb];
+  const int b = int(blockIdx.x), i = threadIdx.x & (kCheb - 1), g = threadIdx.x / kCheb;
+  ct[threadIdx.x] = cospi(double(threadIdx.x) * (0.5 / kCheb));
+  double2 f = make_double2(0.0, 0.0);
+  for (int s = g; s < ns; s += 4) {
+    const double2 v = node[(size_t(s) * nbox + b) * kCheb + i];
+    f.x += v.x;
+    f.y += v.y;
+  }
+  part[threadIdx.x] = f;
+  __syncthreads();
+  if (g == 0) {
+    for (int q = 1; q < 4; ++q) {
+      f.x += part[q * kCheb + i].x;
+      f.y += part[q * kCheb + i].y;
+    }
+    part[i] = f;
+  }
+  __syncthreads();
+  if (g > 0) return;
+  double2 c = make_double2(0.0, 0.0);
+  for (int m = 0; m < kCheb; ++m) {
+    const double t = ct[(i * (2 * m + 1)) & (4 * kCheb - 1)];
+    c.x = fma(part[m].x, t, c.x);
+    c.y = fma(part[m].y, t, c.y);
+  }
+  const double sc = (i == 0 ? 1.0 : 2.0) / kCheb;
+  cheb[size_t(b) * kCheb + i] = make_double2(sc * c.x, sc * c.y);
+}
+
+// coef[e] = scale (far polynomial + near terms) at the entry's theta.
+__global__ __launch_bounds__(64) void k_mode_near(double2* __restrict__ coef, const double2* __restrict__ cheb,
+                                                  FarBoxes fb, int cnx, int cny, int sym,
+                                                  const double* __restrict__ sxt, const double* __restrict__ syt,
+                                                  double t, double g, double H, double fc, double scale,
+                                                  const double* __restrict__ tab, int nterm) {
+  const int ne = sym ? cnx * (cnx + 1) / 2 : cnx * cny;
+  const int e = int(blockIdx.x) * 64 + int(threadIdx.x);
+  if (e >= ne) return;
+  int cx, cy;
+  if (sym) {
+    tri_coords(e, cx, cy);
+  } else {
+    cx = e % cnx;
+    cy = e / cnx;
+  }
+  const double sx = sxt[cx], sy = syt[cy];
+  const double th2 = t * t * fma(g * H, fma(sx, sx, sy * sy), fc * fc);
+  const int b = far_box(fb, sqrt(th2));
+  double sc, sd;
+  far_span(fb, b, sc, sd);
+  int nl, nh;
+  far_window(fb, sc, sd, nterm, nl, nh);
+  const double x2 = 2.0 * ((th2 - sc) / sd);
+  const double2* cb = cheb + size_t(b) * kCheb;
+  double u1 = 0.0, u2 = 0.0, v1 = 0.0, v2 = 0.0;   // Clenshaw, both sums
+#pragma unroll 8
+  for (int k = kCheb - 1; k >= 1; --k) {
+    const double2 c = cb[k];
+    const double nu = fma(x2, u1, c.x - u2), nv = fma(x2, v1, c.y - v2);
+    u2 = u1;
+    u1 = nu;
+    v2 = v1;
+    v1 = nv;
+  }
+  const double2 c0 = cb[0];
+  const double f1 = fma(0.5 * x2, u1, c0.x - u2), f2 = fma(0.5 * x2, v1, c0.y - v2);
+  TermAcc c;
+  const double2* tb = reinterpret_cast<const double2*>(tab);
+  int j = nl;
+  for (; j + 3 < nh; j += 4) {
+    double q[4][6];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const double2 v = tb[size_t(j + m) * 3 + r];
+        q[m][2 * r] = v.x;
+        q[m][2 * r + 1] = v.y;
+      }
+    const double s1 = q[0][0] + th2, s2 = q[1][0] + th2, s3 = q[2][0] + th2, s4 = q[3][0] + th2;
+    const double d1 = fma(s1, s1, q[0][1]), d2 = fma(s2, s2, q[1][1]);
+    const double d3 = fma(s3, s3, q[2][1]), d4 = fma(s4, s4, q[3][1]);
+    const double p12 = d1 * d2, p34 = d3 * d4;
+    const double r = recip(p12 * p34);
+    const double r12 = r * p34, r34 = r * p12;
+    c.one(q[0], s1, r12 * d2);
+    c.one(q[1], s2, r12 * d1);
+    c.one(q[2], s3, r34 * d4);
+    c.one(q[3], s4, r34 * d3);
+  }
+  for (; j < nh; ++j) {
+    const double* q = tab + size_t(j) * kTermDoubles;
+    const double s = q[0] + th2;
+    c.one(q, s, recip(fma(s, s, q[1])));
+  }
+  coef[e] = make_double2(scale * (f1 + (c.c1a + c.c1b)), scale * (f2 + (c.c2a + c.c2b)));
+}
+
 // F: [3][ny][nxh] half spectra, filtered in place with the coefficients of
 // the mode's canonical frequency: F <- scale c0 F + C1 X F + C2 X^2 F,
 // X = t A(k) with the mode's own (signed) symbols.
@@ -306,6 +535,7 @@ __global__ __launch_bounds__(256) void k_copy_check(const double* __restrict__ f
 constexpr int kCoefWaves = 4;
 constexpr int kCoefBlocks = 8192;
 constexpr int kMinTermsPerWave = 32;
+constexpr int kFarWaves = 4096;  // k_mode_far: waves wanted on the chip (4 per SIMD)
 // Split sums of at most this many bytes are added by k_mode_apply as it reads
 // them (they stay in L2); larger ones by k_mode_coef_sum first.
 constexpr size_t kSplitsInApplyBytes = size_t(2) << 20;
@@ -321,6 +551,81 @@ void mode_coef_shape(int entries, int nterm, int* nw_out, int* ns_out) {
 }
 
 int mode_entries(int cnx, int cny, int sym) { return sym ? cnx * (cnx + 1) / 2 : cnx * cny; }
+
+// Boxes for theta in [0, thmax] and whether they pay.  Work in units of one
+// term at one theta: direct, entries x nterm; boxed, nodes x nterm for the far
+// sums (32 thmax / w + the graded boxes) plus entries x (near terms of a box,
+// 1.76 w / h, at kNearCost: their loads are per lane, 48 bytes a term, where
+// the direct sums read the table through scalar loads) and two launches more
+// (kFarLaunches); w minimises the two sums.  Measured (pole-sum stage, events;
+// direct -> boxed): 2048^2, t rho 5000 (131841 entries, 10034 terms) 510 -> 76
+// us, at kNearCost 1.5 88; 1501 x 1201, t rho 2000 (451351, 4034) 648 -> 68;
+// 1000^2, h = 0.2, t rho 1500 (31626, 7534) 121 -> 45; 701 x 310, t rho 1000
+// (27378, 2034) 34 -> 25; 512^2, t rho 1000 (8385, 2034) stays direct, 14.
+// Error against long double sums (c1 theta, c2 theta^2; rms, t rho 1000):
+// direct 1.5e-16, 3.0e-16, boxed 2.2e-16, 3.4e-16, beside the rounding of
+// theta^2 itself (theta eps / 2 of the result, 5e-14).
+constexpr double kNearCost = 3.0;
+constexpr double kFarLaunches = 2.0e7;
+
+FarBoxes far_boxes(double thmax, double h, double d, int entries, int nterm) {
+  FarBoxes fb{};
+  if (!(h > 0.0 && d > 0.0 && thmax > 0.0 && thmax < 1e7)) return fb;
+  const double near = kFarA / h * kNearCost;
+  double w = std::sqrt(kCheb * thmax * nterm / (near * entries));
+  if (!(w >= 1.0)) w = 1.0;
+  int k = 0;
+  double tg = 4.0;
+  while (tg < w) {
+    tg *= 2.0;
+    ++k;
+  }
+  const int uni = thmax > tg ? int((thmax - tg) / w) + 1 : 0;
+  const int nbox = k + 1 + uni;
+  const double cost = double(kCheb) * nbox * nterm + double(entries) * (near * w + 2.0 * kCheb) + kFarLaunches;
+  if (cost > 0.8 * double(entries) * nterm) return fb;
+  fb.w = w;
+  fb.inv_w = 1.0 / w;
+  fb.tg = tg;
+  fb.d = d;
+  fb.inv_h = 1.0 / h;
+  fb.k = k;
+  fb.nbox = nbox;
+  return fb;
+}
+
+void far_shape(int nbox, int nterm, int* nw_out, int* ns_out) {
+  const int blocks = (nbox + 1) / 2;
+  int nw = 1;
+  while (nw < kCoefWaves && nterm >= 128 * nw) nw *= 2;
+  int ns = 1;
+  while (ns < 64 && blocks * ns * nw < kFarWaves && nterm >= 2 * ns * nw * kMinTermsPerWave) ns *= 2;
+  *nw_out = nw;
+  *ns_out = ns;
+}
+
+size_t far_doubles2(const FarBoxes& fb, int nterm) {
+  if (fb.nbox == 0) return 0;
+  int nw = 1, ns = 1;
+  far_shape(fb.nbox, nterm, &nw, &ns);
+  return size_t(ns + 1) * fb.nbox * kCheb;
+}
+
+void launch_mode_boxed(double2* coef, double2* far, const FarBoxes& fb, int cnx, int cny, int sym, const double* sxt,
+                       const double* syt, double t, double g, double H, double fc, double scale, const double* tab,
+                       int nterm, hipStream_t s) {
+  const int ne = mode_entries(cnx, cny, sym);
+  int nw = 1, ns = 1;
+  far_shape(fb.nbox, nterm, &nw, &ns);
+  double2* cheb = far;
+  double2* node = far + size_t(fb.nbox) * kCheb;
+  const size_t lds = size_t(nw - 1) * 128 * sizeof(double);
+  hipLaunchKernelGGL(k_mode_far, dim3(unsigned((fb.nbox + 1) / 2), unsigned(ns)), dim3(64 * nw), lds, s, node, fb,
+                     tab, nterm);
+  hipLaunchKernelGGL(k_mode_cheb, dim3(unsigned(fb.nbox)), dim3(4 * kCheb), 0, s, cheb, node, fb.nbox, ns);
+  hipLaunchKernelGGL(k_mode_near, dim3(unsigned((ne + 63) / 64)), dim3(64), 0, s, coef, cheb, fb, cnx, cny, sym, sxt,
+                     syt, t, g, H, fc, scale, tab, nterm);
+}
 
 bool mode_sum_in_apply(int entries, int ns) { return ns > 1 && size_t(ns) * entries * 16 <= kSplitsInApplyBytes; }
 

@@ -250,6 +250,7 @@ class DevCopies {
 // with device copies made on demand.
 struct SymTable {
   std::vector<double> s;
+  double s2max = 0.0;   // largest s_x^2 + s_y^2
   DevCopies dev;
 };
 
@@ -272,6 +273,10 @@ static std::shared_ptr<const SymTable> symbol_table(int nx, int ny, int deriv) {
   st->s.resize(size_t(nx / 2 + 1) + ny);
   for (int k = 0; k <= nx / 2; ++k) st->s[k] = axis_symbol(k, nx, deriv);
   for (int k = 0; k < ny; ++k) st->s[nx / 2 + 1 + k] = axis_symbol(k, ny, deriv);
+  double mx = 0.0, my = 0.0;
+  for (int k = 0; k <= nx / 2; ++k) mx = std::max(mx, st->s[k] * st->s[k]);
+  for (int k = 0; k < ny; ++k) my = std::max(my, st->s[nx / 2 + 1 + k] * st->s[nx / 2 + 1 + k]);
+  st->s2max = mx + my;
   std::shared_ptr<const SymTable> out = st;
   std::lock_guard<std::mutex> lk(mu);
   for (auto it = cache.begin(); it != cache.end(); ++it)
@@ -2417,6 +2422,7 @@ struct TermTable {
   int P = 0, nterm = 0;
   double kappa = 0.0, c0 = 0.0;
   std::vector<double> tab;   // nterm x (a, b^2, A1, B1, A2, B2)
+  double d = 0.0;            // entry j has poles at -+d +- i h j (0: it has not)
   DevCopies dev;
 };
 
@@ -2460,6 +2466,15 @@ static std::shared_ptr<const TermTable> term_table(int M, double h, int scheme) 
     }
   }
   tt->nterm = int(tab.size() / 6);
+  // a = d^2 - (h j)^2 and b^2 = (2 d h j)^2 in every entry?
+  if (tt->nterm > 1 && tab[0] > 0.0) {
+    tt->d = std::sqrt(tab[0]);
+    for (int j = 0; j < tt->nterm; ++j) {
+      const double y = h * j, a = tab[0] - y * y, b2 = 4.0 * tab[0] * y * y;
+      if (!(std::fabs(tab[6 * j] - a) <= 1e-9 * (tab[0] + y * y) && std::fabs(tab[6 * j + 1] - b2) <= 1e-9 * b2))
+        tt->d = 0.0;
+    }
+  }
   std::shared_ptr<const TermTable> out = tt;
   std::lock_guard<std::mutex> lk(mu);
   for (auto it = cache.begin(); it != cache.end(); ++it)
@@ -2514,16 +2529,25 @@ static void fourier_canon(int nx, int ny, int deriv, int* cnx, int* cny) {
   *cny = canon_count(ny, ny - 1, deriv);
 }
 
-static size_t fourier_bytes(int nx, int ny, int deriv, int nterm, size_t fft_work) {
+// The boxes of the pole sums for this call (nbox = 0: direct sums).
+static FarBoxes fourier_boxes(const rexii_swe_op* op, double t, int deriv, double h, const FourierPlan& fp) {
+  int cnx = 0, cny = 0;
+  fourier_canon(op->nx, op->ny, deriv, &cnx, &cny);
+  const double s2 = symbol_table(op->nx, op->ny, deriv)->s2max;
+  const double thmax = std::fabs(t) * std::sqrt(op->f_cor * op->f_cor + op->g * op->H0 * s2);
+  return far_boxes(thmax, h, fp.tab->d, mode_entries(cnx, cny, op->nx == op->ny ? 1 : 0), fp.nterm);
+}
+
+static size_t fourier_bytes(int nx, int ny, int deriv, int nterm, size_t fft_work, const FarBoxes& fb) {
   const size_t nm = size_t(nx / 2 + 1) * ny;
   int cnx = 0, cny = 0;
   fourier_canon(nx, ny, deriv, &cnx, &cny);
   const int ne = mode_entries(cnx, cny, nx == ny ? 1 : 0);
   int nw = 1, ns = 1;
   mode_coef_shape(ne, nterm, &nw, &ns);
-  const size_t part = (ns > 1) ? al256(size_t(ns) * ne * 16) : 0;
-  // spectra, coefficients, split sums, finiteness words, and (copied in by
-  // the no-allocation entry point) the term and symbol tables
+  const size_t part = fb.nbox > 0 ? al256(far_doubles2(fb, nterm) * 16) : (ns > 1) ? al256(size_t(ns) * ne * 16) : 0;
+  // spectra, coefficients, split sums or the boxes' sums, finiteness words,
+  // and (copied in by the no-allocation entry point) the term and symbol tables
   return al256(3 * nm * 16) + al256(size_t(ne) * 16) + part + al256(kCopyCheckMaxBlocks * sizeof(int)) +
          al256(size_t(nterm) * 48) + al256((size_t(nx / 2 + 1) + ny) * 8) + al256(fft_work);
 }
@@ -2553,8 +2577,10 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     FourierPlan fp;
     rexii_status s = fourier_plan(op, t, o, deriv, fp);
     if (s != REXII_OK) return s;
+    FarBoxes fb = fourier_boxes(op, t, deriv, o.h, fp);
     if (noalloc) {
-      const size_t fixed = fourier_bytes(nx, ny, deriv, fp.nterm, 0);
+      const size_t fixed = std::min(fourier_bytes(nx, ny, deriv, fp.nterm, 0, fb),
+                                    fourier_bytes(nx, ny, deriv, fp.nterm, 0, FarBoxes{}));
       if (fixed > REXII_STATIC_SCRATCH_BYTES)
         return set_error(REXII_ERR_WORKSPACE, "problem needs more than the " +
                                                   std::to_string(REXII_STATIC_SCRATCH_BYTES >> 20) +
@@ -2565,7 +2591,11 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     void *fwd = nullptr, *inv = nullptr;
     s = fft_plans(nx, ny, &work, &fwd, &inv, !noalloc);
     if (s != REXII_OK) return s;
-    const size_t need = fourier_bytes(nx, ny, deriv, fp.nterm, work);
+    size_t need = fourier_bytes(nx, ny, deriv, fp.nterm, work, fb);
+    if (noalloc && need > REXII_STATIC_SCRATCH_BYTES) {
+      fb = FarBoxes{};
+      need = fourier_bytes(nx, ny, deriv, fp.nterm, work, fb);
+    }
     int cnx = 0, cny = 0;
     fourier_canon(nx, ny, deriv, &cnx, &cny);
     if (noalloc) {
@@ -2588,13 +2618,16 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     const int ne = mode_entries(cnx, cny, sq);
     int nw = 1, ns = 1;
     mode_coef_shape(ne, fp.nterm, &nw, &ns);
-    const bool sum_in_apply = mode_sum_in_apply(ne, ns);
+    const bool boxed = fb.nbox > 0;
+    if (boxed) far_shape(fb.nbox, fp.nterm, &nw, &ns);
+    const bool sum_in_apply = !boxed && mode_sum_in_apply(ne, ns);
     const std::vector<double>& htab = fp.tab->tab;
     const std::shared_ptr<const SymTable> sym = symbol_table(nx, ny, deriv);
     const int ncheck = copy_check_blocks(n3);
     double2* F = ar.take<double2>(3 * nm);
     double2* coef = ar.take<double2>(size_t(ne));
-    double2* part = (ns > 1) ? ar.take<double2>(size_t(ns) * ne) : nullptr;
+    double2* part = boxed ? ar.take<double2>(far_doubles2(fb, fp.nterm))
+                          : (ns > 1) ? ar.take<double2>(size_t(ns) * ne) : nullptr;
     int* flags = ar.take<int>(kCopyCheckMaxBlocks);
     void* wk = work ? static_cast<void*>(ar.take<char>(work)) : nullptr;
     // the term and symbol tables: the library's device copies, or (the
@@ -2617,6 +2650,11 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     const bool prof = (o.profile != 0);
     const double scale = 1.0 / (double(nx) * ny);
     auto pole_sums = [&](hipStream_t q) {
+      if (boxed) {
+        launch_mode_boxed(coef, part, fb, cnx, cny, sq, sxt, syt, t, op->g, op->H0, op->f_cor, scale, tab, fp.nterm,
+                          q);
+        return;
+      }
       launch_mode_coef(coef, part, cnx, cny, sq, sxt, syt, t, op->g, op->H0, op->f_cor, scale, tab, fp.nterm, nw, ns,
                        q);
     };
@@ -3251,7 +3289,12 @@ rexii_status rexii_fourier_workspace_size(const rexii_swe_op* op, const rexii_op
   size_t work = 0;
   v = fft_plans(op->nx, op->ny, &work, nullptr, nullptr);
   if (v != REXII_OK) return v;
-  *bytes = fourier_bytes(op->nx, op->ny, derivative, fp.nterm, work);
+  try {
+    *bytes = fourier_bytes(op->nx, op->ny, derivative, fp.nterm, work,
+                           fourier_boxes(op, t, derivative, resolve_opts(opts).h, fp));
+  } catch (const std::bad_alloc&) {
+    return set_error(REXII_ERR_OOM, "host allocation failed");
+  }
   return clear_error();
 }
 
