@@ -343,15 +343,18 @@ rexii_status rexii_shifted_solve(const rexii_swe_op* op, const double* f, double
  *     repeat along each axis: they are formed once per distinct pair
  *     (about 1/8 of the half spectrum on even grids with centred
  *     differences; on square grids the pair is unordered, about 1/16) and
- *     applied to every mode.
+ *     applied to every mode.  With many pairs and terms the terms far from
+ *     an interval of frequencies are summed as one polynomial there.
  *   Report: P, M, N, m0, h, t, rho, kappa_sum; solves = terms of the sum
  *     (two poles of one n share a denominator); total_iters = distinct
  *     frequencies the sums were formed at; slots = waves per block of the
  *     sum kernel; tile_rows = its term splits; alg_bytes = algorithmic HBM bytes of the path;
  *     kernel_bytes = those of the apply kernel (96 per half-spectrum mode).
- *     With opts.profile = 1: step_ms[0..4] = copy and finiteness check,
- *     forward FFT, pole sums, apply, inverse FFT (HIP events, ms);
- *     kernel_ms = step_ms[2], kernel_launches = 1.
+ *     With opts.profile = 1: step_ms[0..4] (HIP events, ms) = rows forward
+ *     of eta and of the velocities (with the finiteness check), pole sums,
+ *     columns (FFT, filter, inverse FFT), rows inverse; where rocFFT does
+ *     the transforms, copy and finiteness check, forward FFT, pole sums,
+ *     filter, inverse FFT.  kernel_ms = step_ms[2], kernel_launches = 1.
  * Errors: INVALID_ARG (also for a depth field or an unknown derivative),
  * NONFINITE (u is written anyway), OOM, HIP (including rocFFT failures),
  * WORKSPACE. */

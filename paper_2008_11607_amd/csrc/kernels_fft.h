@@ -15,7 +15,7 @@ namespace rexii {
 int canon_count(int n, int kmax, int deriv);
 // coef [cny][cnx] = scale (Re c1, Re c2) per canonical pair; nw waves per
 // block, the terms in ns splits (part: ns x entries double2 when ns > 1).
-void mode_coef_shape(int entries, int nterm, int* nw, int* ns);
+void mode_coef_shape(int entries, int nterm, bool whole, int* nw, int* ns);
 // sxt, syt: the axis symbols s(k) of the x wavenumbers 0..nx/2 and the y
 // wavenumbers 0..ny-1 (axis_symbol), device.
 double axis_symbol(int k, int n, int deriv);
@@ -44,12 +44,40 @@ size_t far_doubles2(const FarBoxes& fb, int nterm);  // double2 of scratch
 void launch_mode_boxed(double2* coef, double2* far, const FarBoxes& fb, int cnx, int cny, int sym, const double* sxt,
                        const double* syt, double t, double g, double H, double fc, double scale, const double* tab,
                        int nterm, hipStream_t s);
-// F [3][ny][nx/2+1] <- a0 F + C1 t A F + C2 (t A)^2 F with (C1, C2) from
-// coef (ns <= 1: scaled entries; ns > 1: ns x ne unscaled split sums, added
-// in order and multiplied by scale).
-void launch_mode_apply(double2* F, const double2* coef, int ns, int ne, double scale, int cnx, int sym, int nx,
-                       int ny, int deriv, const double* sxt, const double* syt, double t, double g, double H,
-                       double fc, double a0, hipStream_t s);
+// What the filter of a mode needs: the coefficients (ns <= 1: scaled entries;
+// ns > 1: ns x ne unscaled split sums, added in order and multiplied by
+// scale) and the axis symbols.
+struct ModeFilter {
+  const double2* coef;
+  int ns, ne;
+  double scale;
+  int cnx, sym, nx, ny, deriv;
+  const double *sxt, *syt;
+  double t, g, H, fc, a0;
+};
+// F [3][ny][nx/2+1] <- a0 F + C1 t A F + C2 (t A)^2 F
+void launch_mode_apply(double2* F, const ModeFilter& mf, hipStream_t s);
+
+// Own transforms (kernels_fft2d.hip).  fft_points: 0 if a length is not done
+// there; fft_axis_doubles/fill: its table (twiddles and chirp), to be handed
+// to fft_axis as a device copy.
+struct FftAxis {
+  int n, lm;  // length, log2 of the points of its FFT
+  const double2 *tw, *chirp, *bhat;
+};
+int fft_points(int n);
+size_t fft_axis_doubles(int n);
+void fft_axis_fill(int n, double* out);
+FftAxis fft_axis(int n, const double* tab);
+int rows_blocks(const FftAxis& ax, int pairs);
+// Row pairs [first, first + pairs) of the 3 (ny+1)/2 of a state; one word per
+// block in flags (rows_blocks of them).
+hipError_t launch_rows_fwd(const double* f, double2* G, const FftAxis& ax, int ny, int first, int pairs, int* flags,
+                           hipStream_t s);
+hipError_t launch_cols(double2* G, const FftAxis& ax, int nxh, const ModeFilter& mf, const int* flags, int nflags,
+                       int* word, hipStream_t s);
+hipError_t launch_rows_inv(const double2* G, double* u, const FftAxis& ax, int ny, hipStream_t s);
+
 // u = f and one finiteness word per block: flags[copy_check_blocks(n)]
 // (at most kCopyCheckMaxBlocks), each 0 or 1.
 constexpr int kCopyCheckMaxBlocks = 2048;

@@ -43,6 +43,7 @@
 
 #include "kernels.h"
 #include "kernels_fft.h"
+#include "mode_filter.h"
 #include "rexii_internal.h"
 
 namespace rexii {
@@ -149,21 +150,6 @@ __device__ __forceinline__ void term_sums(const double* __restrict__ tab, int nt
   c2 = c.c2a + c.c2b;
 }
 
-// Canonical wavenumber of k on an axis of n points: the smallest index
-// with the same s^2 (centred differences: sin^2(2 pi k / n) has period n/2
-// and is symmetric about n/4 for even n, symmetric about n/2 for odd n;
-// Fourier differentiation: s^2 depends on |signed k|, the Nyquist mode's
-// derivative is 0).  theta, and with it the coefficients of r(t A(k)),
-// depends on the mode only through these two numbers.
-__host__ __device__ inline int canon_index(int k, int n, int deriv) {
-  if (deriv == 0 && n % 2 == 0) {
-    const int h = n / 2, kc = k % h;
-    return kc < h - kc ? kc : h - kc;
-  }
-  if (deriv != 0 && 2 * k == n) return 0;
-  return k < n - k ? k : n - k;
-}
-
 int canon_count(int n, int kmax, int deriv) {
   int c = 0;
   for (int k = 0; k <= kmax; ++k) {
@@ -181,9 +167,6 @@ int canon_count(int n, int kmax, int deriv) {
 // added in wave order through (nw - 1) x 1 KB of dynamic LDS.  With one
 // split the block writes scale (c1, c2) to coef; with several it writes its
 // unscaled sums to part[s][e] and k_mode_coef_sum adds the splits in order.
-// Symmetric tables (square grids: s_x and s_y are the same function, so the
-// pairs (a, b) and (b, a) share theta): entries e = b (b + 1) / 2 + a, a <= b.
-__host__ __device__ inline int tri_index(int a, int b) { return a <= b ? b * (b + 1) / 2 + a : a * (a + 1) / 2 + b; }
 __device__ inline void tri_coords(int e, int& a, int& b) {
   b = int((sqrt(8.0 * double(e) + 1.0) - 1.0) * 0.5);
   if ((b + 1) * (b + 2) / 2 <= e) ++b;
@@ -462,52 +445,18 @@ __global__ __launch_bounds__(64) void k_mode_near(double2* __restrict__ coef, co
   coef[e] = make_double2(scale * (f1 + (c.c1a + c.c1b)), scale * (f2 + (c.c2a + c.c2b)));
 }
 
-// F: [3][ny][nxh] half spectra, filtered in place with the coefficients of
-// the mode's canonical frequency: F <- scale c0 F + C1 X F + C2 X^2 F,
-// X = t A(k) with the mode's own (signed) symbols.
-__global__ __launch_bounds__(256) void k_mode_apply(double2* __restrict__ F, const double2* __restrict__ coef,
-                                                    int ns, int ne, double scale, int cnx, int sym, int nx, int ny,
-                                                    int deriv, const double* __restrict__ sxt,
-                                                    const double* __restrict__ syt, double t, double g, double H,
-                                                    double fc, double a0) {
-  const int nxh = nx / 2 + 1;
-  const int nm = nxh * ny;
+// F: [3][ny][nxh] half spectra, filtered in place.
+__global__ __launch_bounds__(256) void k_mode_apply(double2* __restrict__ F, ModeFilter mf) {
+  const int nxh = mf.nx / 2 + 1;
+  const int nm = nxh * mf.ny;
   const int m = int(blockIdx.x) * 256 + threadIdx.x;
   if (m >= nm) return;
-  const int kx = m % nxh, ky = m / nxh;
-  const int ca = canon_index(kx, nx, deriv), cb = canon_index(ky, ny, deriv);
-  const int e = sym ? tri_index(ca, cb) : cb * cnx + ca;
-  double2 c;
-  if (ns <= 1) {
-    c = coef[e];
-  } else {
-    // the splits' unscaled sums, added in split order (as k_mode_coef_sum)
-    double c1 = 0.0, c2 = 0.0;
-    for (int q = 0; q < ns; ++q) {
-      const double2 v = coef[size_t(q) * ne + e];
-      c1 += v.x;
-      c2 += v.y;
-    }
-    c = make_double2(scale * c1, scale * c2);
-  }
-  const double sx = sxt[kx], sy = syt[ky];
   double2 f[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q) f[q] = F[size_t(q) * nm + m];
-  // X v with X = t A(k); -i a (x + i y) = (a y, -a x)
-  const double hx = t * H * sx, hy = t * H * sy, gx = t * g * sx, gy = t * g * sy, tf = t * fc;
-  auto apply = [&](const double2 (&v)[3], double2 (&o)[3]) {
-    o[0] = make_double2(hx * v[1].y + hy * v[2].y, -(hx * v[1].x + hy * v[2].x));
-    o[1] = make_double2(gx * v[0].y + tf * v[2].x, -gx * v[0].x + tf * v[2].y);
-    o[2] = make_double2(gy * v[0].y - tf * v[1].x, -gy * v[0].x - tf * v[1].y);
-  };
-  double2 x1[3], x2[3];
-  apply(f, x1);
-  apply(x1, x2);
+  mode_filter(mf, m % nxh, m / nxh, f);
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
-    F[size_t(q) * nm + m] = make_double2(a0 * f[q].x + c.x * x1[q].x + c.y * x2[q].x,
-                                         a0 * f[q].y + c.x * x1[q].y + c.y * x2[q].y);
+  for (int q = 0; q < 3; ++q) F[size_t(q) * nm + m] = f[q];
 }
 
 // u = f; flags[b] = 1 if block b met a value that is not finite, else 0
@@ -535,17 +484,26 @@ __global__ __launch_bounds__(256) void k_copy_check(const double* __restrict__ f
 constexpr int kCoefWaves = 4;
 constexpr int kCoefBlocks = 8192;
 constexpr int kMinTermsPerWave = 32;
+// Where k_cols reads the coefficients (whole = true) the splits would be added
+// for each of a thread's modes one after the other: splits only where the
+// waves of the blocks leave more than half the SIMDs empty.  512^2: 8 splits,
+// sums + columns 15 + 27 us, one split of 16 waves 19 + 16.
+constexpr int kWholeWaves = 2048;
 constexpr int kFarWaves = 4096;  // k_mode_far: waves wanted on the chip (4 per SIMD)
 // Split sums of at most this many bytes are added by k_mode_apply as it reads
 // them (they stay in L2); larger ones by k_mode_coef_sum first.
 constexpr size_t kSplitsInApplyBytes = size_t(2) << 20;
 
-void mode_coef_shape(int entries, int nterm, int* nw_out, int* ns_out) {
+void mode_coef_shape(int entries, int nterm, bool whole, int* nw_out, int* ns_out) {
   const int blocks = (entries + 63) / 64;
-  int nw = 1;
-  while (nw < kCoefWaves && nterm >= 128 * nw) nw *= 2;
-  int ns = 1;
-  while (ns < 64 && blocks * ns < kCoefBlocks && nterm >= 2 * ns * nw * kMinTermsPerWave) ns *= 2;
+  int nw = 1, ns = 1;
+  if (whole) {
+    while (nw < kModeWaves && nterm >= 64 * nw) nw *= 2;
+    while (ns < 64 && blocks * ns * nw < kWholeWaves && nterm >= 2 * ns * nw * kMinTermsPerWave) ns *= 2;
+  } else {
+    while (nw < kCoefWaves && nterm >= 128 * nw) nw *= 2;
+    while (ns < 64 && blocks * ns < kCoefBlocks && nterm >= 2 * ns * nw * kMinTermsPerWave) ns *= 2;
+  }
   *nw_out = nw;
   *ns_out = ns;
 }
@@ -640,12 +598,9 @@ void launch_mode_coef(double2* coef, double2* part, int cnx, int cny, int sym, c
     hipLaunchKernelGGL(k_mode_coef_sum, dim3(unsigned((ne + 255) / 256)), dim3(256), 0, s, coef, part, ne, ns, scale);
 }
 
-void launch_mode_apply(double2* F, const double2* coef, int ns, int ne, double scale, int cnx, int sym, int nx,
-                       int ny, int deriv, const double* sxt, const double* syt, double t, double g, double H,
-                       double fc, double a0, hipStream_t s) {
-  const long nm = long(nx / 2 + 1) * ny;
-  hipLaunchKernelGGL(k_mode_apply, dim3(unsigned((nm + 255) / 256)), dim3(256), 0, s, F, coef, ns, ne, scale, cnx,
-                     sym, nx, ny, deriv, sxt, syt, t, g, H, fc, a0);
+void launch_mode_apply(double2* F, const ModeFilter& mf, hipStream_t s) {
+  const long nm = long(mf.nx / 2 + 1) * mf.ny;
+  hipLaunchKernelGGL(k_mode_apply, dim3(unsigned((nm + 255) / 256)), dim3(256), 0, s, F, mf);
 }
 
 int copy_check_blocks(size_t n) {

@@ -289,6 +289,42 @@ static std::shared_ptr<const SymTable> symbol_table(int nx, int ny, int deriv) {
   return out;
 }
 
+// Tables of one transform length (kernels_fft2d.hip), kept like the symbols
+// (16 most recent lengths).
+struct AxisTable {
+  std::vector<double> v;
+  DevCopies dev;
+};
+
+static std::shared_ptr<const AxisTable> axis_table(int n) {
+  static std::mutex mu;
+  using Entry = std::pair<int, std::shared_ptr<const AxisTable>>;
+  static std::deque<Entry>& cache = *new std::deque<Entry>();
+  auto take = [&]() -> std::shared_ptr<const AxisTable> {
+    for (auto it = cache.begin(); it != cache.end(); ++it)
+      if (it->first == n) {
+        auto hit = *it;
+        cache.erase(it);
+        cache.push_front(hit);
+        return hit.second;
+      }
+    return nullptr;
+  };
+  {
+    std::lock_guard<std::mutex> lk(mu);
+    if (auto hit = take()) return hit;
+  }
+  auto at = std::make_shared<AxisTable>();
+  at->v.resize(fft_axis_doubles(n));
+  fft_axis_fill(n, at->v.data());
+  std::shared_ptr<const AxisTable> out = at;
+  std::lock_guard<std::mutex> lk(mu);
+  if (auto hit = take()) return hit;   // made meanwhile by another thread
+  cache.push_front({n, out});
+  while (cache.size() > 16) cache.pop_back();
+  return out;
+}
+
 // ---------------------------------------------------------------------------
 // problem description
 // ---------------------------------------------------------------------------
@@ -2529,6 +2565,11 @@ static void fourier_canon(int nx, int ny, int deriv, int* cnx, int* cny) {
   *cny = canon_count(ny, ny - 1, deriv);
 }
 
+// finiteness words: one a block of the check (rocFFT route) or of the forward
+// rows (at most 3 x 2048 pairs, in two launches), and their sum
+constexpr int kFourierFlags = 3 * 2048 + 8;
+static_assert(kFourierFlags > kCopyCheckMaxBlocks, "finiteness words");
+
 // The boxes of the pole sums for this call (nbox = 0: direct sums).
 static FarBoxes fourier_boxes(const rexii_swe_op* op, double t, int deriv, double h, const FourierPlan& fp) {
   int cnx = 0, cny = 0;
@@ -2538,18 +2579,42 @@ static FarBoxes fourier_boxes(const rexii_swe_op* op, double t, int deriv, doubl
   return far_boxes(thmax, h, fp.tab->d, mode_entries(cnx, cny, op->nx == op->ny ? 1 : 0), fp.nterm);
 }
 
-static size_t fourier_bytes(int nx, int ny, int deriv, int nterm, size_t fft_work, const FarBoxes& fb) {
+// Transforms by kernels_fft2d.hip, or by rocFFT: lengths the former's buffers
+// do not hold, and grids of lengths with no prime above 13 where a chirp
+// would work many more points than the length has: over 1024, and 513..1024
+// at under a third of its points, in y, or in x beside another chirp.
+// Measured (call, rocFFT -> own, us): 701 x 310 262 -> 110, 1501 x 1201
+// 1398 -> 362, 125^2 86 -> 56, 384^2 84 -> 76, 700 x 900 171 -> 163, 1920 x
+// 1024 249 -> 221, 512^2 93 -> 73, 2048^2 510 -> 286, 4096^2 1776 -> 1077; the
+// other side of the line: 600^2 120 -> 128, 512 x 1080 149 -> 148, 1200^2
+// 215 -> 295, 1536^2 287 -> 371, 2000^2 457 -> 467.
+static bool fourier_own(int nx, int ny) {
+  if (fft_points(nx) == 0 || fft_points(ny) == 0) return false;
+  auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
+  auto friendly = [](int n) {
+    for (int p : {2, 3, 5, 7, 11, 13})
+      while (n % p == 0) n /= p;
+    return n == 1;
+  };
+  auto wasteful = [&](int n) { return !pow2(n) && (n > 1024 || (n > 512 && fft_points(n) > 3 * n)); };
+  if (!friendly(nx) || !friendly(ny)) return true;
+  return !wasteful(ny) && (!wasteful(nx) || pow2(ny));
+}
+
+static size_t fourier_bytes(int nx, int ny, int deriv, int nterm, size_t fft_work, const FarBoxes& fb, bool own) {
   const size_t nm = size_t(nx / 2 + 1) * ny;
   int cnx = 0, cny = 0;
   fourier_canon(nx, ny, deriv, &cnx, &cny);
   const int ne = mode_entries(cnx, cny, nx == ny ? 1 : 0);
   int nw = 1, ns = 1;
-  mode_coef_shape(ne, nterm, &nw, &ns);
+  mode_coef_shape(ne, nterm, own, &nw, &ns);
   const size_t part = fb.nbox > 0 ? al256(far_doubles2(fb, nterm) * 16) : (ns > 1) ? al256(size_t(ns) * ne * 16) : 0;
   // spectra, coefficients, split sums or the boxes' sums, finiteness words,
-  // and (copied in by the no-allocation entry point) the term and symbol tables
-  return al256(3 * nm * 16) + al256(size_t(ne) * 16) + part + al256(kCopyCheckMaxBlocks * sizeof(int)) +
-         al256(size_t(nterm) * 48) + al256((size_t(nx / 2 + 1) + ny) * 8) + al256(fft_work);
+  // and (copied in by the no-allocation entry point) the term, symbol and
+  // transform tables
+  const size_t fft = own ? al256(fft_axis_doubles(nx) * 8) + al256(fft_axis_doubles(ny) * 8) : al256(fft_work);
+  return al256(3 * nm * 16) + al256(size_t(ne) * 16) + part + al256((own ? kFourierFlags : kCopyCheckMaxBlocks) * sizeof(int)) +
+         al256(size_t(nterm) * 48) + al256((size_t(nx / 2 + 1) + ny) * 8) + fft;
 }
 
 // noalloc: device scratch from the library's static array, FFT plans only
@@ -2579,8 +2644,8 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     if (s != REXII_OK) return s;
     FarBoxes fb = fourier_boxes(op, t, deriv, o.h, fp);
     if (noalloc) {
-      const size_t fixed = std::min(fourier_bytes(nx, ny, deriv, fp.nterm, 0, fb),
-                                    fourier_bytes(nx, ny, deriv, fp.nterm, 0, FarBoxes{}));
+      const size_t fixed = std::min(fourier_bytes(nx, ny, deriv, fp.nterm, 0, fb, false),
+                                    fourier_bytes(nx, ny, deriv, fp.nterm, 0, FarBoxes{}, false));
       if (fixed > REXII_STATIC_SCRATCH_BYTES)
         return set_error(REXII_ERR_WORKSPACE, "problem needs more than the " +
                                                   std::to_string(REXII_STATIC_SCRATCH_BYTES >> 20) +
@@ -2591,10 +2656,21 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     void *fwd = nullptr, *inv = nullptr;
     s = fft_plans(nx, ny, &work, &fwd, &inv, !noalloc);
     if (s != REXII_OK) return s;
-    size_t need = fourier_bytes(nx, ny, deriv, fp.nterm, work, fb);
+    bool own = fourier_own(nx, ny);
+    size_t need = fourier_bytes(nx, ny, deriv, fp.nterm, work, fb, own);
     if (noalloc && need > REXII_STATIC_SCRATCH_BYTES) {
-      fb = FarBoxes{};
-      need = fourier_bytes(nx, ny, deriv, fp.nterm, work, fb);
+      // the layout with the least scratch: no call that fits is refused
+      for (int k = 3; k >= 0; --k) {
+        const FarBoxes b = (k & 1) ? fb : FarBoxes{};
+        const bool w = (k & 2) != 0 && fourier_own(nx, ny);
+        const size_t nb = fourier_bytes(nx, ny, deriv, fp.nterm, work, b, w);
+        if (nb <= REXII_STATIC_SCRATCH_BYTES) {
+          fb = b;
+          own = w;
+          need = nb;
+          break;
+        }
+      }
     }
     int cnx = 0, cny = 0;
     fourier_canon(nx, ny, deriv, &cnx, &cny);
@@ -2617,19 +2693,27 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     const int sq = (nx == ny) ? 1 : 0;   // square grid: unordered frequency pairs
     const int ne = mode_entries(cnx, cny, sq);
     int nw = 1, ns = 1;
-    mode_coef_shape(ne, fp.nterm, &nw, &ns);
+    mode_coef_shape(ne, fp.nterm, own, &nw, &ns);
     const bool boxed = fb.nbox > 0;
     if (boxed) far_shape(fb.nbox, fp.nterm, &nw, &ns);
     const bool sum_in_apply = !boxed && mode_sum_in_apply(ne, ns);
     const std::vector<double>& htab = fp.tab->tab;
     const std::shared_ptr<const SymTable> sym = symbol_table(nx, ny, deriv);
-    const int ncheck = copy_check_blocks(n3);
+    const int npy = (ny + 1) / 2;
+    FftAxis ax{}, ay{};
+    std::shared_ptr<const AxisTable> axt, ayt;
+    if (own) {
+      axt = axis_table(nx);
+      ayt = axis_table(ny);
+      ax = fft_axis(nx, nullptr);
+    }
+    const int ncheck = own ? 1 : copy_check_blocks(n3);
     double2* F = ar.take<double2>(3 * nm);
     double2* coef = ar.take<double2>(size_t(ne));
     double2* part = boxed ? ar.take<double2>(far_doubles2(fb, fp.nterm))
                           : (ns > 1) ? ar.take<double2>(size_t(ns) * ne) : nullptr;
-    int* flags = ar.take<int>(kCopyCheckMaxBlocks);
-    void* wk = work ? static_cast<void*>(ar.take<char>(work)) : nullptr;
+    int* flags = ar.take<int>(own ? kFourierFlags : kCopyCheckMaxBlocks);
+    void* wk = work && !own ? static_cast<void*>(ar.take<char>(work)) : nullptr;
     // the term and symbol tables: the library's device copies, or (the
     // no-allocation entry point) copies from pageable host memory into its
     // scratch
@@ -2642,9 +2726,21 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
       HIPCHK(hipMemcpyAsync(dsym, sym->s.data(), sym->s.size() * sizeof(double), hipMemcpyHostToDevice, st));
       tab = dtab;
       sxt = dsym;
+      if (own) {
+        double* dx = ar.take<double>(axt->v.size());
+        HIPCHK(hipMemcpyAsync(dx, axt->v.data(), axt->v.size() * sizeof(double), hipMemcpyHostToDevice, st));
+        ax = fft_axis(nx, dx);
+        double* dy = ar.take<double>(ayt->v.size());
+        HIPCHK(hipMemcpyAsync(dy, ayt->v.data(), ayt->v.size() * sizeof(double), hipMemcpyHostToDevice, st));
+        ay = fft_axis(ny, dy);
+      }
     } else {
       tab = fp.tab->dev.get(htab);
       sxt = sym->dev.get(sym->s);
+      if (own) {
+        ax = fft_axis(nx, axt->dev.get(axt->v));
+        ay = fft_axis(ny, ayt->dev.get(ayt->v));
+      }
     }
     const double* syt = sxt + (nx / 2 + 1);
     const bool prof = (o.profile != 0);
@@ -2658,17 +2754,32 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
       launch_mode_coef(coef, part, cnx, cny, sq, sxt, syt, t, op->g, op->H0, op->f_cor, scale, tab, fp.nterm, nw, ns,
                        q);
     };
-    auto apply_modes = [&](hipStream_t q) {
-      launch_mode_apply(F, sum_in_apply ? part : coef, sum_in_apply ? ns : 1, ne, scale, cnx, sq, nx, ny, deriv, sxt,
-                        syt, t, op->g, op->H0, op->f_cor, scale * fp.c0, q);
-    };
-    // the whole sequence on stream q (eager, or captured into a graph)
+    const ModeFilter mf{sum_in_apply ? part : coef, sum_in_apply ? ns : 1, ne, scale, cnx, sq, nx, ny, deriv, sxt, syt,
+                        t, op->g, op->H0, op->f_cor, scale * fp.c0};
+    // the words are read from pinned host memory (kept per host thread for
+    // the life of the process): copied there, ordered on the stream, or
+    // written there by k_cols; without pinned memory, copied after the
+    // stream is drained
+    static thread_local int* hflag = nullptr;
+    if (!noalloc && !hflag)
+      HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&hflag), kCopyCheckMaxBlocks * sizeof(int),
+                           hipHostMallocPortable | hipHostMallocMapped));
+    const int fx1 = own ? rows_blocks(ax, npy) : 0;   // blocks of the first field's rows (profiled calls)
+    int* word = noalloc ? flags + kFourierFlags - 1 : hflag;
+    // the whole sequence on stream q
     auto enqueue = [&](hipStream_t q) -> rexii_status {
+      if (own) {
+        HIPCHK(launch_rows_fwd(f, F, ax, ny, 0, 3 * npy, flags, q));
+        pole_sums(q);
+        HIPCHK(launch_cols(F, ay, nx / 2 + 1, mf, flags, rows_blocks(ax, 3 * npy), word, q));
+        HIPCHK(launch_rows_inv(F, u, ax, ny, q));
+        return REXII_OK;
+      }
       launch_copy_check(f, u, n3, flags, q);  // the forward transform may overwrite its input
       rexii_status e1 = fft_execute(fwd, u, F, wk, work, q);
       if (e1 != REXII_OK) return e1;
       pole_sums(q);
-      apply_modes(q);
+      launch_mode_apply(F, mf, q);
       return fft_execute(inv, F, u, wk, work, q);
     };
     // profiling events: created once per host thread and kept
@@ -2678,17 +2789,31 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
         for (auto& e : ev) HIPCHK(hipEventCreate(&e));
       // one stage after the other, timed
       HIPCHK(hipEventRecord(ev[0], st));
-      launch_copy_check(f, u, n3, flags, st);  // the forward transform may overwrite its input
+      if (own)
+        HIPCHK(launch_rows_fwd(f, F, ax, ny, 0, npy, flags, st));
+      else
+        launch_copy_check(f, u, n3, flags, st);  // the forward transform may overwrite its input
       HIPCHK(hipEventRecord(ev[1], st));
-      s = fft_execute(fwd, u, F, wk, work, st);
-      if (s != REXII_OK) return s;
+      if (own) {
+        HIPCHK(launch_rows_fwd(f, F, ax, ny, npy, 2 * npy, flags + fx1, st));
+      } else {
+        s = fft_execute(fwd, u, F, wk, work, st);
+        if (s != REXII_OK) return s;
+      }
       HIPCHK(hipEventRecord(ev[2], st));
       pole_sums(st);
       HIPCHK(hipEventRecord(ev[3], st));
-      apply_modes(st);
+      if (own)
+        HIPCHK(launch_cols(F, ay, nx / 2 + 1, mf, flags, fx1 + rows_blocks(ax, 2 * npy), word, st));
+      else
+        launch_mode_apply(F, mf, st);
       HIPCHK(hipEventRecord(ev[4], st));
-      s = fft_execute(inv, F, u, wk, work, st);
-      if (s != REXII_OK) return s;
+      if (own) {
+        HIPCHK(launch_rows_inv(F, u, ax, ny, st));
+      } else {
+        s = fft_execute(inv, F, u, wk, work, st);
+        if (s != REXII_OK) return s;
+      }
       HIPCHK(hipEventRecord(ev[5], st));
     } else {
       s = enqueue(st);
@@ -2701,15 +2826,10 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
       // no pinned memory: the stream is drained, then the words are copied
       hflags.resize(ncheck);
       HIPCHK(hipStreamSynchronize(st));
-      HIPCHK(hipMemcpy(hflags.data(), flags, ncheck * sizeof(int), hipMemcpyDeviceToHost));
+      HIPCHK(hipMemcpy(hflags.data(), own ? word : flags, ncheck * sizeof(int), hipMemcpyDeviceToHost));
       fl = hflags.data();
     } else {
-      // the words are read into pinned host memory (kept per host thread for
-      // the life of the process), ordered on the stream
-      static thread_local int* hflag = nullptr;
-      if (!hflag)
-        HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&hflag), kCopyCheckMaxBlocks * sizeof(int), hipHostMallocDefault));
-      HIPCHK(hipMemcpyAsync(hflag, flags, ncheck * sizeof(int), hipMemcpyDeviceToHost, st));
+      if (!own) HIPCHK(hipMemcpyAsync(hflag, flags, ncheck * sizeof(int), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
       fl = hflag;
     }
@@ -2728,8 +2848,10 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
       rep->slots = nw;
       rep->tile_rows = ns;    // term splits of the sum kernel
       rep->total_iters = ne;  // distinct frequencies the pole sums were formed at
-      // copy 16, forward FFT 8 + 16 nm/n, apply 2 x 48 nm/n, inverse 16 nm/n + 8 bytes per point and field
-      rep->alg_bytes = double(n3) * 32.0 + 3.0 * double(nm) * (16.0 + 96.0 + 16.0);
+      // rows 8 + 16 nm/n, columns 32 nm/n, rows 16 nm/n + 8 bytes per point and
+      // field; rocFFT: copy 16, forward FFT 8 + 16 nm/n, apply 32 nm/n, inverse
+      // 16 nm/n + 8
+      rep->alg_bytes = double(n3) * (own ? 16.0 : 32.0) + 3.0 * double(nm) * 64.0;
       rep->kernel_bytes = 96.0 * double(nm);
       if (prof) {
         float ms[5] = {};
@@ -3291,7 +3413,7 @@ rexii_status rexii_fourier_workspace_size(const rexii_swe_op* op, const rexii_op
   if (v != REXII_OK) return v;
   try {
     *bytes = fourier_bytes(op->nx, op->ny, derivative, fp.nterm, work,
-                           fourier_boxes(op, t, derivative, resolve_opts(opts).h, fp));
+                           fourier_boxes(op, t, derivative, resolve_opts(opts).h, fp), fourier_own(op->nx, op->ny));
   } catch (const std::bad_alloc&) {
     return set_error(REXII_ERR_OOM, "host allocation failed");
   }
