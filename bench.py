@@ -37,6 +37,10 @@ sys.path.insert(0, ROOT)
 
 METRIC = "grid-pt·pole solves/s + HBM GB/s at rel-L2 ≤1e-6 vs FP64 oracle"
 HBM_PEAK_GBS = 8000.0
+FP32_PEAK_TFLOPS = 157.3
+# COCG inner step, real flops per complex point: (L - zeta) p 20, the updates
+# of d, r and p 24, four bilinear sums and |r|^2 36
+COCG_FLOPS_PER_POINT = 80
 D = 512
 TRHO = 1000.0
 FC = 10.0
@@ -352,7 +356,7 @@ def run_multishift(args):
                 "w_energy_drift": (w_energy(u[0].cpu().numpy(), Hf) / gold["w_energy_f"] - 1.0) if gold else None,
                 "ms_pass1": rep["step_ms"][0], "ms_host_small": rep["step_ms"][1], "ms_pass2": rep["step_ms"][2],
                 "tail": rep["max_rel_residual"],
-                "roofline": {"bound": "hbm", "kernel": "k_lz_step (pass 2)", "achieved": ach, "peak": HBM_PEAK_GBS,
+                "roofline": {"bound": "hbm", "kernel": "pass 2 (k_lz_gather; k_lz_step for vectors that were not kept)", "achieved": ach, "peak": HBM_PEAK_GBS,
                              "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "traffic": None,
                              "avg_launch_ms": k_ms / m, "launches": m, "alg_bytes_per_launch": k_b / m,
                              "kernel_time_share": k_ms * 1e-3 / el}}
@@ -561,22 +565,29 @@ def _fourier_case(D, fc, trho, nbumps, seed, gold_name, steps, warmup):
     P, nterm, nfreq = reps[0]["P"], reps[0]["solves"], reps[0]["total_iters"]
     nm = (D // 2 + 1) * D
     k_ms = sum(r["kernel_ms"] for r in reps) / steps
-    # the direct sums' operations; where the far terms are summed as
-    # polynomials (2048^2) fewer are done, and the rate is that of the direct
-    # sums the stage stands for
     flops = nfreq * nterm * FLOPS_PER_TERM
     achieved = flops / (k_ms * 1e-3) / 1e12
     step_ms = [sum(r["step_ms"][k] for r in reps) / steps for k in range(5)]
+    roof = {"bound": "alu", "kernel": "k_mode_coef", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS,
+            "traffic": traffic_if_current("k_mode_coef", D),
+            "avg_launch_ms": k_ms, "launches": steps, "alg_flops_per_launch": flops,
+            "waves_per_block": reps[0]["slots"], "term_splits": reps[0]["tile_rows"]}
+    if achieved > FP64_PEAK_TFLOPS:
+        # the far terms are summed as polynomials here, the direct sums'
+        # operations are not done; the largest kernel is the column pass,
+        # which moves the spectrum in and out once
+        k_ms = step_ms[3]
+        cols = reps[0]["kernel_bytes"] / (k_ms * 1e-3) / 1e9
+        roof = {"bound": "hbm", "kernel": "k_cols", "achieved": cols, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": cols / HBM_PEAK_GBS, "avg_launch_ms": k_ms, "launches": steps,
+                "alg_bytes_per_launch": reps[0]["kernel_bytes"]}
+    roof["measured_in"] = "profiled calls after the timed ones (same workload)"
+    roof["kernel_time_share"] = k_ms * steps * 1e-3 / el
     return {"D": D, "t_rho": trho, "f_c": fc, "P": P, "terms": nterm, "distinct_frequencies": nfreq,
             "half_spectrum_modes": nm, "el": el, "ms": 1000.0 * el / steps,
             "value": D * D * P / (el / steps), "rel_l2_vs_oracle": sampled_rel_l2(u, gold),
-            "roofline": {"bound": "alu", "kernel": "k_mode_coef", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
-                         "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS,
-                         "traffic": traffic_if_current("k_mode_coef", D),
-                         "avg_launch_ms": k_ms, "launches": steps, "alg_flops_per_launch": flops,
-                         "waves_per_block": reps[0]["slots"], "term_splits": reps[0]["tile_rows"],
-                         "measured_in": "profiled calls after the timed ones (same workload)",
-                         "kernel_time_share": k_ms * steps * 1e-3 / el},
+            "roofline": roof,
             "ms_by_stage": {"rows_forward_eta": step_ms[0], "rows_forward_uv": step_ms[1], "pole_sums": step_ms[2],
                             "columns": step_ms[3], "rows_inverse": step_ms[4]},
             "hbm_gbs_alg": sum(r["alg_bytes"] for r in reps) / el / 1e9}
@@ -818,23 +829,25 @@ def main():
     err = sampled_rel_l2(u, gold)
     print(f"headline: {args.steps} steps, {ms:.1f} ms/step, rel-L2 {err:.2e}", file=sys.stderr, flush=True)
 
-    def pass_roofline(precision, tol, kernel):
-        """One more apply with a HIP event pair around every launch of the
-        pass kernel (on the library's stream): algorithmic bytes per launch /
-        average launch time."""
+    def pass_roofline(precision, tol, peak):
+        """One more apply with a HIP event pair around every launch of k_chip
+        (on the library's stream), which holds the solves' vectors in
+        registers and LDS: algorithmic flops of the inner steps / its time."""
         t1 = time.perf_counter()
         up, rp = rexii.apply(fd, t, fc=FC, precision=precision, tol=tol, pole_batch=args.slots, profile=1)
         torch.cuda.synchronize()
         ep = time.perf_counter() - t1
-        k_l, k_ms, k_b = rp["kernel_launches"], rp["kernel_ms"], rp["kernel_bytes"]
-        ach = (k_b / k_l) / (k_ms / k_l * 1e-3) / 1e9
-        return up, rp, {"bound": "hbm", "kernel": kernel, "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": ach / HBM_PEAK_GBS, "traffic": traffic_if_current(kernel),
-                        "avg_launch_ms": k_ms / k_l, "launches": k_l, "alg_bytes_per_launch": k_b / k_l,
+        k_l, k_ms = rp["kernel_launches"], rp["kernel_ms"]
+        flops = rp["total_iters"] * D * D * COCG_FLOPS_PER_POINT
+        ach = flops / (k_ms * 1e-3) / 1e12
+        return up, rp, {"bound": "alu", "kernel": "k_chip", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
+                        "frac": ach / peak, "traffic": None,
+                        "avg_launch_ms": k_ms / k_l, "launches": k_l, "alg_flops_per_launch": flops / k_l,
+                        "streaming_equivalent_gbs": rp["kernel_bytes"] / (k_ms * 1e-3) / 1e9,
                         "kernel_time_share": k_ms * 1e-3 / ep, "profiled_apply_ms": 1000 * ep,
                         "measured_in": "a separate apply with per-launch HIP events (same workload)"}
 
-    up, rp, roof = pass_roofline("mixed", 1e-6, "k_pass_f32")
+    up, rp, roof = pass_roofline("mixed", 1e-6, FP32_PEAK_TFLOPS)
     alg_gbs = reps[0]["alg_bytes"] / (el / args.steps) / 1e9
     out = {
         "metric": METRIC, "value": value, "unit": "grid-pt·pole solves/s", "n_gpus": 1,
@@ -843,7 +856,7 @@ def main():
         "config": {"workload": "lrsw-fd-512x512-trho1000-16bumps", "D": D, "t_rho": TRHO, "f_c": FC,
                    "precision": "mixed (FP32 inner COCG, FP64 residual/refinement/pole sum)", "tol": 1e-6,
                    "P": P, "solves": reps[0]["solves"], "h": 0.5, "slots": reps[0]["slots"],
-                   "path": "default (HIP graph replay)"},
+                   "path": "default (inner steps on the chip)"},
         "rel_l2_vs_oracle": err,
         "err_bound": reps[0]["err_bound"],
         "hbm_gbs_alg": alg_gbs,
@@ -868,7 +881,7 @@ def main():
         torch.cuda.synchronize()
         e64 = (time.perf_counter() - t1) / n64
         e64rel = sampled_rel_l2(u, gold)
-        _, _, roof64 = pass_roofline("fp64", 1e-10, "k_pass_f64")
+        _, _, roof64 = pass_roofline("fp64", 1e-10, FP64_PEAK_TFLOPS)
         out["fp64"] = {"value": D * D * r64s[0]["P"] / e64, "ms": 1000 * e64, "steps": n64, "P": r64s[0]["P"],
                        "rel_l2_vs_oracle": e64rel, "err_bound": r64s[0]["err_bound"],
                        "total_iters": r64s[0]["total_iters"], "max_iters": r64s[0]["max_iters"],

@@ -7,7 +7,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librexii.so")
 
-SOURCES = ["coeffs.cpp", "kernels.hip", "kernels_chip.hip", "kernels_vh.hip", "kernels_fft.hip", "kernels_fft2d.hip", "kernels_lz.hip", "circulant.hip", "precond.hip", "solver.hip"]
+# kernels.hip includes kernels_chip.hip, kernels_fft.hip includes kernels_fft2d.hip
+SOURCES = ["coeffs.cpp", "kernels.hip", "kernels_vh.hip", "kernels_fft.hip", "kernels_lz.hip", "circulant.hip", "precond.hip", "solver.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed-FP32 instructions in device code

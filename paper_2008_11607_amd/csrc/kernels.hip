@@ -1205,3 +1205,6 @@ template void launch_pass<float>(const Eng&, int, hipStream_t);
 template void launch_pass<double>(const Eng&, int, hipStream_t);
 
 }  // namespace rexii
+
+// built with this file: one translation unit
+#include "kernels_chip.hip"

@@ -772,3 +772,6 @@ rexii_status static_scratch(void** ptr) {
 }
 
 }  // namespace rexii
+
+// built with this file: one translation unit
+#include "kernels_fft2d.hip"
