@@ -9,7 +9,7 @@
 namespace rexii {
 
 constexpr unsigned long long kNoWord = ~0ull;   // a NaN pattern no sum produces
-constexpr unsigned kFormPolls = 1u << 22;
+constexpr unsigned kFormPolls = 1u << 24;
 constexpr unsigned kRunPolls = 1u << 23;
 
 __device__ __forceinline__ unsigned long long ald(const unsigned long long* p) {

@@ -3,11 +3,13 @@
 // One call of rexii_apply:
 //   1. rho and the pole set (coeffs.cpp; eq. matrixAccuracyBound);
 //   2. per-pole Helmholtz shifts and accumulation weights (kernels.h);
-//   3. solves scheduled in batches of B concurrent slots, poles sorted by
-//      their expected Krylov cost so that a batch finishes together;
-//   4. per batch: a chunk of kernels (FP64 residual/refinement step, then C
-//      inner COCG iterations) replayed from a HIP graph until every slot has
-//      converged, then FP64 weighted accumulation (Sec. 2.2, reduced sum);
+//   3. solves queued by their expected Krylov cost, the longest first, over
+//      B concurrent slots;
+//   4. a chunk of kernels (finished slots added to the FP64 pole sum and
+//      refilled, FP64 residual/refinement steps, inner iterations: on the
+//      chip where a solve fits a group of blocks, else streamed passes
+//      replayed from a HIP graph) until the queue is empty (Sec. 2.2, reduced
+//      sum);
 //   5. the output is rebuilt from the three accumulated fields.
 #include <hip/hip_runtime.h>
 
