@@ -9,8 +9,6 @@
 namespace rexii {
 
 constexpr unsigned long long kNoWord = ~0ull;   // a NaN pattern no sum produces
-constexpr unsigned kFormPolls = 1u << 24;
-constexpr unsigned kRunPolls = 1u << 23;
 
 __device__ __forceinline__ unsigned long long ald(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -129,26 +127,30 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // per XCD): a block waits only for blocks that start as soon as others leave.
 // ctl: [8 + x] tickets, then per group at kChipCtlHead + g kChipCtlGroup:
 // [0] arrivals, [1] state (0 forming, 1 ready, 2 cancelled).  Returns false
-// for a block beyond the groups and for a group that did not fill (*late).
+// for a block beyond the groups, for one of a group without work (with
+// gpx > 0 group k of XCD x works on item 8 k + x of `items`; the others do
+// not wait for each other) and for a group that did not fill (late).
 struct GroupPlace {
   int gid, rank, xcd;
 };
-__device__ __forceinline__ bool join_group(int* ctl, int G, int gpx, int* sh, GroupPlace& gp, bool& late) {
+__device__ __forceinline__ bool join_group(int* ctl, int G, int gpx, int items, const ChipWaits& waits, int* sh,
+                                           GroupPlace& gp, bool& late) {
   if (threadIdx.x == 0) {
     int x = 0;
     if (gpx > 0) asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
     x &= 7;
     const int ticket = __hip_atomic_fetch_add(&ctl[8 + x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int k = ticket / G;
-    const bool over = gpx > 0 && k >= gpx;
+    const bool over = gpx > 0 && (k >= gpx || 8 * k + x >= items);
     const int g = x * gpx + k;
     int* w = ctl + kChipCtlHead + (over ? 0 : g) * kChipCtlGroup;
-    if (!over && __hip_atomic_fetch_add(&w[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1)
+    if (!over && __hip_atomic_fetch_add(&w[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1 &&
+        g != waits.late_group)
       atomicCAS(&w[1], 0, 1);
     unsigned n = 0;
     int st = 2, lt = 0;
     while (!over && (st = ldc(&w[1])) == 0) {
-      if (++n > kFormPolls && atomicCAS(&w[1], 0, 2) == 0) lt = 1;
+      if (++n > waits.form_polls && atomicCAS(&w[1], 0, 2) == 0) lt = 1;
       __builtin_amdgcn_s_sleep(2);
     }
     sh[0] = st;

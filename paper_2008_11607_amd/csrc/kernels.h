@@ -204,6 +204,20 @@ constexpr int kChipCtlGroup = 32;  // control words per group
 constexpr int chip_pitch(int rt) { return rt | 1; }  // LDS places of an item's rows
 constexpr int kChipMaxLds = 152 * 1024;
 constexpr int kChipMaxG = 64;      // largest group timed
+// How the blocks of a launch wait for each other.  $REXII_CHIP_WAITS =
+// form_polls,run_polls,late_group,late_from overrides it (tests of what follows a wait
+// that ends without its condition: every block still leaves the kernel).
+struct ChipWaits {
+  unsigned form_polls;   // polls of a block for its group to fill
+  unsigned run_polls;    // polls for a word of a running group
+  int late_group;        // a group that never fills, or -1
+  int late_from;         // ... in the launches of a call from this one on
+  ChipWaits at(int launch) const {
+    ChipWaits w = *this;
+    if (launch < late_from) w.late_group = -1;
+    return w;
+  }
+};
 struct Chip {
   int nx, ny;        // the slots' common grid
   int nch, L;        // chains of rows y, y + 2, ... and their length
@@ -214,6 +228,7 @@ struct Chip {
   int variant;       // index of the kernel (chip_variants)
   int ctl_words;
   int gpx;           // groups per XCD (a group then lies on one), or 0
+  ChipWaits waits;
   unsigned long long* rec;  // [ngroups][3][G][kChipRec] partial sums
   void* ring;               // [ngroups][3][G][2][nx] edge rows of q
   int* ctl;                 // [ctl_words], zero before each launch (k_assign)

@@ -43,6 +43,8 @@
 // wait only for blocks that start as soon as others leave), and every wait
 // counts its polls and gives up past a limit, a group that has not started
 // by cancelling itself (its slots run in the next launch).
+#include <climits>
+
 #include "kernels.h"
 #include "chip_sync.h"
 
@@ -123,7 +125,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
   if (G > 1) {
     GroupPlace gp;
     bool late = false;
-    if (!join_group(c.ctl, G, c.gpx, reinterpret_cast<int*>(red), gp, late)) {
+    if (!join_group(c.ctl, G, c.gpx, INT_MAX, c.waits, reinterpret_cast<int*>(red), gp, late)) {
       if (late && tid == 0) e.counter[2] = 2;
       return;
     }
@@ -198,7 +200,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
         unsigned n = 0;
         unsigned long long w;
         while (unsigned((w = ald(reinterpret_cast<unsigned long long*>(gc + 4))) >> 32) != seq + 1) {
-          if (++n > kRunPolls) {
+          if (++n > c.waits.run_polls) {
             ctl.bad = 1;
             break;
           }
@@ -394,7 +396,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
 #pragma unroll
               for (int u = 0; u < 8; ++u) have = have && w[u] != kNoWord;
               if (__all(have)) break;
-              if (++n > kRunPolls) {
+              if (++n > c.waits.run_polls) {
                 ctl.bad = 1;
                 break;
               }
@@ -441,14 +443,14 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
           unsigned n = 0;
           while (rtop[j] && !there(qt[j])) {
             qt[j] = take(rup + col[j]);
-            if (++n > kRunPolls) {
+            if (++n > c.waits.run_polls) {
               ctl.bad = 1;
               break;
             }
           }
           while (rbot[j] && !there(qb[j])) {
             qb[j] = take(rdn + col[j]);
-            if (++n > kRunPolls) {
+            if (++n > c.waits.run_polls) {
               ctl.bad = 1;
               break;
             }
@@ -549,7 +551,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       __hip_atomic_fetch_add(&gc[2], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned n = 0;
       while (ldc(&gc[2]) < G) {
-        if (++n > kRunPolls) {
+        if (++n > c.waits.run_polls) {
           e.counter[2] = 1;
           break;
         }

@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include "kernels.h"
+
 namespace rexii {
 
 // Two poles z, -conj(z) of a term with their weights.
@@ -22,6 +24,7 @@ struct LzChip {
   int G, Sc, nt, rt, lds;   // blocks a state, runs a column, threads, rows a run, LDS bytes
   int gpx, rec_stride;      // groups per XCD (a state then lies on one) or 0; words between records
   int groups, ctl_words;
+  ChipWaits waits;
   int j0, steps;            // first step (1-based) and their number
   int kept, ldb;            // vectors kept in memory (place of buf_j: see run_multishift), row of beta
   size_t stride;            // doubles between states

@@ -187,7 +187,8 @@ __global__ __launch_bounds__(kLzNT) void k_lz_norm(const double* __restrict__ pa
 // RT - 1) rows with buf_j and buf_{j-1} (and the depth) in registers; LDS
 // holds eta and H u for the east and west neighbours and the runs' edge rows
 // of H v.  A launch runs `steps` steps from the vectors in memory; a step
-// writes buf_{j+1} there (the basis), posts eta and H v of the strip's edge
+// writes buf_{j+1} there (the basis: only steps whose vector is kept run here,
+// so the two vectors a launch starts from outlive it), posts eta and H v of the strip's edge
 // rows and one partial norm, and waits once for the other blocks, as the
 // chip COCG kernel does.  Four mailbox buffers: the words of sync i are
 // emptied after sync i + 1 and known to be gone at the end of i + 2, before
@@ -213,14 +214,13 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
   if (G > 1) {
     GroupPlace gp;
     bool late = false;
-    if (!join_group(c.ctl, G, c.gpx, sh, gp, late)) {
+    if (!join_group(c.ctl, G, c.gpx, c.nrhs, c.waits, sh, gp, late)) {
       if (late && tid == 0) c.flag[0] = 2;
       return;
     }
     gid = gp.gid;
     rank = gp.rank;
     st = local ? (gid - gp.xcd * c.gpx) * 8 + gp.xcd : gid;
-    if (st >= c.nrhs) return;
   }
   const size_t n = size_t(nx) * ny, n3 = 3 * n;
   double* vec = c.vecs + size_t(st) * c.stride;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
           unsigned long long w;
           unsigned k = 0;
           while (!__all((w = ald(th)) != kNoWord)) {
-            if (++k > kRunPolls) {
+            if (++k > c.waits.run_polls) {
               sh[5] = 1;
               break;
             }
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       if (rtop) {
         unsigned long long a, b;
         while ((a = ald(rup)) == kNoWord || (b = ald(rup + nx)) == kNoWord) {
-          if (++k > kRunPolls) {
+          if (++k > c.waits.run_polls) {
             sh[5] = 1;
             break;
           }
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       if (rbot) {
         unsigned long long a, b;
         while ((a = ald(rdn)) == kNoWord || (b = ald(rdn + nx)) == kNoWord) {
-          if (++k > kRunPolls) {
+          if (++k > c.waits.run_polls) {
             sh[5] = 1;
             break;
           }
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       __hip_atomic_fetch_add(&gc[2], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned k = 0;
       while (ldc(&gc[2]) < G) {
-        if (++k > kRunPolls) {
+        if (++k > c.waits.run_polls) {
           c.flag[0] = 1;
           break;
         }

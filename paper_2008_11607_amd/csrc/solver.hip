@@ -778,6 +778,14 @@ static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* 
   return true;
 }
 
+// Limits of the waits: seconds, for blocks that start late or wait for words.
+static ChipWaits chip_waits() {
+  ChipWaits w{1u << 24, 1u << 23, -1, 0};
+  if (const char* v = std::getenv("REXII_CHIP_WAITS"))
+    (void)std::sscanf(v, "%u,%u,%d,%d", &w.form_polls, &w.run_polls, &w.late_group, &w.late_from);
+  return w;
+}
+
 struct Engine {
   hipStream_t st;
   EngineSize z;
@@ -785,6 +793,8 @@ struct Engine {
   bool profile = false;
   Eng e{};
   Chip chip{};             // the chip kernel's launch (e.chip_words > 0)
+  ChipWaits waits{};
+  int chip_launches = 0;
   int* hcount = nullptr;   // pinned host mirror of the counters
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
@@ -979,6 +989,7 @@ struct Engine {
     c.rec = static_cast<unsigned long long*>(e.p1);
     c.ctl = reinterpret_cast<int*>(static_cast<char*>(e.p1) + rec);
     c.ring = e.r1;
+    waits = chip_waits();
     chip = c;
     e.chip_ctl = c.ctl;
     e.chip_words = c.ctl_words;
@@ -999,6 +1010,7 @@ struct Engine {
         launch_pass_scalars(e, st);
       }
       if (with_events) HIPCHK(hipEventRecord(evs[0], st));
+      chip.waits = waits.at(chip_launches++);
       launch_chip(e, chip, st);
       if (with_events) HIPCHK(hipEventRecord(evs[1], st));
     }
@@ -3187,6 +3199,8 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     int m = 0, launched = 0, next_check = 0;
     bool done = false, hit_max = false;
     double host_s = 0.0, rho_seen = 0.0;
+    const ChipWaits waits = chip_waits();
+    int chip_launches = 0;
     if (on_chip) {
       chip.kept = kept;
       chip.ldb = ldb;
@@ -3200,12 +3214,17 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       chip.flag = flag;
     }
     auto enqueue = [&](int upto) {
-      if (on_chip && upto > launched) {
+      // on the chip: step j writes buf_{j+1}, in a place of its own while
+      // j < kept.  Later vectors lie in two places in turn: buf_m and
+      // buf_{m+1} would be gone when a group that did not form has to repeat
+      // the steps from m, so those steps are launched one by one.
+      const int last = on_chip ? std::min(upto, kept - 1) : 0;
+      if (last > launched) {
         chip.j0 = launched + 1;
-        chip.steps = upto - launched;
+        chip.steps = last - launched;
+        chip.waits = waits.at(chip_launches++);
         launch_lz_chip(chip, st);
-        launched = upto;
-        return;
+        launched = last;
       }
       for (int j = launched + 1; j <= upto; ++j)
         launch_lz_step(place(j), place(std::max(j - 1, 1)), place(j + 1), stride, Hf, H0, g, fc, nx, ny, nrhs, j, beta,

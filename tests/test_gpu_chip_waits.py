@@ -1,0 +1,64 @@
+"""What follows a wait of the on-chip kernels that ends without its condition:
+REXII_CHIP_WAITS makes one group of blocks never fill, or a wait give up at
+its first look; every block leaves the kernel, the host goes on another way."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2008_11607_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rx():
+    from paper_2008_11607_amd import rexii
+    rexii.load()
+    return rexii
+
+
+def _multishift(rx, f, t, ws):
+    lib = rx.load()
+    nrhs, ny, nx = f.shape[0], f.shape[2], f.shape[3]
+    op, o, rep, u = rx.make_op(nx, ny), rx.make_opts(), rx.Report(), torch.full_like(f, float("nan"))
+    st = lib.rexii_apply_multishift(ctypes.byref(op), nrhs, ctypes.c_void_p(f.data_ptr()), ctypes.c_void_p(u.data_ptr()),
+                                    float(t), ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), ws.numel(), rx._stream(),
+                                    ctypes.byref(rep))
+    torch.cuda.synchronize()
+    return st, u, rep.as_dict()
+
+
+def _multishift_case(rx, nx, ny, nrhs, kept):
+    """States, time, and workspaces that keep every vector and `kept` of them."""
+    # smooth states: the coefficients of the first steps are small beside those
+    # of the hundreds that follow
+    f = torch.stack([torch.from_numpy(inputs.gaussian_bumps(nx, ny, nbumps=2, seed=40 + r)) for r in range(nrhs)]).cuda()
+    t = 600.0 / rx.rho(nx, ny)
+    lib, op, o, nb = rx.load(), rx.make_op(nx, ny), rx.make_opts(), ctypes.c_size_t()
+    assert lib.rexii_multishift_basis_size(ctypes.byref(op), nrhs, float(t), ctypes.byref(o), ctypes.byref(nb)) == 0
+    bound = (nx * nx + ny * ny) ** 0.5 + 10.0          # of rho, as the library sizes by it
+    all_kept = int(1.35 * t * bound + 128)
+    few = (nb.value - (all_kept - kept) * nrhs * f[0].numel() * 8) // 256 * 256
+    return f, t, [torch.empty(n, dtype=torch.uint8, device="cuda") for n in (nb.value, few)]
+
+
+@pytest.mark.parametrize("late,start", [(0, 0), (0, 1), (1, 1), (2, 1), (5, 1)])
+@pytest.mark.parametrize("nx,ny,nrhs,kept", [(96, 72, 1, 6), (130, 66, 3, 6), (130, 66, 3, 40), (256, 192, 2, 11)])
+def test_lanczos_group_that_never_fills(rx, monkeypatch, nx, ny, nrhs, kept, late, start):
+    """Steps that a group missed are repeated by single launches, beside states
+    whose group ran them and with vectors beyond the kept ones.  The recurrence
+    is the same in FP64: 1e-12 for several hundred terms of 1e-16.  (From other
+    vectors than its own a step's coefficient is off by a factor, and the
+    product of hundreds of them scales the vectors formed again.)"""
+    f, t, (ws, few) = _multishift_case(rx, nx, ny, nrhs, kept)
+    st, ref, r0 = _multishift(rx, f, t, ws)
+    assert st == 0
+    monkeypatch.setenv("REXII_CHIP_WAITS", f"2000,{1 << 23},{late},{start}")
+    for w in (ws, few):
+        w.fill_(0xFF)                                  # NaN in every place not written
+        st, u, rep = _multishift(rx, f, t, w)
+        assert st == 0, rx.last_error()
+        assert rep["solves"] == r0["solves"]
+        for r in range(nrhs):
+            assert float((u[r] - ref[r]).norm() / ref[r].norm()) <= 1e-12, r
