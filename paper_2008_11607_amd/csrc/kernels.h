@@ -172,7 +172,7 @@ struct Eng {
                          // [1] their common tile count (0 if they differ;
                          // bit 30 set when every slot works, so the list is
                          // 0, 1, ..., B-1), [2..] working slot indices
-  int* counter;          // [4] host-visible counts ([2]: a chip group gave up)
+  int* counter;          // [4] host-visible counts ([2]: kChipGaveUp, kChipLate)
   int2* items;           // [B * (cap_blk + 7)] (slot, tile): 8 band lists when tile counts differ
                          // (filled when the working slots' tile counts differ)
   double* part;          // [B][cap_blk][kNDots]
@@ -204,6 +204,9 @@ constexpr int kChipCtlGroup = 32;  // control words per group
 constexpr int chip_pitch(int rt) { return rt | 1; }  // LDS places of an item's rows
 constexpr int kChipMaxLds = 152 * 1024;
 constexpr int kChipMaxG = 64;      // largest group timed
+// Outcomes of a launch, bits of one word that is cleared before it.
+constexpr int kChipGaveUp = 1;     // a wait inside a running group gave up: an error, its mailboxes are not empty
+constexpr int kChipLate = 2;       // a group did not form: its work is still to be done
 // How the blocks of a launch wait for each other.  $REXII_CHIP_WAITS =
 // form_polls,run_polls,late_group,late_from overrides it (tests of what follows a wait
 // that ends without its condition: every block still leaves the kernel).

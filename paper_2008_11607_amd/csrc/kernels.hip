@@ -950,6 +950,7 @@ __global__ __launch_bounds__(kSchedNT) void k_assign(Eng e) {
     *e.next = next;
     e.counter[0] = working + (next < e.S ? 1 : 0);
     e.counter[1] = next;
+    e.counter[2] = 0;
   }
   if (uniform > 0) return;
   // band lists: list x holds band x of every working slot in slot order

@@ -126,7 +126,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
     GroupPlace gp;
     bool late = false;
     if (!join_group(c.ctl, G, c.gpx, INT_MAX, c.waits, reinterpret_cast<int*>(red), gp, late)) {
-      if (late && tid == 0) e.counter[2] = 2;
+      if (late && tid == 0) atomicOr(&e.counter[2], kChipLate);
       return;
     }
     gid = gp.gid;
@@ -212,7 +212,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
     __syncthreads();
     const int slot = uni(ctl.slot);
     if (uni(ctl.bad) != 0) {
-      if (tid == 0) e.counter[2] = 1;
+      if (tid == 0) atomicOr(&e.counter[2], kChipGaveUp);
       return;
     }
     if (slot < 0) break;
@@ -510,7 +510,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       __syncthreads();
     }
     if (act == 2) {
-      if (tid == 0) e.counter[2] = 1;
+      if (tid == 0) atomicOr(&e.counter[2], kChipGaveUp);
       return;
     }
     // ---- back to memory: d, and r and p if the inner solve goes on
@@ -552,7 +552,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       unsigned n = 0;
       while (ldc(&gc[2]) < G) {
         if (++n > c.waits.run_polls) {
-          e.counter[2] = 1;
+          atomicOr(&e.counter[2], kChipGaveUp);
           break;
         }
       }

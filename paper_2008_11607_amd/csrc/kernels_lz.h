@@ -35,7 +35,7 @@ struct LzChip {
   unsigned long long* rec;
   unsigned long long* ring;
   int* ctl;
-  int* flag;                // 1: a wait passed its limit, 2: a group did not form
+  int* flag;                // kChipGaveUp, kChipLate
 };
 bool lz_chip_config(int nx, int ny, int nrhs, bool depth, int cus, LzChip* c);
 size_t lz_chip_bytes(const LzChip& c);

@@ -215,7 +215,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
     GroupPlace gp;
     bool late = false;
     if (!join_group(c.ctl, G, c.gpx, c.nrhs, c.waits, sh, gp, late)) {
-      if (late && tid == 0) c.flag[0] = 2;
+      if (late && tid == 0) atomicOr(c.flag, kChipLate);
       return;
     }
     gid = gp.gid;
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
     step(B, A, c.j0 + k + 1);
   }
   if (bad) {
-    if (tid == 0) c.flag[0] = 1;
+    if (tid == 0) atomicOr(c.flag, kChipGaveUp);
     return;
   }
   // ---- the mailboxes empty for the next launch
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       unsigned k = 0;
       while (ldc(&gc[2]) < G) {
         if (++k > c.waits.run_polls) {
-          c.flag[0] = 1;
+          atomicOr(c.flag, kChipGaveUp);
           break;
         }
       }

@@ -1156,9 +1156,9 @@ struct Engine {
           enqueue_chunk<T>(false);
         HIPCHK(hipStreamSynchronize(st));
       }
-      if (hcount[2] == 1) throw HipError{REXII_ERR_HIP, "a block of the chip kernel waited past its limit"};
+      if (hcount[2] & kChipGaveUp) throw HipError{REXII_ERR_HIP, "a block of the chip kernel waited past its limit"};
       // an XCD had fewer blocks than its groups need: groups of any blocks
-      if (hcount[2] == 2) chip.gpx = 0;
+      if (hcount[2] & kChipLate) chip.gpx = 0;
       if (hcount[0] == 0) break;
       if (every > 0.0) {
         const auto now = std::chrono::steady_clock::now();
@@ -3273,7 +3273,7 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       if (on_chip) HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
       read_beta(m + 1, launched);
       if (on_chip && *hflag != 0) {
-        if (*hflag == 1) throw HipError{REXII_ERR_HIP, "a block of the Lanczos kernel waited past its limit"};
+        if (*hflag & kChipGaveUp) throw HipError{REXII_ERR_HIP, "a block of the Lanczos kernel waited past its limit"};
         // a group of blocks did not come together: these steps once more, one launch each
         on_chip = false;
         launched = m;

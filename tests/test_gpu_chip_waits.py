@@ -62,3 +62,23 @@ def test_lanczos_group_that_never_fills(rx, monkeypatch, nx, ny, nrhs, kept, lat
         assert rep["solves"] == r0["solves"]
         for r in range(nrhs):
             assert float((u[r] - ref[r]).norm() / ref[r].norm()) <= 1e-12, r
+
+
+def test_a_wait_that_gave_up_is_an_error(rx, monkeypatch):
+    """... also where a late group reports after it (2000 polls against one),
+    and the next call is a right one."""
+    f, t, (ws, _) = _multishift_case(rx, 130, 66, 3, 6)
+    g = f[0, :, :64, :96].contiguous()
+    u0 = rx.apply(g, 0.1, pole_batch=64)[0]
+    st, m0, _ = _multishift(rx, f, t, ws)
+    assert st == 0
+    with monkeypatch.context() as m:
+        m.setenv("REXII_CHIP_WAITS", "2000,0,0,0")
+        st, _, _ = _multishift(rx, f, t, ws)
+        assert st == -6 and "past its limit" in rx.last_error()
+        with pytest.raises(rx.RexiiError) as e:
+            rx.apply(g, 0.1, pole_batch=64)
+        assert e.value.status == -6 and "past its limit" in str(e.value)
+    st, m1, _ = _multishift(rx, f, t, ws)
+    assert st == 0 and bool((m0 == m1).all())
+    assert bool((rx.apply(g, 0.1, pole_batch=64)[0] == u0).all())
