@@ -124,7 +124,10 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 
 // A block's place among the groups of a launch.  Groups fill in the order in
 // which blocks start (of any XCD, or with gpx > 0 of one XCD each, gpx groups
-// per XCD): a block waits only for blocks that start as soon as others leave.
+// per XCD): a block waits only for blocks that start as soon as others leave,
+// provided that no other launch of this kind holds CUs (the host gives such
+// launches of a process one after the other; against another process the
+// limit of the wait helps).
 // ctl: [8 + x] tickets, then per group at kChipCtlHead + g kChipCtlGroup:
 // [0] arrivals, [1] state (0 forming, 1 ready, 2 cancelled).  Returns false
 // for a block beyond the groups, for one of a group without work (with

@@ -39,10 +39,10 @@
 // nobody looks for the words of i + 3 before it has the record of i + 2.
 //
 // Waits end: a group starts only when all its blocks are on the chip (its
-// members are taken in the order in which blocks start, so blocks of a group
-// wait only for blocks that start as soon as others leave), and every wait
-// counts its polls and gives up past a limit, a group that has not started
-// by cancelling itself (its slots run in the next launch).
+// members are taken in the order in which blocks start, and no other launch
+// of this kind runs beside it), and every wait counts its polls and gives up
+// past a limit, a group that has not started by cancelling itself (its slots
+// run in the next launch).
 #include <climits>
 
 #include "kernels.h"

@@ -17,6 +17,7 @@
 #include <chrono>
 #include <cmath>
 #include <complex>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -115,6 +116,10 @@ static inline size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 // ---------------------------------------------------------------------------
 struct DevCtx {
   std::mutex mu;
+  // turns of the launches whose blocks wait for each other (ChipTurn)
+  std::mutex turn_mu;
+  std::condition_variable turn_cv;
+  uint64_t turn_next = 0, turn_now = 0;
   hipStream_t st = nullptr;
   hipEvent_t ev = nullptr;
   void* pin = nullptr;         // staging of device-to-host reads
@@ -158,6 +163,42 @@ struct CtxHold {
     tl_ctx = prev;
     c->mu.unlock();
   }
+};
+
+// A launch whose blocks wait for each other (k_chip, k_lz_chip) has the
+// device's only turn until its stream has been drained: of two such launches
+// at once each could hold a part of the CUs that a group needs, and neither
+// would go on.  Each fills the chip, so calls that overlap lose nothing by
+// it.  Turns are given in the order in which they are asked for.  A thread
+// that waits here holds no other thread up: its own launches before this one
+// end by themselves.
+class ChipTurn {
+ public:
+  ChipTurn() = default;
+  ChipTurn(const ChipTurn&) = delete;
+  ChipTurn& operator=(const ChipTurn&) = delete;
+  ~ChipTurn() { give(); }
+  void take() {
+    if (c_) return;
+    DevCtx* c = device_ctx();
+    if (!c) return;
+    std::unique_lock<std::mutex> lk(c->turn_mu);
+    const uint64_t mine = c->turn_next++;
+    c->turn_cv.wait(lk, [&] { return c->turn_now == mine; });
+    c_ = c;
+  }
+  void give() {
+    if (!c_) return;
+    {
+      std::lock_guard<std::mutex> lk(c_->turn_mu);
+      ++c_->turn_now;
+    }
+    c_->turn_cv.notify_all();
+    c_ = nullptr;
+  }
+
+ private:
+  DevCtx* c_ = nullptr;
 };
 
 // Pinned host memory of at least `bytes` from the held set (grown on
@@ -778,9 +819,13 @@ static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* 
   return true;
 }
 
-// Limits of the waits: seconds, for blocks that start late or wait for words.
+// Limits of the waits, in polls of at least half a microsecond.  A group's
+// blocks start as soon as blocks of other kernels leave the CUs, so 20 ms
+// (other processes' launches may hold them for longer: the group's work is
+// then left for the next launch); a word of a running group is microseconds
+// away, its limit of seconds only ends what cannot go on.
 static ChipWaits chip_waits() {
-  ChipWaits w{1u << 24, 1u << 23, -1, 0};
+  ChipWaits w{1u << 15, 1u << 23, -1, 0};
   if (const char* v = std::getenv("REXII_CHIP_WAITS"))
     (void)std::sscanf(v, "%u,%u,%d,%d", &w.form_polls, &w.run_polls, &w.late_group, &w.late_from);
   return w;
@@ -794,6 +839,7 @@ struct Engine {
   Eng e{};
   Chip chip{};             // the chip kernel's launch (e.chip_words > 0)
   ChipWaits waits{};
+  ChipTurn turn;
   int chip_launches = 0;
   int* hcount = nullptr;   // pinned host mirror of the counters
   hipGraphExec_t gexec = nullptr;
@@ -1011,6 +1057,7 @@ struct Engine {
       }
       if (with_events) HIPCHK(hipEventRecord(evs[0], st));
       chip.waits = waits.at(chip_launches++);
+      turn.take();
       launch_chip(e, chip, st);
       if (with_events) HIPCHK(hipEventRecord(evs[1], st));
     }
@@ -1133,6 +1180,7 @@ struct Engine {
       if (profile) {
         enqueue_chunk<T>(true);
         HIPCHK(hipStreamSynchronize(st));
+        turn.give();
         const int steps = e.chip_words > 0 ? 1 : chunk;
         for (int i = 0; i < steps; ++i) {
           float ms = 0.f;
@@ -1155,6 +1203,7 @@ struct Engine {
         else
           enqueue_chunk<T>(false);
         HIPCHK(hipStreamSynchronize(st));
+        turn.give();
       }
       if (hcount[2] & kChipGaveUp) throw HipError{REXII_ERR_HIP, "a block of the chip kernel waited past its limit"};
       // an XCD had fewer blocks than its groups need: groups of any blocks
@@ -3201,6 +3250,7 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
     double host_s = 0.0, rho_seen = 0.0;
     const ChipWaits waits = chip_waits();
     int chip_launches = 0;
+    ChipTurn turn;
     if (on_chip) {
       chip.kept = kept;
       chip.ldb = ldb;
@@ -3223,6 +3273,9 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
         chip.j0 = launched + 1;
         chip.steps = last - launched;
         chip.waits = waits.at(chip_launches++);
+        // groups past those that fit wait for a whole launch of the others
+        chip.waits.form_polls += 64u * unsigned(chip.steps);
+        turn.take();
         launch_lz_chip(chip, st);
         launched = last;
       }
@@ -3272,6 +3325,7 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       HIPCHK(hipGetLastError());
       if (on_chip) HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
       read_beta(m + 1, launched);
+      turn.give();
       if (on_chip && *hflag != 0) {
         if (*hflag & kChipGaveUp) throw HipError{REXII_ERR_HIP, "a block of the Lanczos kernel waited past its limit"};
         // a group of blocks did not come together: these steps once more, one launch each
