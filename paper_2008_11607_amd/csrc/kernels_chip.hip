@@ -537,6 +537,7 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       Z->it_total = itt0 + steps;
       Z->alpha = make_double2(al64.x * icx, al64.y * icx);
       Z->beta = be64;
+      Z->dcp = Z->alpha;   // should the passes take the next step: d += alpha p
       if (steps > 0) Z->rr = rr64;
       if (act == 1) Z->status = kInnerDone;
     }

@@ -1160,7 +1160,8 @@ struct Engine {
     }
     // a chunk of the chip path is seven launches, enqueued faster than they
     // run: no graph
-    const bool graphed = !profile && e.chip_words == 0;
+    bool graphed = !profile && e.chip_words == 0;
+    int late = 0;
     if (profile) {
       evs.resize((z.method == 1 ? kBcgEvents : 2) * chunk);
       for (hipEvent_t& ev : evs) HIPCHK(hipEventCreate(&ev));
@@ -1206,8 +1207,21 @@ struct Engine {
         turn.give();
       }
       if (hcount[2] & kChipGaveUp) throw HipError{REXII_ERR_HIP, "a block of the chip kernel waited past its limit"};
-      // an XCD had fewer blocks than its groups need: groups of any blocks
-      if (hcount[2] & kChipLate) chip.gpx = 0;
+      // an XCD had fewer blocks than its groups need: groups of any blocks;
+      // neither come together (something else holds CUs, or the stream has
+      // too few of them): the passes take over, from the slots as they are
+      late = (hcount[2] & kChipLate) ? late + 1 : 0;
+      if (late > 0) {
+        chip.gpx = 0;
+        if (late == 2) {
+          e.chip_ctl = nullptr;
+          e.chip_words = 0;
+          if (!profile) {
+            build_graph<T>();
+            graphed = true;
+          }
+        }
+      }
       if (hcount[0] == 0) break;
       if (every > 0.0) {
         const auto now = std::chrono::steady_clock::now();

@@ -6,6 +6,8 @@ import ctypes
 import pytest
 import torch
 
+from oracle import expm_modes as em
+from oracle import lrsw
 from paper_2008_11607_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -82,3 +84,18 @@ def test_a_wait_that_gave_up_is_an_error(rx, monkeypatch):
     st, m1, _ = _multishift(rx, f, t, ws)
     assert st == 0 and bool((m0 == m1).all())
     assert bool((rx.apply(g, 0.1, pole_batch=64)[0] == u0).all())
+
+
+@pytest.mark.parametrize("late,start,slots,nx,ny,vel,prof", [(0, 0, 1, 128, 96, False, 0), (0, 1, 1, 75, 101, False, 1),
+                                                             (0, 1, 8, 75, 101, True, 0), (3, 0, 64, 128, 96, True, 1)])
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-10), ("mixed", 1e-6)])
+def test_cocg_group_that_never_fills(rx, monkeypatch, precision, bar, late, start, slots, nx, ny, vel, prof):
+    """Other groups take the late one's slots; with one group only, or groups
+    late for good, the passes take over (start 1: in the middle of a solve).
+    Bars: the targets of the two precisions against the exact exponential."""
+    op = lrsw.LRSW(nx, ny, fc=10.0)
+    fh, t = inputs.gaussian_bumps(nx, ny, nbumps=3, seed=50, velocity=vel), 150.0 / lrsw.rho(op)
+    monkeypatch.setenv("REXII_CHIP_WAITS", f"2000,{1 << 23},{late},{start}")
+    u, rep = rx.apply(torch.from_numpy(fh).cuda(), t, precision=precision, pole_batch=slots, profile=prof)
+    assert rep["not_converged"] == 0 and rep["slots"] == slots and rep["max_iters"] > 256
+    assert em.rel_l2(u.cpu().numpy(), em.expm_closed_real(op, fh, t)) <= bar
