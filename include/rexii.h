@@ -420,8 +420,11 @@ rexii_status rexii_apply_fourier_noalloc(const rexii_swe_op* op, const double* f
  *   Workspace: at least rexii_multishift_workspace_size() bytes (no vector is
  *     kept: every step runs twice), better rexii_multishift_basis_size() (the
  *     vectors and the small problem to expect for this t, at most 32 GiB of
- *     vectors; a depth field is read on the null stream), or NULL (as the
- *     least).  Any size between keeps what fits.
+ *     vectors), or NULL (as the least).  Any size between keeps what fits.
+ *     rexii_multishift_basis_size_on() reads a depth field on `stream`, in
+ *     order with the work that forms it there; rexii_multishift_basis_size()
+ *     reads it on the null stream, with which streams created as
+ *     non-blocking do not synchronise.
  *   Report: solves = max_iters = m, total_iters = sum of m over states,
  *     P, M, N for the largest small problem, rho = its Gershgorin bound,
  *     max_rel_residual = largest tail ratio, alg_bytes = algorithmic HBM
@@ -434,6 +437,8 @@ rexii_status rexii_multishift_workspace_size(const rexii_swe_op* op, int32_t nrh
                                              size_t* bytes);
 rexii_status rexii_multishift_basis_size(const rexii_swe_op* op, int32_t nrhs, double t, const rexii_opts* opts,
                                          size_t* bytes);
+rexii_status rexii_multishift_basis_size_on(const rexii_swe_op* op, int32_t nrhs, double t, const rexii_opts* opts,
+                                            hipStream_t stream, size_t* bytes);
 
 rexii_status rexii_apply_multishift(const rexii_swe_op* op, int32_t nrhs, const double* f, double* u, double t,
                                     const rexii_opts* opts, void* workspace, size_t ws_bytes,

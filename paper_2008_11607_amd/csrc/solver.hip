@@ -3546,6 +3546,11 @@ rexii_status rexii_multishift_workspace_size(const rexii_swe_op* op, int32_t nrh
 
 rexii_status rexii_multishift_basis_size(const rexii_swe_op* op, int32_t nrhs, double t, const rexii_opts* opts,
                                          size_t* bytes) {
+  return rexii_multishift_basis_size_on(op, nrhs, t, opts, nullptr, bytes);
+}
+
+rexii_status rexii_multishift_basis_size_on(const rexii_swe_op* op, int32_t nrhs, double t, const rexii_opts* opts,
+                                            hipStream_t stream, size_t* bytes) {
   rexii_status v = check_op_and_t(op, t, true);
   if (v != REXII_OK) return v;
   if (!bytes || nrhs <= 0) return set_error(REXII_ERR_INVALID_ARG, "need bytes and nrhs > 0");
@@ -3554,7 +3559,7 @@ rexii_status rexii_multishift_basis_size(const rexii_swe_op* op, int32_t nrhs, d
     double hs = op->H0;
     if (op->H_field) {
       CtxHold hold;
-      hs = device_hmax(op->H_field, size_t(op->nx) * op->ny, nullptr);
+      hs = device_hmax(op->H_field, size_t(op->nx) * op->ny, stream);
     }
     const double rho = std::sqrt(op->g * hs) * std::sqrt(double(op->nx) * op->nx + double(op->ny) * op->ny) +
                        std::fabs(op->f_cor);

@@ -69,6 +69,7 @@ EXPORTS = ["rexii_default_opts", "rexii_coeffs", "rexii_rho", "rexii_workspace_s
            "rexii_apply", "rexii_apply_adjoint", "rexii_apply_batched", "rexii_batched_workspace_size",
            "rexii_shifted_solve", "rexii_apply_fourier", "rexii_fourier_workspace_size",
            "rexii_apply_multishift", "rexii_multishift_workspace_size", "rexii_multishift_basis_size",
+           "rexii_multishift_basis_size_on",
            "rexii_coeffs_rexi",
            "rexii_apply_fourier_noalloc", "rexii_apply_circulant", "rexii_circulant_workspace_size",
            "rexii_fit_gaussian", "rexii_last_error"]
@@ -118,6 +119,8 @@ def load():
     lib.rexii_multishift_workspace_size.restype = ctypes.c_int
     lib.rexii_multishift_basis_size.argtypes = [P(SweOp), i32, dbl, P(Opts), P(sz)]
     lib.rexii_multishift_basis_size.restype = ctypes.c_int
+    lib.rexii_multishift_basis_size_on.argtypes = [P(SweOp), i32, dbl, P(Opts), vp, P(sz)]
+    lib.rexii_multishift_basis_size_on.restype = ctypes.c_int
     lib.rexii_circulant_workspace_size.argtypes = [i32, i32, vp, vp, i32, dbl, dbl, i32, i32, P(Opts), P(sz)]
     lib.rexii_circulant_workspace_size.restype = ctypes.c_int
     lib.rexii_apply_circulant.argtypes = [i32, i32, vp, vp, i32, vp, vp, dbl, dbl, i32, i32, P(Opts), vp, sz, vp,
@@ -388,7 +391,8 @@ def apply_multishift(f, t, g=1.0, fc=10.0, H=1.0, Hfield=None, out=None, **opts)
     o = make_opts(**opts)
     rep = Report()
     nb = ctypes.c_size_t()
-    _check(lib.rexii_multishift_basis_size(ctypes.byref(op), int(nrhs), float(t), ctypes.byref(o), ctypes.byref(nb)))
+    _check(lib.rexii_multishift_basis_size_on(ctypes.byref(op), int(nrhs), float(t), ctypes.byref(o), _stream(),
+                                              ctypes.byref(nb)))
     ws = torch.empty(nb.value, dtype=torch.uint8, device=f.device) if nb.value else None
     st = lib.rexii_apply_multishift(ctypes.byref(op), int(nrhs), ctypes.c_void_p(f.data_ptr()),
                                     ctypes.c_void_p(u.data_ptr()), float(t), ctypes.byref(o), *_ws_args(ws),
