@@ -55,9 +55,10 @@ void launch_lz_step(const double* cur, const double* prev, double* out, size_t s
 // u = sum_{j < m} coef[j] vecs[j], vectors of n3 doubles.
 void launch_lz_gather(const double* vecs, size_t n3, int m, const double* coef, double* u, hipStream_t s);
 // The small problem of one state: b = its beta row, y[j], coef[j] = y_j / b_{j-1}
-// and out = (|y|^2, |last 8 of y|^2); scratch: lz_small_bytes(m, npair), 256-byte aligned.
-size_t lz_small_bytes(int m, int npair);
-void launch_lz_small(const double* b, int m, double t, const LzPair* pairs, int npair, void* scratch, double* y,
+// and out = (|y|^2, |last 8 of y|^2), 64 nb pairs at a time; scratch:
+// lz_small_bytes(m, nb), 256-byte aligned.
+size_t lz_small_bytes(int m, int nb);
+void launch_lz_small(const double* b, int m, double t, const LzPair* pairs, int npair, int nb, void* scratch, double* y,
                      double* coef, double* out, hipStream_t s);
 
 }  // namespace rexii

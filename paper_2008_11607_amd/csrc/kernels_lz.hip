@@ -516,11 +516,12 @@ __global__ __launch_bounds__(256) void k_lz_gather(const double* __restrict__ ve
 //   x_1 = 1 / delta_1, x_{j+1} = -t b_j x_j / delta_{j+1}.
 // Bound: the serial chain of one reciprocal a row (about 130 cycles): 1184
 // rows and 2062 pairs take 0.2 ms here and took 3.5 ms on 16 host threads.
-// part[block][j] = the block's sum over its 64 pairs.
+// part[block][j] = the block's sum over its 64 pairs, added to what earlier
+// pairs left there (again).
 constexpr int kSmU = 8;   // rows whose loads are in flight together
 __global__ __launch_bounds__(64) void k_lz_small(const double* __restrict__ b, int m, double t,
                                                  const LzPair* __restrict__ pairs, int npair, double2* inv,
-                                                 double* __restrict__ part) {
+                                                 double* __restrict__ part, int again) {
   const int lane = threadIdx.x;
   const int q = blockIdx.x * 64 + lane;
   LzPair pr;
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(64) void k_lz_small(const double* __restrict__ b, i
       if (j > m) break;
       const double v = ((k & 1) == 0) ? c1r * x.x + c1i * x.y : c2r * x.x + c2i * x.y;   // j0 is odd
       const double s = wave_total63(v);
-      if (lane == 63) pp[j - 1] = s;
+      if (lane == 63) pp[j - 1] = again ? pp[j - 1] + s : s;
       const double sub = -t * bb[k];
       x = make_double2(sub * (x.x * id[k].x - x.y * id[k].y), sub * (x.x * id[k].y + x.y * id[k].x));
     }
@@ -738,16 +739,17 @@ void launch_lz_chip(const LzChip& c, hipStream_t s) {
                      c);
 }
 
-size_t lz_small_bytes(int m, int npair) {
-  const size_t nb = (size_t(npair) + 63) / 64;
-  return nb * 64 * m * sizeof(double2) + nb * m * sizeof(double) + 512;
+size_t lz_small_bytes(int m, int nb) {
+  return size_t(nb) * 64 * m * sizeof(double2) + size_t(nb) * m * sizeof(double) + 512;
 }
-void launch_lz_small(const double* b, int m, double t, const LzPair* pairs, int npair, void* scratch, double* y,
+void launch_lz_small(const double* b, int m, double t, const LzPair* pairs, int npair, int nb, void* scratch, double* y,
                      double* coef, double* out, hipStream_t s) {
-  const int nb = (npair + 63) / 64;
   double2* inv = static_cast<double2*>(scratch);
   double* part = reinterpret_cast<double*>(inv + size_t(nb) * 64 * m);
-  hipLaunchKernelGGL(k_lz_small, dim3(nb), dim3(64), 0, s, b, m, t, pairs, npair, inv, part);
+  for (int q = 0; q < npair; q += 64 * nb) {
+    const int left = npair - q, blocks = std::min(nb, (left + 63) / 64);
+    hipLaunchKernelGGL(k_lz_small, dim3(blocks), dim3(64), 0, s, b, m, t, pairs + q, left, inv, part, q > 0 ? 1 : 0);
+  }
   hipLaunchKernelGGL(k_lz_ysum, dim3(1), dim3(1024), 0, s, part, nb, m, b, y, coef, out);
 }
 

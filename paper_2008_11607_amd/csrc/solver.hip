@@ -3046,10 +3046,19 @@ static void small_problem(const double* b, int m, double t, double beta0, const 
 // Krylov dimension and pole pairs to expect for t rho (the dimension at which
 // the small solution's tail has met tol, with the next check's margin).
 static int lz_expect_m(double trho, int mmax) { return int(std::min<double>(mmax, 1.35 * trho + 128.0)); }
-static int lz_expect_pairs(double trho, double h) { return int(trho / h) + 64; }
+static int lz_expect_pairs(double trho, double h) { return int(std::min(double(1 << 22), trho / h)) + 64; }
+// The recurrences of the small problem in room bytes: blocks of 64 pairs
+// worked at a time (0: not one fits).
+static int lz_small_blocks(int m, int np, size_t room) {
+  const size_t two = lz_small_bytes(m, 2), one = lz_small_bytes(m, 1);
+  return room < one ? 0 : int(std::min<size_t>((size_t(np) + 63) / 64, 1 + (room - one) / (two - one)));
+}
+// All pairs at once up to this many bytes (t rho 7000 at h = 0.5); beyond it
+// several launches in turn, each a chain of about 1 ms per 10^4 rows.
+constexpr size_t kLzSmall = size_t(2) << 30;
 static size_t lz_scratch(double trho, double h, int mmax) {
-  const int np = lz_expect_pairs(trho, h);
-  return al256(size_t(np) * sizeof(LzPair)) + al256(lz_small_bytes(lz_expect_m(trho, mmax), np));
+  const int np = lz_expect_pairs(trho, h), m = lz_expect_m(trho, mmax);
+  return al256(size_t(np) * sizeof(LzPair)) + al256(lz_small_bytes(m, lz_small_blocks(m, np, kLzSmall)));
 }
 constexpr size_t kLzBudget = size_t(32) << 30;   // most bytes of kept vectors asked for
 constexpr size_t kLzOwn = size_t(2) << 30;       // ... and allocated by a call without a workspace
@@ -3308,14 +3317,15 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       const int np = sr[r].P / 2;
       double* yr = ydev + size_t(r) * ldy;
       const size_t pb = al256(size_t(np) * sizeof(LzPair));
-      if (pb + lz_small_bytes(mm, np) <= scr_room) {
+      const int nb_small = pb < scr_room ? lz_small_blocks(mm, np, scr_room - pb) : 0;
+      if (nb_small > 0) {
         pairs.resize(np);
         for (int q = 0; q < np; ++q)
           pairs[q] = LzPair{make_double2(zp[2 * q].re, zp[2 * q].im), make_double2(wp[2 * q].re, wp[2 * q].im),
                             make_double2(wp[2 * q + 1].re, wp[2 * q + 1].im)};
         HIPCHK(hipMemcpyAsync(scr, pairs.data(), size_t(np) * sizeof(LzPair), hipMemcpyHostToDevice, st));
-        launch_lz_small(beta + size_t(r) * ldb, mm, t, reinterpret_cast<const LzPair*>(scr), np, scr + pb, yr, coef,
-                        small_out, st);
+        launch_lz_small(beta + size_t(r) * ldb, mm, t, reinterpret_cast<const LzPair*>(scr), np, nb_small, scr + pb, yr,
+                        coef, small_out, st);
         HIPCHK(hipMemcpyAsync(hsmall, small_out, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
         wait_reads();
         sr[r].tail = (hsmall[0] > 0.0) ? std::sqrt(hsmall[1] / hsmall[0]) : 0.0;
