@@ -393,7 +393,12 @@ def apply_multishift(f, t, g=1.0, fc=10.0, H=1.0, Hfield=None, out=None, **opts)
     nb = ctypes.c_size_t()
     _check(lib.rexii_multishift_basis_size_on(ctypes.byref(op), int(nrhs), float(t), ctypes.byref(o), _stream(),
                                               ctypes.byref(nb)))
-    ws = torch.empty(nb.value, dtype=torch.uint8, device=f.device) if nb.value else None
+    try:
+        ws = torch.empty(nb.value, dtype=torch.uint8, device=f.device)
+    except torch.cuda.OutOfMemoryError:
+        # no room for the vectors: the least workspace, whose steps run twice
+        _check(lib.rexii_multishift_workspace_size(ctypes.byref(op), int(nrhs), ctypes.byref(o), ctypes.byref(nb)))
+        ws = torch.empty(nb.value, dtype=torch.uint8, device=f.device)
     st = lib.rexii_apply_multishift(ctypes.byref(op), int(nrhs), ctypes.c_void_p(f.data_ptr()),
                                     ctypes.c_void_p(u.data_ptr()), float(t), ctypes.byref(o), *_ws_args(ws),
                                     _stream(), ctypes.byref(rep))
