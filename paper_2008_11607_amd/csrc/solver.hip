@@ -2980,6 +2980,7 @@ static SmallResult small_plan(const double* b, int m, double t, double h, int m0
   // the segment i [-rho(A), rho(A)]: a bound on rho(A) caps Gershgorin's
   rho = std::min(rho, rho_cap);
   res.rho = rho;
+  if (t * rho / h > 1.0e9) throw HipError{REXII_ERR_INVALID_ARG, "t*rho/h too large for this library"};
   res.M = m_rule(t, std::max(rho, 1e-300), h, m0);
   res.N = res.M + terms_L();
   poles_weights(res.M, h, z, w);
@@ -3343,9 +3344,9 @@ static rexii_status run_multishift(const rexii_swe_op* op, int nrhs, const doubl
       // straight to the next chunk end at which a check can fall due (the
       // bound on rho(T) only grows with m)
       const double due = std::max(double(next_check), 0.75 * t * rho_seen);
-      int to = m + chunk;
-      if (rho_seen > 0.0 && due > to) to = m + chunk * int(std::ceil((due - m) / chunk));
-      enqueue(std::min(mmax, to));
+      double to = m + chunk;
+      if (rho_seen > 0.0 && due > to) to = m + chunk * std::ceil((due - m) / chunk);
+      enqueue(int(std::min(double(mmax), to)));
       HIPCHK(hipGetLastError());
       if (on_chip) HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
       read_beta(m + 1, launched);

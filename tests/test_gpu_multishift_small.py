@@ -46,3 +46,14 @@ def test_no_room_for_the_vectors():
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert float((u - v).norm() / u.norm()) <= 1e-12   # a few hundred terms of 1e-16
+
+
+@pytest.mark.parametrize("trho", [4e9, 1e12, 1e200])
+def test_time_step_past_every_integer(trho):
+    """The step at which a check falls due is past an int: the cap on m ends
+    pass 1, and the pole count is refused as by the other entry points."""
+    from paper_2008_11607_amd import rexii as rx
+    f = torch.from_numpy(inputs.gaussian_bumps(32, 24, nbumps=3, seed=4)).cuda()
+    with pytest.raises(rx.RexiiError) as e:
+        rx.apply_multishift(f, trho / rx.rho(32, 24), max_iter=96)
+    assert e.value.status == -1 and "too large" in str(e.value)
