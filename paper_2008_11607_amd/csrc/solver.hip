@@ -3566,6 +3566,10 @@ rexii_status rexii_multishift_basis_size_on(const rexii_swe_op* op, int32_t nrhs
   if (v != REXII_OK) return v;
   if (!bytes || nrhs <= 0) return set_error(REXII_ERR_INVALID_ARG, "need bytes and nrhs > 0");
   const rexii_opts o = resolve_opts(opts);
+  if (t == 0.0) {   // u = f: nothing is read but f
+    *bytes = multishift_bytes(op->nx, op->ny, nrhs, o.max_iter);
+    return clear_error();
+  }
   try {
     double hs = op->H0;
     if (op->H_field) {
