@@ -744,6 +744,15 @@ static size_t problem_bytes(const Problem& p) {
   return al256(2 * p.n() * 8) + al256(3 * p.n() * 8) + al256((8 + 256) * 8) + al256(p.n() * 8) + al256(p.n() * 4);
 }
 
+// Bytes of the mailboxes of `groups` groups: their records and control words,
+// and the edge rows.  A group of one block has none.
+static size_t chip_rec_bytes(int groups, int G) {
+  return size_t(G > 1 ? groups : 0) * (size_t(3) * G * kChipRec * 8 + kChipCtlGroup * 4) + kChipCtlHead * 4;
+}
+static size_t chip_ring_bytes(int groups, int G, int Gc, int nx, int eb) {
+  return Gc > 1 ? size_t(groups) * 6 * G * nx * eb : 0;
+}
+
 // Launch shape of the chip kernel for slots on an nx x ny grid; false where
 // no variant holds a slot (the passes then stream it).
 //   A group of G blocks holds one slot: G = 1 with every chain in the block,
@@ -784,10 +793,15 @@ static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* 
         if (occ < 0) occ = chip_occupancy(is_f32, k, nt, int(lds));
         if (occ < 1) break;
         // on one XCD where the queue fills every XCD's groups
-        const int gpx = (G > 1) ? (cus / 8) * occ / G : 0;
+        int gpx = (G > 1) ? (cus / 8) * occ / G : 0;
         const bool onx = gpx > 0 && nsolves >= 8 * gpx;
-        const int groups = onx ? 8 * gpx : std::min(cus * occ / G, std::max(1, nsolves));
+        int groups = onx ? 8 * gpx : std::min(cus * occ / G, std::max(1, nsolves));
+        // ... of the groups whose mailboxes fit into the slots' second r and p vectors
+        const size_t room = size_t(nsolves) * nx * ny * eb;
+        while (groups > 0 && (chip_rec_bytes(groups, G) > room || chip_ring_bytes(groups, G, Gc, nx, eb) > room))
+          groups -= onx ? 8 : 1;
         if (groups < 1) continue;
+        if (onx) gpx = groups / 8;
         const int per_cu = (groups * G + cus - 1) / cus;
         const double cyc = v.Q * v.RT * 50.0 + 350.0;
         const double chain = ((nt / 64 + 3) / 4) * 4.0 * cyc +
@@ -815,7 +829,7 @@ static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* 
   // steps of one launch: loading and storing a slot's vectors costs about a
   // step of the streaming passes, a launch's last groups wait for each other
   out->K = 256;
-  out->ctl_words = kChipCtlHead + kChipCtlGroup * out->ngroups;
+  out->ctl_words = kChipCtlHead + (out->G > 1 ? kChipCtlGroup * out->ngroups : 0);
   return true;
 }
 
@@ -1028,10 +1042,8 @@ struct Engine {
     Chip c;
     std::memset(static_cast<void*>(&c), 0, sizeof(c));
     if (!chip_config(plans[0]->nx, plans[0]->ny, e.d_is_f32, cus, z.B, &c)) return;
-    const size_t room = size_t(z.B) * z.cap * z.eb;
-    const size_t rec = size_t(c.ngroups) * 3 * c.G * kChipRec * 8, ctl = size_t(c.ctl_words) * 4;
-    const size_t ring = (c.Gc > 1) ? size_t(c.ngroups) * 6 * c.G * c.nx * z.eb : 0;
-    if (rec + ctl > room || ring > room) return;
+    const size_t rec = chip_rec_bytes(c.ngroups, c.G) - size_t(c.ctl_words) * 4;
+    const size_t ring = chip_ring_bytes(c.ngroups, c.G, c.Gc, c.nx, int(z.eb));
     c.rec = static_cast<unsigned long long*>(e.p1);
     c.ctl = reinterpret_cast<int*>(static_cast<char*>(e.p1) + rec);
     c.ring = e.r1;
@@ -1041,7 +1053,7 @@ struct Engine {
     e.chip_words = c.ctl_words;
     double none;
     std::memset(&none, 0xff, sizeof(none));
-    launch_fill_value(reinterpret_cast<double*>(c.rec), rec / 8, none, st);
+    if (rec > 0) launch_fill_value(reinterpret_cast<double*>(c.rec), rec / 8, none, st);
     if (ring > 0) launch_fill_value(static_cast<double*>(c.ring), ring / 8, none, st);
   }
 
