@@ -897,7 +897,7 @@ struct Engine {
   // SolveDesc::yidx, or the queue position when that is -1) or nullptr to
   // accumulate only.
   void setup(Arena& ar, const std::vector<Problem*>& probs, const EngineSize& zs, int prec, int user_max_iter,
-             double inner_eta, bool prof, double2* yout, int ystride) {
+             double inner_eta, bool prof, double2* yout, int ystride, const Chip* shape = nullptr) {
     z = zs;
     precision = prec;
     profile = prof;
@@ -1029,19 +1029,22 @@ struct Engine {
     grid = int(std::max<size_t>(size_t(cus) * std::max(1, occ), items));
     grid = ((grid + 7) / 8) * 8;
     e.grid_small = ((cus * 4 + 7) / 8) * 8;
-    setup_chip(cus);
+    setup_chip(cus, shape);
   }
 
   // Inner steps on the chip where every problem has the same grid and a
   // shape fits.  The chip kernel never swaps r and p, so its mailboxes lie
-  // in the second r and p vectors.
-  void setup_chip(int cus) {
+  // in the second r and p vectors.  shape: the launch, if it was chosen before.
+  void setup_chip(int cus, const Chip* shape) {
     if (z.method != 0) return;
     for (int i = 1; i < z.ninst; ++i)
       if (plans[i]->nx != plans[0]->nx || plans[i]->ny != plans[0]->ny) return;
     Chip c;
     std::memset(static_cast<void*>(&c), 0, sizeof(c));
-    if (!chip_config(plans[0]->nx, plans[0]->ny, e.d_is_f32, cus, z.B, &c)) return;
+    if (shape)
+      c = *shape;
+    else if (!chip_config(plans[0]->nx, plans[0]->ny, e.d_is_f32, cus, z.B, &c))
+      return;
     const size_t rec = chip_rec_bytes(c.ngroups, c.G) - size_t(c.ctl_words) * 4;
     const size_t ring = chip_ring_bytes(c.ngroups, c.G, c.Gc, c.nx, int(z.eb));
     c.rec = static_cast<unsigned long long*>(e.p1);
@@ -1866,46 +1869,93 @@ static void run_pc(Job& jb, Arena& ar) {
   en->solve_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
 }
 
+// Problem indices by grid, in order of first use.
+static std::vector<std::vector<int>> by_grid(const std::vector<Problem*>& ptrs) {
+  std::vector<std::vector<int>> groups;
+  std::map<std::pair<int, int>, size_t> index;
+  for (size_t i = 0; i < ptrs.size(); ++i) {
+    const Plan& pl = ptrs[i]->pl;
+    auto it = index.emplace(std::make_pair(pl.nx, pl.ny), groups.size());
+    if (it.second) groups.emplace_back();
+    groups[it.first->second].push_back(int(i));
+  }
+  return groups;
+}
+
+// Whether one chip engine per grid in turn takes less time than one engine
+// that streams every slot through HBM (z).  Estimates in us, fitted to 94
+// batches of 2 to 64 grids of 8 to 512 points a side, t rho 1 to 100, both
+// ways timed (largest error 1.6 times, the slower way never taken by more
+// than 3% over streaming): a streamed step costs 13 to 17 us and 0.04 to
+// 0.055 a slot and 0.006 to 0.01 a tile; an engine costs 140 (FP64) or 230 us
+// and its steps on the chip 2.7 or 4.6, or as many times more as its slots
+// take turns.  32 grids of 16 to 80 points, t rho 1, FP64: streamed 5.5 ms, by
+// grid 10.2; t rho 60: 128 and 45.
+static bool by_grid_pays(const std::vector<Problem*>& ptrs, const std::vector<std::vector<int>>& groups,
+                         const EngineSize& z, bool mixed, int cus) {
+  double steps = 0.0, tiles = 0.0, longest = 0.0, chip = 0.0;
+  for (const auto& g : groups) {
+    const Plan& p0 = ptrs[g[0]]->pl;
+    double sum = 0.0, most = 0.0;
+    for (int i : g)
+      for (const SolveDesc& d : ptrs[i]->pl.solves) {
+        sum += d.cost;
+        most = std::max(most, d.cost);
+      }
+    steps += sum;
+    tiles += sum * make_geo(p0.nx, p0.ny, kTY).nblk;
+    longest = std::max(longest, most);
+    const double blocks = std::max(1.0, double(p0.nx) * p0.ny / (mixed ? 11000.0 : 4096.0));   // a slot's
+    chip += std::max(most, sum * blocks / cus);
+  }
+  const double passes = std::max(longest, steps / z.B), np = double(ptrs.size()), ng = double(groups.size());
+  return mixed ? 230.0 * ng + 4.6 * chip < 125.0 + 11.0 * np + 13.4 * passes + 0.055 * steps + 0.0062 * tiles
+               : 138.0 * ng + 2.7 * chip < 17.0 + 16.0 * np + 17.0 * passes + 0.041 * steps + 0.0099 * tiles;
+}
+
 // A batch of unlike grids whose slots each fit on the chip: one engine per
 // grid in turn, in the same memory, instead of one engine that streams every
 // slot through HBM (a launch of the chip kernel has one shape).  The engines'
 // statistics are merged into jb.en.  False: nothing was done.
 static bool run_by_grid(Job& jb, Arena& ar, size_t mark, const EngineSize& z) {
   if (z.method != 0) return false;
-  std::vector<std::vector<int>> groups;   // problem indices by grid, in order of first use
-  std::map<std::pair<int, int>, size_t> index;
-  for (size_t i = 0; i < jb.ptrs.size(); ++i) {
-    const Plan& pl = jb.ptrs[i]->pl;
-    auto it = index.emplace(std::make_pair(pl.nx, pl.ny), groups.size());
-    if (it.second) groups.emplace_back();
-    groups[it.first->second].push_back(int(i));
-  }
+  const std::vector<std::vector<int>> groups = by_grid(jb.ptrs);
   if (groups.size() < 2) return false;
   int dev = 0, cus = 0;
   HIPCHK(hipGetDevice(&dev));
   HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const bool mixed = jb.o.precision == REXII_PREC_MIXED;
-  for (const auto& g : groups) {
-    Chip c;
-    if (!chip_config(jb.ptrs[g[0]]->pl.nx, jb.ptrs[g[0]]->pl.ny, mixed ? 1 : 0, cus, z.B, &c)) return false;
+  if (!by_grid_pays(jb.ptrs, groups, z, mixed, cus)) return false;
+  std::vector<EngineSize> sizes;
+  std::vector<Chip> shapes(groups.size());
+  for (size_t k = 0; k < groups.size(); ++k) {
+    std::vector<Problem*> sub;
+    for (int i : groups[k]) sub.push_back(jb.ptrs[i]);
+    ar.reset(mark);
+    EngineSize zs = engine_size(sub, jb.o.pole_batch, jb.o.precision, jb.o.tile_rows);
+    while (zs.B > 1 && engine_bytes(zs) > ar.remaining()) zs.B = std::max(1, (zs.B * 3) / 4);
+    if (engine_bytes(zs) > ar.remaining()) return false;
+    sizes.push_back(zs);
+    std::memset(static_cast<void*>(&shapes[k]), 0, sizeof(Chip));
+    if (!chip_config(sub[0]->pl.nx, sub[0]->pl.ny, mixed ? 1 : 0, cus, zs.B, &shapes[k])) return false;
   }
   std::unique_ptr<Engine> all(new Engine(jb.st));
   all->z = z;
   all->z.B = 0;
   all->precision = jb.o.precision;
   for (Problem* p : jb.ptrs) all->plans.push_back(&p->pl);
-  for (const auto& g : groups) {
+  for (size_t k = 0; k < groups.size(); ++k) {
+    const std::vector<int>& g = groups[k];
+    const EngineSize& zs = sizes[k];
     Job sub;
     sub.st = jb.st;
     sub.o = jb.o;
     for (int i : g) sub.ptrs.push_back(jb.ptrs[i]);
     ar.reset(mark);
-    EngineSize zs = engine_size(sub.ptrs, jb.o.pole_batch, jb.o.precision, jb.o.tile_rows);
-    while (zs.B > 1 && engine_bytes(zs) > ar.remaining()) zs.B = std::max(1, (zs.B * 3) / 4);
     sub.en = new Engine(jb.st);
     Engine& en = *sub.en;
     en.setup(ar, sub.ptrs, zs, jb.o.precision, jb.o.max_iter, mixed ? jb.o.inner_tol : 0.0, jb.o.profile != 0, nullptr,
-             zs.cap);
+             zs.cap, &shapes[k]);
     if (mixed) {
       en.run<float>();
       rerun_fp64(sub, ar, mark, nullptr);

@@ -32,3 +32,24 @@ def test_short_grids_run_on_the_chip(rx, precision, nx, ny, trho):
     u, rep = rx.apply(torch.from_numpy(fh).cuda(), t, precision=precision, tol=bar, profile=1)
     assert rep["kernel_launches"] < 16 and rep["not_converged"] == 0
     assert em.rel_l2(u.cpu().numpy(), em.expm_closed_real(op, fh, t)) <= bar
+
+
+# (launches of a call's chip engines are few; the passes come in sixteens)
+@pytest.mark.parametrize("precision,count,trho,streamed", [("fp64", 24, 1.0, True), ("fp64", 24, 60.0, False),
+                                                           ("mixed", 24, 5.0, True), ("mixed", 24, 80.0, False),
+                                                           ("fp64", 2, 20.0, False)])
+def test_unlike_grids_one_engine_or_one_per_grid(rx, precision, count, trho, streamed):
+    """Short queues on many unlike grids go through one streamed engine, long
+    ones through a chip engine per grid: 24 engines cost more than all steps
+    of the former."""
+    shapes = [(16 + 3 * i % 50, 16 + 7 * i % 40) for i in range(count)]
+    ops = [lrsw.LRSW(nx, ny, fc=10.0) for nx, ny in shapes]
+    fs = [inputs.gaussian_bumps(nx, ny, nbumps=2, seed=i, velocity=i % 3 == 0) for i, (nx, ny) in enumerate(shapes)]
+    ts = [trho / lrsw.rho(op) for op in ops]
+    bar = 1e-10 if precision == "fp64" else 1e-6
+    us, reps = rx.apply_batched([torch.from_numpy(f).cuda() for f in fs], ts, fc=10.0, precision=precision, tol=bar,
+                                profile=1)
+    assert (reps[0]["kernel_launches"] % 16 == 0) == streamed, reps[0]["kernel_launches"]
+    for op, f, t, u, rep in zip(ops, fs, ts, us, reps):
+        assert rep["not_converged"] == 0
+        assert em.rel_l2(u.cpu().numpy(), em.expm_closed_real(op, f, t)) <= bar
