@@ -2192,45 +2192,42 @@ static int autotune_slots(const std::vector<JobItem>& items, const rexii_opts& o
   HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const std::string key = tune_key(items, o, cus);
   *th = 0;
-  const int cached = tune_lookup(key, th);
-  if (cached > 0) return cached;
   size_t nsolves = 0, maxp = 0;
   bool depth = false;
-  {
-    std::vector<JobItem> its = items;
-    for (JobItem& it : its) {
-      if (it.skip) continue;
-      Problem pb;
-      if (sizing_plan(it, o, pb) != REXII_OK) return 0;
-      nsolves += pb.pl.solves.size();
-      maxp = std::max(maxp, pb.n());
-      depth = depth || it.op->H_field != nullptr;
-    }
+  std::vector<Problem> pbs(items.size());
+  std::vector<Problem*> ptrs;
+  for (size_t i = 0; i < items.size(); ++i) {
+    if (items[i].skip) continue;
+    if (sizing_plan(items[i], o, pbs[i]) != REXII_OK) return 0;
+    ptrs.push_back(&pbs[i]);
+    nsolves += pbs[i].pl.solves.size();
+    maxp = std::max(maxp, pbs[i].n());
+    depth = depth || items[i].op->H_field != nullptr;
   }
   const bool bicg = depth || o.method == 1;
-  if (!bicg) {
+  const int cached = tune_lookup(key, th);
+  if (!bicg && !ptrs.empty()) {
     // slots whose inner steps run on the chip: the count decides little (the
-    // groups take the slots in turn), the default stands
-    std::vector<Problem> pbs(items.size());
-    std::vector<Problem*> ptrs;
-    for (size_t i = 0; i < items.size(); ++i) {
-      if (items[i].skip || sizing_plan(items[i], o, pbs[i]) != REXII_OK) continue;
-      ptrs.push_back(&pbs[i]);
+    // groups take the slots in turn), so the default stands whatever a line
+    // of the file says, and a batch that runs one engine per grid has no one
+    // count
+    const bool mixed = o.precision == REXII_PREC_MIXED;
+    const std::vector<std::vector<int>> groups = by_grid(ptrs);
+    const EngineSize z = engine_size(ptrs, 0, o.precision, o.tile_rows);
+    bool chip = groups.size() == 1 || by_grid_pays(ptrs, groups, z, mixed, cus);
+    for (size_t k = 0; chip && k < groups.size(); ++k) {
+      Chip c{};
+      const Plan& pl = ptrs[groups[k][0]]->pl;
+      chip = chip_config(pl.nx, pl.ny, mixed, cus, z.B, &c);
     }
-    bool same = !ptrs.empty();
-    for (Problem* p : ptrs) same = same && p->pl.nx == ptrs[0]->pl.nx && p->pl.ny == ptrs[0]->pl.ny;
-    Chip c{};
-    if (same) {
-      const EngineSize z = engine_size(ptrs, 0, o.precision, o.tile_rows);
-      if (chip_config(ptrs[0]->pl.nx, ptrs[0]->pl.ny, o.precision == REXII_PREC_MIXED, cus, z.B, &c)) {
-        // (the plan counts unpaired solves: half of them may pair up)
-        const int B = std::max(1, std::min(z.B, (z.S + 1) / 2));
-        tune_store(key, B, z.th, 0.0);
-        *th = z.th;
-        return B;
-      }
+    if (chip) {
+      // (the plan counts unpaired solves: half of them may pair up)
+      if (groups.size() == 1 && cached == 0) tune_store(key, std::max(1, std::min(z.B, (z.S + 1) / 2)), z.th, 0.0);
+      *th = 0;
+      return 0;
     }
   }
+  if (cached > 0) return cached;
   std::vector<int> ths;
   if (bicg && o.tile_rows == 0)
     ths = {32, 16};

@@ -53,3 +53,24 @@ def test_unlike_grids_one_engine_or_one_per_grid(rx, precision, count, trho, str
     for op, f, t, u, rep in zip(ops, fs, ts, us, reps):
         assert rep["not_converged"] == 0
         assert em.rel_l2(u.cpu().numpy(), em.expm_closed_real(op, f, t)) <= bar
+
+
+def test_autotuner_leaves_chip_engines_alone(rx, tmp_path, monkeypatch):
+    """Calls whose steps run on the chip take the default slot count: one engine
+    per grid is not tuned through streamed engines, and the line that a short
+    call left does not narrow a long one."""
+    tune = tmp_path / "tune.txt"
+    monkeypatch.setenv("REXII_TUNE_CACHE", str(tune))
+    shapes = [(64, 64), (96, 80), (72, 100)]
+    fs = [torch.from_numpy(inputs.gaussian_bumps(nx, ny, nbumps=2, seed=nx)).cuda() for nx, ny in shapes]
+    ts = [100.0 / rx.rho(nx, ny) for nx, ny in shapes]
+    u0, r0 = rx.apply_batched(fs, ts)
+    u1, r1 = rx.apply_batched(fs, ts, pole_batch=-1)
+    assert not tune.exists()
+    assert [r["slots"] for r in r0] == [r["slots"] for r in r1]
+    assert all(bool((a == b).all()) for a, b in zip(u0, u1))
+    rx.apply(fs[0], ts[0] / 200.0, pole_batch=-1)
+    assert "nx=64 ny=64" in tune.read_text()
+    u2, r2 = rx.apply(fs[0], ts[0], pole_batch=-1)
+    u3, r3 = rx.apply(fs[0], ts[0])
+    assert r2["slots"] == r3["slots"] and bool((u2 == u3).all())
