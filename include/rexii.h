@@ -160,10 +160,9 @@ typedef struct rexii_report {
                                (capped at 1e-2)                             */
     double max_rel_residual; /* largest final FP64 relative residual        */
     double seconds;          /* host wall time of the call (seconds_total)  */
-    double alg_bytes;        /* algorithmic HBM bytes of the Krylov kernels
-                                (COCG steps that hold their vectors on the
-                                chip count the bytes the streaming pass
-                                moves for them)                             */
+    double alg_bytes;        /* HBM bytes of the Krylov iterations with their
+                                vectors streamed; COCG steps that hold them
+                                on the chip move less (kernel_bytes)        */
     int32_t stagnated;       /* FP64 solves stopped at their residual floor
                                above their tolerance (their residuals enter
                                err_bound)                                  */
@@ -172,7 +171,8 @@ typedef struct rexii_report {
      * pass kernel (of the kernel that runs the inner steps on the chip where
      * the grid allows it), and the algorithmic bytes of those launches (a
      * pass reads x, r, p and writes them once: 6 complex values per grid
-     * point and live solve; 3 for the first pass after an FP64 residual) */
+     * point and live solve; 3 for the first pass after an FP64 residual; a
+     * launch of up to 256 steps on the chip moves as much as one pass) */
     int64_t kernel_launches;
     double kernel_ms;
     double kernel_bytes;

@@ -93,7 +93,9 @@ struct SolveDev {
 struct SolveStat {
   double rn2, bn2;
   int it_total, rounds, status, stagnated;
-  int skips, pad;   // COCG inner steps that left d alone (see Slot::dmode)
+  int skips;            // COCG inner steps that left d alone (see Slot::dmode)
+  int visits, chip_its; // launches of k_chip that took the solve, and their steps
+  int pad;
 };
 
 struct Slot {
@@ -132,7 +134,9 @@ struct Slot {
   int dmode;         // COCG: kDUpdate or kDSkip for the next inner step
   int fin;           // COCG: the inner round ends after the next step
   int skips;         // COCG: inner steps with dmode = kDSkip
-  int pad2;
+  int visits;        // launches of k_chip that took the slot,
+  int chip_its;      // and the steps they made
+  int pad2[3];
 };
 
 // COCG correction updates.  An inner step with alpha_i, beta_i adds

@@ -872,7 +872,7 @@ __device__ __forceinline__ int assign_solve(const Eng& e, int s, int next) {
   S->dcp = S->dcr = zero;
   S->dmode = kDUpdate;
   S->fin = 0;
-  S->skips = 0;
+  S->skips = S->visits = S->chip_its = 0;
   return nblk;
 }
 
@@ -912,6 +912,8 @@ __global__ __launch_bounds__(kSchedNT) void k_assign(Eng e) {
       ss.status = st;
       ss.stagnated = ldc(&S->stagnated);
       ss.skips = ldc(&S->skips);
+      ss.visits = ldc(&S->visits);
+      ss.chip_its = ldc(&S->chip_its);
       ss.pad = 0;
       e.stats[sv] = ss;
       st = kIdle;

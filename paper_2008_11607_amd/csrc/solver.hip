@@ -1250,10 +1250,6 @@ struct Engine {
     }
     stats.resize(z.S);
     read_to_host(stats.data(), e.stats, z.S * sizeof(SolveStat), st);
-    // steps of the chip kernel count as the bytes that the passes stream for
-    // them (in FP64 every other step leaves d alone)
-    if (e.chip_words > 0 && z.eb == 16)
-      for (SolveStat& s : stats) s.skips = s.it_total / 2;
     solve_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
 #ifdef REXII_DEBUG_CHECKS
     int dbg[16];
@@ -1293,6 +1289,16 @@ struct Engine {
         // read)
         const double eb = double(z.eb);
         const int R = stats[j].rounds;
+        if (stats[j].visits > 0) {
+          // k_chip: a launch reads r, p and d (no d in a round's first) and
+          // writes d (and r and p, if the round goes on); the first launch of
+          // every later round moves d into x64.  Steps of passes that took
+          // over count as below.
+          const int V = stats[j].visits, more = std::max(0, V - (R - 1));
+          pass_bytes += pts * (eb * (3.0 * V + 3.0 * more) + std::max(0, R - 2) * (32.0 + eb) +
+                               6.0 * eb * (stats[j].it_total - stats[j].chip_its) - 2.0 * eb * stats[j].skips);
+          continue;
+        }
         pass_bytes += pts * (6.0 * eb * stats[j].it_total - 2.0 * eb * stats[j].skips + (8.0 + 2.0 * eb) +
                              std::max(0, R - 1) * (24.0 + 3.0 * eb) + std::max(0, R - 1) * eb +
                              std::max(0, R - 2) * (32.0 - eb));
@@ -1308,6 +1314,7 @@ struct RunSummary {
   int max_iters = 0, max_rounds = 0, not_conv = 0, breakdowns = 0, stagnated = 0;
   int64_t total_iters = 0;
   int64_t total_skips = 0;   // COCG steps that left d alone
+  int64_t chip_iters = 0;    // COCG steps in k_chip
   double max_rel_res = 0.0;
   // error bound of the result (relative, W-norm): sum over the solves of
   // wsum * (achieved |r3|) / |f|_W; explicit shifts: the largest relative
@@ -1326,6 +1333,7 @@ static RunSummary summarize(const Engine& en, int inst) {
     r.max_rounds = std::max(r.max_rounds, s.rounds);
     r.total_iters += s.it_total;
     r.total_skips += s.skips;
+    r.chip_iters += s.chip_its;
     if (s.status == kFailBreakdown) r.breakdowns++;
     else if (s.status != kDone) r.not_conv++;
     r.stagnated += s.stagnated;
@@ -1383,8 +1391,11 @@ static void fill_report(rexii_report* rep, const Plan& pl, const Engine* en, int
     const double per_pt = en->z.method == 2   ? 34.0 * 16.0 + 2.0 * 8.0
                           : en->z.method == 1 ? 13.0 * eb + 3.0 * (eb == 8.0 ? 4.0 : 8.0)
                                               : 6.0 * eb;
+    // (COCG steps on the chip: as the passes stream them, every other FP64
+    // step leaving d alone)
+    const double skips = double(r.total_skips) + (eb == 16.0 ? 0.5 * double(r.chip_iters) : 0.0);
     rep->alg_bytes = double(pl.nx) * pl.ny *
-                     (double(r.total_iters) * per_pt - (en->z.method == 0 ? double(r.total_skips) * 2.0 * eb : 0.0));
+                     (double(r.total_iters) * per_pt - (en->z.method == 0 ? skips * 2.0 * eb : 0.0));
     rep->slots = en->z.B;
     rep->tile_rows = en->z.th;
     rep->kernel_launches = en->launches;

@@ -74,3 +74,17 @@ def test_autotuner_leaves_chip_engines_alone(rx, tmp_path, monkeypatch):
     u2, r2 = rx.apply(fs[0], ts[0], pole_batch=-1)
     u3, r3 = rx.apply(fs[0], ts[0])
     assert r2["slots"] == r3["slots"] and bool((u2 == u3).all())
+
+
+@pytest.mark.parametrize("precision,eb", [("fp64", 16), ("mixed", 8)])
+def test_kernel_bytes_are_those_that_move(rx, precision, eb):
+    """A launch of the chip kernel reads and writes a slot's vectors once, not
+    once a step: at least r, p and d for every solve, at most six values a
+    launch and x64 once a round, far under the streamed steps' bytes."""
+    n = 128 * 128
+    f = torch.from_numpy(inputs.gaussian_bumps(128, 128, nbumps=3, seed=8)).cuda()
+    _, rep = rx.apply(f, 200.0 / rx.rho(128, 128), precision=precision, profile=1)
+    assert rep["solves"] * n * 3 * eb <= rep["kernel_bytes"]
+    visits = rep["solves"] * (rep["max_refine"] + rep["max_iters"] / 256.0)
+    assert rep["kernel_bytes"] <= n * visits * (6 * eb + 32)
+    assert rep["kernel_bytes"] <= 0.2 * rep["alg_bytes"]
