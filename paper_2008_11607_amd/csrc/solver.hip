@@ -2748,13 +2748,16 @@ static bool fourier_own(int nx, int ny) {
   return !wasteful(ny) && (!wasteful(nx) || pow2(ny));
 }
 
-static size_t fourier_bytes(int nx, int ny, int deriv, int nterm, size_t fft_work, const FarBoxes& fb, bool own) {
+// one: the direct sums in one split (no scratch of their own).
+static size_t fourier_bytes(int nx, int ny, int deriv, int nterm, size_t fft_work, const FarBoxes& fb, bool own,
+                            bool one = false) {
   const size_t nm = size_t(nx / 2 + 1) * ny;
   int cnx = 0, cny = 0;
   fourier_canon(nx, ny, deriv, &cnx, &cny);
   const int ne = mode_entries(cnx, cny, nx == ny ? 1 : 0);
   int nw = 1, ns = 1;
   mode_coef_shape(ne, nterm, own, &nw, &ns);
+  if (one) ns = 1;
   const size_t part = fb.nbox > 0 ? al256(far_doubles2(fb, nterm) * 16) : (ns > 1) ? al256(size_t(ns) * ne * 16) : 0;
   // spectra, coefficients, split sums or the boxes' sums, finiteness words,
   // and (copied in by the no-allocation entry point) the term, symbol and
@@ -2819,6 +2822,17 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
         }
       }
     }
+    bool one = false;
+    if (ws && ws_bytes < need) {
+      // a workspace sized for a longer step holds every shorter one's, in
+      // some layout: the scratch of the pole sums does not grow with t as
+      // boxes take the place of split sums
+      for (int k = 0; k < 2 && ws_bytes < need; ++k) {
+        fb = FarBoxes{};
+        one = k == 1;
+        need = fourier_bytes(nx, ny, deriv, fp.nterm, work, fb, own, one);
+      }
+    }
     int cnx = 0, cny = 0;
     fourier_canon(nx, ny, deriv, &cnx, &cny);
     if (noalloc) {
@@ -2842,6 +2856,7 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     int nw = 1, ns = 1;
     mode_coef_shape(ne, fp.nterm, own, &nw, &ns);
     const bool boxed = fb.nbox > 0;
+    if (one) ns = 1;
     if (boxed) far_shape(fb.nbox, fp.nterm, &nw, &ns);
     const bool sum_in_apply = !boxed && mode_sum_in_apply(ne, ns);
     const std::vector<double>& htab = fp.tab->tab;
