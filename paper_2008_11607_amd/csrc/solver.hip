@@ -2881,20 +2881,24 @@ static rexii_status run_fourier(const rexii_swe_op* op, const double* f, double*
     // scratch
     const double* tab = nullptr;
     const double* sxt = nullptr;
+    std::vector<double> stage;   // (read by the copy until the stream is drained)
     if (noalloc) {
       double* dtab = ar.take<double>(htab.size());
-      double* dsym = ar.take<double>(sym->s.size());
       HIPCHK(hipMemcpyAsync(dtab, htab.data(), htab.size() * sizeof(double), hipMemcpyHostToDevice, st));
-      HIPCHK(hipMemcpyAsync(dsym, sym->s.data(), sym->s.size() * sizeof(double), hipMemcpyHostToDevice, st));
       tab = dtab;
-      sxt = dsym;
+      // the small tables in one copy (each costs some 5 us of the call): 256-byte places, as take gives
+      const std::vector<double>* small[3] = {&sym->s, own ? &axt->v : nullptr, own ? &ayt->v : nullptr};
+      double* at[3] = {};
+      for (int k = 0; k < (own ? 3 : 1); ++k) {
+        at[k] = ar.take<double>(small[k]->size());
+        stage.resize(size_t(at[k] - at[0]));
+        stage.insert(stage.end(), small[k]->begin(), small[k]->end());
+      }
+      HIPCHK(hipMemcpyAsync(at[0], stage.data(), stage.size() * sizeof(double), hipMemcpyHostToDevice, st));
+      sxt = at[0];
       if (own) {
-        double* dx = ar.take<double>(axt->v.size());
-        HIPCHK(hipMemcpyAsync(dx, axt->v.data(), axt->v.size() * sizeof(double), hipMemcpyHostToDevice, st));
-        ax = fft_axis(nx, dx);
-        double* dy = ar.take<double>(ayt->v.size());
-        HIPCHK(hipMemcpyAsync(dy, ayt->v.data(), ayt->v.size() * sizeof(double), hipMemcpyHostToDevice, st));
-        ay = fft_axis(ny, dy);
+        ax = fft_axis(nx, at[1]);
+        ay = fft_axis(ny, at[2]);
       }
     } else {
       tab = fp.tab->dev.get(htab);
