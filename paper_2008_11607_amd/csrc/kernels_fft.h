@@ -10,9 +10,9 @@ namespace rexii {
 // Fourier-space path (constant depth).  tab holds nterm merged terms
 // (a, b^2, A1, B1, A2, B2); deriv 0: centred-difference symbols, 1: Fourier
 // differentiation.
-// canon_count: number of distinct canonical wavenumbers among k = 0..kmax on
+// canon_count: number of distinct canonical wavenumbers on
 // an axis of n points (modes with the same canonical pair share theta).
-int canon_count(int n, int kmax, int deriv);
+int canon_count(int n, int deriv);
 // coef [cny][cnx] = scale (Re c1, Re c2) per canonical pair; nw waves per
 // block, the terms in ns splits (part: ns x entries double2 when ns > 1).
 void mode_coef_shape(int entries, int nterm, bool whole, int* nw, int* ns);

@@ -150,14 +150,9 @@ __device__ __forceinline__ void term_sums(const double* __restrict__ tab, int nt
   c2 = c.c2a + c.c2b;
 }
 
-int canon_count(int n, int kmax, int deriv) {
-  int c = 0;
-  for (int k = 0; k <= kmax; ++k) {
-    const int v = canon_index(k, n, deriv);
-    c = v > c ? v : c;
-  }
-  return c + 1;
-}
+// 0..n/4 (centred, even n), 0..(n-1)/2 (odd n), 0..n/2-1 (Fourier
+// differentiation, even n: the Nyquist mode has index 0)
+int canon_count(int n, int deriv) { return n % 2 ? (n + 1) / 2 : deriv ? n / 2 : n / 4 + 1; }
 
 // The pole sums per distinct frequency: coef[cy * cnx + cx] = scale (Re c1,
 // Re c2) at theta^2 = t^2 (f_c^2 + g H (s_x^2 + s_y^2)) for the canonical

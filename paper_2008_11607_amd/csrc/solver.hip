@@ -2708,8 +2708,8 @@ static rexii_status fourier_plan(const rexii_swe_op* op, double t, const rexii_o
 // distinct canonical wavenumbers of the half spectrum's x (k = 0..nx/2) and
 // y (k = 0..ny-1) indices
 static void fourier_canon(int nx, int ny, int deriv, int* cnx, int* cny) {
-  *cnx = canon_count(nx, nx / 2, deriv);
-  *cny = canon_count(ny, ny - 1, deriv);
+  *cnx = canon_count(nx, deriv);
+  *cny = canon_count(ny, deriv);
 }
 
 // finiteness words: one a block of the check (rocFFT route) or of the forward
