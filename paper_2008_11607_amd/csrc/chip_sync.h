@@ -9,6 +9,11 @@
 namespace rexii {
 
 constexpr unsigned long long kNoWord = ~0ull;   // a NaN pattern no sum produces
+// Polls for a word of a running group, seconds (it is microseconds away): ends
+// what cannot go on.  k_lz_chip takes the constant (as a launch parameter it
+// cost 1.6% at 512^2, as 2^20 or 2^22 2 to 8%), k_chip the launch parameter
+// (the constant cost 4% at 256^2 in FP64): the code around the waits differs.
+constexpr unsigned kRunPolls = 1u << 23;
 
 __device__ __forceinline__ unsigned long long ald(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -132,7 +137,8 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // [0] arrivals, [1] state (0 forming, 1 ready, 2 cancelled).  Returns false
 // for a block beyond the groups, for one of a group without work (with
 // gpx > 0 group k of XCD x works on item 8 k + x of `items`; the others do
-// not wait for each other) and for a group that did not fill (late).
+// not wait for each other), for a group that did not fill (late) and for a
+// block that is to be dropped.
 struct GroupPlace {
   int gid, rank, xcd;
 };
@@ -156,7 +162,7 @@ __device__ __forceinline__ bool join_group(int* ctl, int G, int gpx, int items, 
       if (++n > waits.form_polls && atomicCAS(&w[1], 0, 2) == 0) lt = 1;
       __builtin_amdgcn_s_sleep(2);
     }
-    sh[0] = st;
+    sh[0] = (waits.run_polls == 0 && ticket - k * G == G - 1) ? 2 : st;
     sh[1] = g;
     sh[2] = ticket - k * G;
     sh[3] = x;

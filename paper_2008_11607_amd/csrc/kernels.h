@@ -212,11 +212,12 @@ constexpr int kChipMaxG = 64;      // largest group timed
 constexpr int kChipGaveUp = 1;     // a wait inside a running group gave up: an error, its mailboxes are not empty
 constexpr int kChipLate = 2;       // a group did not form: its work is still to be done
 // How the blocks of a launch wait for each other.  $REXII_CHIP_WAITS =
-// form_polls,run_polls,late_group,late_from overrides it (tests of what follows a wait
-// that ends without its condition: every block still leaves the kernel).
+// form_polls,run_polls,late_group,late_from overrides it (tests of what follows a
+// wait that ends without its condition: every block still leaves the kernel).
 struct ChipWaits {
   unsigned form_polls;   // polls of a block for its group to fill
-  unsigned run_polls;    // polls for a word of a running group
+  unsigned run_polls;    // polls for a word of a running group; 0: the last block of every
+                         // group leaves when it has formed, its words never come
   int late_group;        // a group that never fills, or -1
   int late_from;         // ... in the launches of a call from this one on
   ChipWaits at(int launch) const {

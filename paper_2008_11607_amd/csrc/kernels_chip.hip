@@ -222,7 +222,6 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
     const int par = sw.i32(SLOT_OFF(parity));
     const int it0 = sw.i32(SLOT_OFF(it_inner)), itt0 = sw.i32(SLOT_OFF(it_total));
     const int rounds = sw.i32(SLOT_OFF(rounds)), max_it = sw.i32(SLOT_OFF(max_it));
-    const int visits = sw.i32(SLOT_OFF(visits)), chip_its = sw.i32(SLOT_OFF(chip_its));
     const double in_tol2 = sw.f64(SLOT_OFF(in_tol2));
     const double cx64 = sw.f64(SLOT_OFF(cx)), icx = 1.0 / cx64;
     const double2 zeta64 = sw.c64(SLOT_OFF(zeta));
@@ -536,8 +535,8 @@ __device__ __forceinline__ void chip_run(const Eng& e, const Chip& c, unsigned c
       Slot* Z = &e.slots[slot];
       Z->it_inner = it0 + steps;
       Z->it_total = itt0 + steps;
-      Z->visits = visits + 1;
-      Z->chip_its = chip_its + steps;
+      Z->visits = ldc(&Z->visits) + 1;
+      Z->chip_its = ldc(&Z->chip_its) + steps;
       Z->alpha = make_double2(al64.x * icx, al64.y * icx);
       Z->beta = be64;
       Z->dcp = Z->alpha;   // should the passes take the next step: d += alpha p

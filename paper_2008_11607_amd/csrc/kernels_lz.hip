@@ -363,7 +363,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
           unsigned long long w;
           unsigned k = 0;
           while (!__all((w = ald(th)) != kNoWord)) {
-            if (++k > c.waits.run_polls) {
+            if (++k > kRunPolls) {
               sh[5] = 1;
               break;
             }
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       if (rtop) {
         unsigned long long a, b;
         while ((a = ald(rup)) == kNoWord || (b = ald(rup + nx)) == kNoWord) {
-          if (++k > c.waits.run_polls) {
+          if (++k > kRunPolls) {
             sh[5] = 1;
             break;
           }
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       if (rbot) {
         unsigned long long a, b;
         while ((a = ald(rdn)) == kNoWord || (b = ald(rdn + nx)) == kNoWord) {
-          if (++k > c.waits.run_polls) {
+          if (++k > kRunPolls) {
             sh[5] = 1;
             break;
           }
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(512, 2) void k_lz_chip(LzChip c) {
       __hip_atomic_fetch_add(&gc[2], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned k = 0;
       while (ldc(&gc[2]) < G) {
-        if (++k > c.waits.run_polls) {
+        if (++k > kRunPolls) {
           atomicOr(c.flag, kChipGaveUp);
           break;
         }

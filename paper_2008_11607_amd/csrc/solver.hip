@@ -833,11 +833,10 @@ static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* 
   return true;
 }
 
-// Limits of the waits, in polls of at least half a microsecond.  A group's
-// blocks start as soon as blocks of other kernels leave the CUs, so 20 ms
-// (other processes' launches may hold them for longer: the group's work is
-// then left for the next launch); a word of a running group is microseconds
-// away, its limit of seconds only ends what cannot go on.
+// A group's blocks start as soon as blocks of other kernels leave the CUs:
+// about 20 ms of polls (of at least half a microsecond).  Other processes'
+// launches may hold CUs for longer: the group's work is then left for the next
+// launch.
 static ChipWaits chip_waits() {
   ChipWaits w{1u << 15, 1u << 23, -1, 0};
   if (const char* v = std::getenv("REXII_CHIP_WAITS"))

@@ -390,8 +390,8 @@ def apply_multishift(f, t, g=1.0, fc=10.0, H=1.0, Hfield=None, out=None, **opts)
     op = make_op(nx, ny, g, fc, H, Hfield)
     o = make_opts(**opts)
     rep = Report()
-    nb = ctypes.c_size_t()
-    _check(lib.rexii_multishift_basis_size_on(ctypes.byref(op), int(nrhs), float(t), ctypes.byref(o), _stream(),
+    nb, stream = ctypes.c_size_t(), _stream()
+    _check(lib.rexii_multishift_basis_size_on(ctypes.byref(op), int(nrhs), float(t), ctypes.byref(o), stream,
                                               ctypes.byref(nb)))
     try:
         ws = torch.empty(nb.value, dtype=torch.uint8, device=f.device)
@@ -401,7 +401,7 @@ def apply_multishift(f, t, g=1.0, fc=10.0, H=1.0, Hfield=None, out=None, **opts)
         ws = torch.empty(nb.value, dtype=torch.uint8, device=f.device)
     st = lib.rexii_apply_multishift(ctypes.byref(op), int(nrhs), ctypes.c_void_p(f.data_ptr()),
                                     ctypes.c_void_p(u.data_ptr()), float(t), ctypes.byref(o), *_ws_args(ws),
-                                    _stream(), ctypes.byref(rep))
+                                    stream, ctypes.byref(rep))
     _check(st, rep)
     return u, rep.as_dict()
 

@@ -1,6 +1,7 @@
 """What follows a wait of the on-chip kernels that ends without its condition:
-REXII_CHIP_WAITS makes one group of blocks never fill, or a wait give up at
-its first look; every block leaves the kernel, the host goes on another way."""
+REXII_CHIP_WAITS makes one group of blocks never fill, or the last block of
+each group leave, so that the others' waits give up; every block leaves the
+kernel, the host goes on another way."""
 import ctypes
 
 import pytest
@@ -67,7 +68,7 @@ def test_lanczos_group_that_never_fills(rx, monkeypatch, nx, ny, nrhs, kept, lat
 
 
 def test_a_wait_that_gave_up_is_an_error(rx, monkeypatch):
-    """... also where a late group reports after it (2000 polls against one),
+    """... also where a late group reports after it (seconds more of polls),
     and the next call is a right one."""
     f, t, (ws, _) = _multishift_case(rx, 130, 66, 3, 6)
     g = f[0, :, :64, :96].contiguous()
@@ -75,7 +76,7 @@ def test_a_wait_that_gave_up_is_an_error(rx, monkeypatch):
     st, m0, _ = _multishift(rx, f, t, ws)
     assert st == 0
     with monkeypatch.context() as m:
-        m.setenv("REXII_CHIP_WAITS", "2000,0,0,0")
+        m.setenv("REXII_CHIP_WAITS", "10000000,0,0,0")
         st, _, _ = _multishift(rx, f, t, ws)
         assert st == -6 and "past its limit" in rx.last_error()
         with pytest.raises(rx.RexiiError) as e:
