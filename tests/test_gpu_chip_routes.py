@@ -2,6 +2,7 @@
 256 steps further; the streamed passes launch 16 steps at a time) and that
 their results meet the bars of the two precisions against the exact
 exponential."""
+import numpy as np
 import pytest
 import torch
 
@@ -88,3 +89,27 @@ def test_kernel_bytes_are_those_that_move(rx, precision, eb):
     visits = rep["solves"] * (rep["max_refine"] + rep["max_iters"] / 256.0)
     assert rep["kernel_bytes"] <= n * visits * (6 * eb + 32)
     assert rep["kernel_bytes"] <= 0.2 * rep["alg_bytes"]
+
+
+@pytest.mark.parametrize("precision,tol,cap", [("fp64", 1e-10, 1), ("fp64", 1e-10, 2), ("fp64", 1e-10, 7),
+                                               ("fp64", 1e-10, 255), ("fp64", 1e-10, 256), ("fp64", 1e-10, 300),
+                                               ("mixed", 1e-6, 300)])
+def test_capped_solves_on_the_chip_keep_their_bound(rx, precision, tol, cap):
+    """A cap that ends an inner solve inside a launch, at its end and in the next
+    one: the written result is the iterate whose residuals are reported, within
+    the bound of its distance to the exact exponential (the rational
+    approximation's own error is 1e-11 at most)."""
+    op = lrsw.LRSW(96, 64, fc=10.0)
+    fh, t = inputs.gaussian_bumps(96, 64, nbumps=2, seed=6, velocity=True), 250.0 / lrsw.rho(op)
+    u = torch.full((3, 64, 96), float("nan"), dtype=torch.float64, device="cuda")
+    try:
+        _, rep = rx.apply(torch.from_numpy(fh).cuda(), t, precision=precision, tol=tol, max_iter=cap, out=u, profile=1)
+    except rx.RexiiError as e:
+        assert e.status == -3
+        rep = e.report
+    # an FP32 solve that its cap ends is run again in FP64, with the same cap
+    assert rep["max_iters"] <= (cap + 1 if precision == "fp64" else 2 * cap + 2)
+    assert rep["kernel_launches"] > 0 and (cap > 16 or rep["not_converged"] > 0)
+    ex = em.expm_closed_real(op, fh, t)
+    diff = np.linalg.norm(u.cpu().numpy() - ex) / np.linalg.norm(fh)   # g = H = 1: the W-norm
+    assert np.isfinite(diff) and diff <= rep["err_bound"] * (1 + 1e-6) + 2e-11
