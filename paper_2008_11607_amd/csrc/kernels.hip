@@ -570,11 +570,14 @@ __global__ __launch_bounds__(kSNT) void k_pass_scalars(Eng e) {
       S->it_inner = 0;
       // the requested reduction of this residual, never below a quarter of
       // the final tolerance.  With FP32 steps on the chip a round that ends
-      // the solve, or ends it but for a factor of two, goes on to a sixteenth:
-      // steps are cheap there, and the sum's error falls four- to tenfold
-      // (tol 1e-7, grids of 200 x 175 to 558 x 193: 2e-10..9e-10 before,
-      // 4e-11..2e-10 now, times within 1%; 512^2, t rho 250: 4.4e-10 to 6e-11,
-      // 189 to 208 ms).
+      // the solve, or ends it but for a factor of two, goes on to a sixteenth,
+      // so that the sum is no further from the exact one than the passes'
+      // sum, whose summation order the chip does not keep.  More than the
+      // tolerance asks for: at tol 1e-7 the error falls four- to tenfold (200
+      // x 175 to 558 x 193: 2e-10..9e-10 with the quarter, 4e-11..2e-10) for
+      // up to 10% more time (512^2, t rho 250: 189 -> 208 ms); at the default
+      // 1e-6, 512^2, t rho 1000, 1.2e-9 -> 5.2e-10 for 1.63M -> 2.29M steps,
+      // 1.40 -> 1.91 s.
       S->in_tol2 = fmax(e.inner_eta2 * n2, 0.0625 * thr);
       if (e.chip_words > 0 && e.inner_eta2 > 0.0 && e.inner_eta2 * n2 <= 4.0 * thr) S->in_tol2 = thr / 256.0;
     }

@@ -19,16 +19,19 @@
 //   sums of all G blocks; alpha, beta, stop test (every block by itself)
 // so a step waits once for the other blocks.
 //
-// Bound: VALU issue (42 instructions a point and step, and about 250 a
-// wavefront) plus one exchange between the blocks a step: 4.4 us a step for
-// 256^2 in FP64 (16 blocks), 5.7 us for 512^2 in FP32 (32 blocks), of which
-// about 2.0 and 3.0 us are VALU.  Measured whole calls, passes -> chip: 64^2
-// t rho 100 FP64 7.3 -> 1.4 ms, 130 x 66 with velocities t rho 150 56.7 ->
-// 13.5 ms, 256^2 t rho 300 FP64 225 to 296 -> 70 ms, 512^2 t rho 250 mixed
-// 504 to 543 -> 175 ms (the passes run at 5.5 TB/s of HBM there).  Tried and
-// left out: two blocks of 256 threads a CU (10 to 25% slower), four
-// wavefronts a SIMD at 128 registers (spills), the edge rows' state in LDS
-// (3 to 6% slower), sleeps in the waits and raised wave priority (no change).
+// Bound: VALU issue (44 instructions a point and step and 280 a wavefront in
+// FP32, 42 and 240 in FP64, counted) plus one exchange between the blocks a
+// step: 1.8 us a step for 64^2 in FP64 (one block, no exchange), 4.5 us for
+// 256^2 in FP64 (16 blocks of one XCD), 5.8 us for 512^2 in FP32 (32 blocks),
+// 7.5 us for 512^2 in FP64 (64 blocks across XCDs), and 15 to 60 us a launch;
+// 1.9 and 3.3 us of the middle two are VALU.  Measured whole calls, passes ->
+// chip: 64^2 t rho 100 FP64 7.3 -> 1.3 ms, 130 x 66 with velocities t rho 150
+// 55 -> 12.8 ms, 256^2 t rho 300 FP64 241 to 274 -> 77 to 79 ms, 512^2 t rho
+// 250 mixed, tol 1e-7 513 to 537 -> 210 to 214 ms (the passes run at 5.5 TB/s
+// of HBM there, and end their last rounds earlier).  Tried and left out: two
+// blocks of 256 threads a CU (10 to 25% slower), four wavefronts a SIMD at 128
+// registers (spills), the edge rows' state in LDS (3 to 6% slower), sleeps in
+// the waits and raised wave priority (no change).
 //
 // Communication between the blocks of a group: agent-scope stores and loads.
 // A mailbox word (a sum of a block's record, or part of an edge value) holds
@@ -579,8 +582,13 @@ struct ChipFn {
   void (*fn)(Eng, Chip);
 };
 #define CHIP(T, Q, RT, NT, W) {{Q, RT, NT}, k_chip<T, Q, RT, NT, W>}
-// 1024 threads leave 128 registers a thread, 512 leave 256: r, d and q take
-// 6 (FP32) or 12 (FP64) a point
+// 512 threads leave 256 registers a thread; r, d and q take 6 (FP32) or 12
+// (FP64) a point, so 23 or 8 rows of one column.  Two columns a thread (Q = 2)
+// serve rows of 513 to 1024 points, which one column of 512 threads cannot
+// hold, and 512^2, where 8 rows of two columns put a solve on 32 blocks as 16
+// rows of one do: only the FP32 shape of 8 rows was built, so grids of more
+// than 512 columns with more than 512 rows (64 blocks), and every FP64 grid
+// past 512 columns, are streamed.
 const ChipFn kChipF32[] = {
     CHIP(float, 1, 2, 512, 2),
     CHIP(float, 1, 3, 512, 2),

@@ -15,10 +15,12 @@
 // pass 2 is u = sum_j y_j v_j over the kept vectors (k_lz_gather, 24 bytes a
 // point and vector) and, for the others, the same steps once more with
 // u += y_j v_j (128 bytes a point and step).  Every step twice and the small
-// problem on the host took 44.1 ms at 512^2, t rho = 1000 (17.3 ms now) and
-// 27.1 ms for the 2048^2 depth field at t rho = 100 (13.3 ms now, the sum of
-// 160 vectors 2.8 ms at 5.8 TB/s).  The reductions are in a fixed
-// order, so repeated steps reproduce pass 1 bit for bit.
+// problem on the host took 44.1 ms at 512^2, t rho = 1000 (17.3 ms with the
+// vectors kept, 12.0 with the steps on the chip, below) and 27.1 ms for the
+// 2048^2 depth field at t rho = 100 (13.3 to 15.4 ms now, the sum of 160
+// vectors 2.8 ms at 5.8 TB/s).  The reductions are in a fixed order, so
+// repeated steps reproduce pass 1 bit for bit (a step whose vector is not kept
+// is k_lz_step in both passes).
 //
 // Storage: the vectors are kept unnormalised, buf_j = beta_{j-1} v_j
 // (buf_1 = f, beta_0 = ||f||_W); step j reads buf_j and buf_{j-1} and writes

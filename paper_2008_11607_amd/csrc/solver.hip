@@ -759,13 +759,16 @@ static size_t chip_ring_bytes(int groups, int G, int Gc, int nx, int eb) {
 //   or G = nch Gc with Gc strips per chain.  A thread takes Q column segments
 //   of RT (or RT - 1) chain rows, so RT = ceil(L / (Gc Sc)).
 // Among the shapes that fit, the least estimated time of a step times the
-// turns that the queue takes.  The estimate, in cycles, follows steps timed
-// on MI355X: a wavefront issues about 50 VALU instructions a point and 350 a
-// step (4 cycles each), and a step waits beyond that 2300 cycles in a group
-// of one (3.5 us a step for 64^2 in FP64, 8 rows a thread), 5400 + 40 G on
-// one XCD (4.9 us for 256^2 in FP64 with G = 16, 6.6 us for 512^2 in FP32
-// with G = 32 and 16 rows), 6000 + 110 G across XCDs (8.1 us for 512^2 in
-// FP64 with G = 64).
+// turns that the queue takes.  The estimate, in cycles, was fitted to whole
+// calls on MI355X: a wavefront issues 50 instructions a point and 350 a step (4
+// cycles each; counted: 42 to 44 and 240 to 280), and a step waits beyond that
+// 2300 cycles in a group of one, 5400 + 40 G on one XCD, 6000 + 110 G across
+// XCDs, which include a launch's share of loads and stores (alone: 1.8 us a
+// step for 64^2 in FP64 with one block, 4.5 for 256^2 in FP64 with 16 on one
+// XCD, 5.8 for 512^2 in FP32 with 32, 7.5 for 512^2 in FP64 with 64 across).
+// Against twelve other shapes each, for five grids of 33 x 65 to 128 x 96 at t
+// rho 20 and 60, calls with the shape chosen took 1.00 to 1.29 times the best
+// (1.10 in the mean).
 static bool chip_config(int nx, int ny, int is_f32, int cus, int nsolves, Chip* out) {
   const int nch = (ny % 2 == 0) ? 2 : 1, L = ny / nch;
   const int eb = is_f32 ? 8 : 16;
