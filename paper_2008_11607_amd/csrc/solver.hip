@@ -2733,7 +2733,8 @@ static FarBoxes fourier_boxes(const rexii_swe_op* op, double t, int deriv, doubl
 // would work many more points than the length has: over 1024, and 513..1024
 // at under a third of its points, in y, or in x beside another chirp.
 // Measured (call, rocFFT -> own, us): 701 x 310 262 -> 110, 1501 x 1201
-// 1398 -> 362, 125^2 86 -> 56, 384^2 84 -> 76, 700 x 900 171 -> 163, 1920 x
+// 1398 -> 362, 125^2 86 -> 56, 36 small sizes of 16 to 320 points 42..83 -> 42..65,
+// but 20^2 43 -> 46, 384^2 84 -> 76, 700 x 900 171 -> 163, 1920 x
 // 1024 249 -> 221, 512^2 93 -> 73, 2048^2 510 -> 286, 4096^2 1776 -> 1077; the
 // other side of the line: 600^2 120 -> 128, 512 x 1080 149 -> 148, 1200^2
 // 215 -> 295, 1536^2 287 -> 371, 2000^2 457 -> 467.
